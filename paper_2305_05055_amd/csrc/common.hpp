@@ -75,6 +75,28 @@ __device__ __forceinline__ uint64_t lane63_u64(uint64_t v) {
   return ((uint64_t)hi << 32) | lo;
 }
 
+// A value every lane holds alike (or the first active lane's), in scalar registers.
+__device__ __forceinline__ uint64_t uniform64(uint64_t v) {
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)v);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(v >> 32));
+  return ((uint64_t)hi << 32) | lo;
+}
+
+// The lane id as a value the compiler cannot see through, and a read of lane
+// `from`'s v.  Lane-dependent shuffle addresses are loop-invariant and would
+// otherwise all be kept in registers across the loops they sit in.
+__device__ __forceinline__ uint32_t opaque_lane() {
+  uint32_t l = (uint32_t)lane_id();
+  asm volatile("" : "+v"(l));
+  return l;
+}
+__device__ __forceinline__ uint32_t from_lane(uint32_t v, uint32_t from) {
+  return (uint32_t)__builtin_amdgcn_ds_bpermute((int)(4u * from), (int)v);
+}
+__device__ __forceinline__ uint64_t from_lane(uint64_t v, uint32_t from) {
+  return ((uint64_t)from_lane((uint32_t)(v >> 32), from) << 32) | from_lane((uint32_t)v, from);
+}
+
 // ---- wave-level scans / reductions (64 lanes, DPP) ---------------------------------
 template <typename T>
 __device__ __forceinline__ T wave_incl_scan(T v) {

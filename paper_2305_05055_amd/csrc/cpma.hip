@@ -140,7 +140,7 @@ struct cpma {
   DevBuf kin, kb0, kb1, kdedup, leafid, segpos, seg_leaf, seg_begin, seg_desc, heavy, spill, scan_tmp, ovf, arena,
       stage, pyr, win, wargs, cnt, koff, win_id, welem, P, ccost, ncost, lstart, planU, plan_used,
       spare_bytes, spare_used, spare_head, fg_level, fg_deg, fg_p, fg_c, fg_acc,
-      win_of_leaf, fail, qa, qb, qfirst, qnvis, qvoff, qsum, qcount, qout, lastk, lckpt, ne_rank, ne_list, chain_pfx,
+      win_of_leaf, fail, qa, qb, qfirst, qnvis, qvoff, qsum, qcount, qout, qprefix, lastk, lckpt, ne_rank, ne_list, chain_pfx,
       srec, wide, srcinfo, parts, qparts, fz_meta, fz_v0, fz_v1, fz_byte, fz_member, fz_code, fz_ctr, fz_res,
       ctr_buf, info_buf, qalg_buf, clen, spare_clen, vstage, kvals, kvdedup;
   // key-value sets: the current update batch's values (device, repeat-free and
@@ -184,7 +184,7 @@ struct cpma {
             &qout,      &lastk,     &ne_rank,   &ne_list,     &chain_pfx,  &srec,        &wide,       &srcinfo,
             &parts,     &qparts,    &fz_meta,   &fz_v0,       &fz_v1,      &fz_byte,     &fz_member,  &fz_code,
             &fz_ctr,    &fz_res,    &ctr_buf,   &info_buf,    &qalg_buf,   &lckpt,      &clen,        &spare_clen,
-            &vstage,    &kvals,     &kvdedup};
+            &vstage,    &kvals,     &kvdedup,   &qprefix};
   }
 
   Bounds bounds(uint64_t Lx) const {
@@ -2085,11 +2085,52 @@ static uint32_t interior_blocks(const cpma* s, const QueryArgs& a) {
 }
 static void launch_interior(const QueryArgs& a, uint32_t blocks, hipStream_t st, const uint64_t* voff,
                             const uint64_t* first, uint32_t chunk, unsigned long long* dsum, unsigned long long* dcount,
-                            unsigned long long* alg) {
+                            unsigned long long* alg, const LeafPrefix& lp) {
   if (a.zero_fill && !a.raw && !a.vals)
-    hipLaunchKernelGGL(k_rm_interior<true>, dim3(blocks), dim3(256), 0, st, a, voff, first, chunk, dsum, dcount, alg);
+    hipLaunchKernelGGL(k_rm_interior<true>, dim3(blocks), dim3(256), 0, st, a, voff, first, chunk, dsum, dcount, alg,
+                       lp);
   else
-    hipLaunchKernelGGL(k_rm_interior<false>, dim3(blocks), dim3(256), 0, st, a, voff, first, chunk, dsum, dcount, alg);
+    hipLaunchKernelGGL(k_rm_interior<false>, dim3(blocks), dim3(256), 0, st, a, voff, first, chunk, dsum, dcount, alg,
+                       lp);
+  if (lp.ps && a.q > kPrefixInline)
+    hipLaunchKernelGGL(k_rm_prefix_apply, dim3(grid_for(a.q, 256, 1024)), dim3(256), 0, st, a, voff, first, lp, blocks,
+                       dsum, dcount);
+}
+
+// Memory of the leaf prefixes for a batch of q queries, kept across calls
+// (about 13 bytes per leaf): none for a single query, which never visits a leaf
+// twice, nor when it cannot be had (the scan then visits leaf by leaf).  A
+// handful of queries rarely visits more leaves than the set has: it uses the
+// memory when it is there but does not take it (45 us in a first call).
+constexpr uint64_t kPrefixMinQueries = 32;
+static LeafPrefix leaf_prefix(cpma* s, uint64_t q, uint32_t blocks, hipStream_t st) {
+  LeafPrefix lp{};
+  if (q < 2 || blocks > kPrefixRuns) return lp;
+  const uint64_t steps = (s->L + kStepLeaves - 1) / kStepLeaves;
+  lp.range = (uint32_t)((steps + blocks - 1) / blocks) * kStepLeaves;
+  const size_t need = s->L * 12 + steps * 16 + blocks * 16 + 64;
+  if (s->qprefix.cap < need) {
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (q < kPrefixMinQueries) return lp;
+    if (hipStreamIsCapturing(st, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) {
+      hipGetLastError();
+      return lp;
+    }
+    try {
+      ensure(s->qprefix, need, 0.25);
+    } catch (const Fail& f) {
+      if (f.st != CPMA_ERR_NOMEM) throw;
+      return lp;
+    }
+  }
+  lp.ticket = s->qprefix.as<unsigned int>();
+  lp.ps = s->qprefix.as<uint64_t>() + 1;
+  lp.ss = lp.ps + s->L;
+  lp.sc = lp.ss + steps;
+  lp.ts = lp.sc + steps;
+  lp.tc = lp.ts + blocks;
+  lp.pc = reinterpret_cast<uint32_t*>(lp.tc + blocks);
+  return lp;
 }
 
 static QueryArgs query_args(const cpma* s) {
@@ -2150,6 +2191,7 @@ static cpma_status range_map_impl(const cpma* cs, const uint64_t* lo, const uint
     const uint64_t ewaves = wave_ends ? egrid : 4ull * egrid;
     const uint32_t blocks = interior_blocks(s, a);
     const uint64_t nslots = ewaves + 4ull * blocks;
+    const LeafPrefix lp = leaf_prefix(s, q, blocks, st);
     unsigned long long* qalg = nullptr;
     if (s->stats_on && ((s->stats_mask >> CPMA_PHASE_RANGE_SCAN) & 1u)) {
       ensure(s->qparts, 8 * nslots);
@@ -2157,15 +2199,15 @@ static cpma_status range_map_impl(const cpma* cs, const uint64_t* lo, const uint
     }
     if (wave_ends)
       hipLaunchKernelGGL(k_rm_ends_wave, dim3(egrid), dim3(kWave), 0, st, a, s->qfirst.as<uint64_t>(),
-                         s->qnvis.as<uint64_t>(), dsum, dcount, qalg);
+                         s->qnvis.as<uint64_t>(), dsum, dcount, qalg, lp.ticket);
     else
       hipLaunchKernelGGL(k_rm_ends, dim3(egrid), dim3(256), 0, st, a, s->qfirst.as<uint64_t>(),
-                         s->qnvis.as<uint64_t>(), dsum, dcount, qalg);
+                         s->qnvis.as<uint64_t>(), dsum, dcount, qalg, lp.ticket);
     HIPCHK(hipGetLastError());
     scan<uint64_t>(s, s->qvoff.as<uint64_t>(), q, st, LoadFn<uint64_t>{s->qnvis.as<uint64_t>()});
     PhaseMark ps = phase_begin(s, CPMA_PHASE_RANGE_SCAN, st);
     launch_interior(a, blocks, st, s->qvoff.as<uint64_t>(), s->qfirst.as<uint64_t>(), s->cfg.range_chunk, dsum,
-                    dcount, qalg ? qalg + ewaves : qalg);
+                    dcount, qalg ? qalg + ewaves : qalg, lp);
     HIPCHK(hipGetLastError());
     phase_end(s, ps, st, 32ull * q);
     phase_end(s, pq, st);
@@ -2290,13 +2332,14 @@ cpma_status cpma_range_map_noalloc(const cpma* cs, const uint64_t* lo, const uin
                                      : grid_for(q, 256, (uint32_t)s->num_cus * 16);
     if (wave_ends)
       hipLaunchKernelGGL(k_rm_ends_wave, dim3(egrid), dim3(kWave), 0, st, a, first, nvis, dsum, dcount,
-                         (unsigned long long*)nullptr);
+                         (unsigned long long*)nullptr, (unsigned int*)nullptr);
     else
       hipLaunchKernelGGL(k_rm_ends, dim3(egrid), dim3(256), 0, st, a, first, nvis, dsum, dcount,
-                         (unsigned long long*)nullptr);
+                         (unsigned long long*)nullptr, (unsigned int*)nullptr);
     HIPCHK(hipGetLastError());
     HIPCHK(scan_exclusive<uint64_t>(LoadFn<uint64_t>{nvis}, q, voff, tmp, st));
-    launch_interior(a, interior_blocks(s, a), st, voff, first, s->cfg.range_chunk, dsum, dcount, nullptr);
+    launch_interior(a, interior_blocks(s, a), st, voff, first, s->cfg.range_chunk, dsum, dcount, nullptr,
+                    LeafPrefix{});
     HIPCHK(hipGetLastError());
   });
 }

@@ -54,7 +54,8 @@ __global__ void __launch_bounds__(256) k_rm_ends(QueryArgs a, uint64_t* __restri
                                                  uint64_t* __restrict__ nint,
                                                  unsigned long long* __restrict__ sum,
                                                  unsigned long long* __restrict__ count,
-                                                 unsigned long long* __restrict__ alg) {
+                                                 unsigned long long* __restrict__ alg, unsigned int* ticket) {
+  if (ticket && blockIdx.x == 0 && threadIdx.x == 0) *ticket = 0;  // for k_rm_interior's prefix pass
   uint64_t visited = 0;
   for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < a.q;
        i += (uint64_t)gridDim.x * blockDim.x) {
@@ -125,7 +126,8 @@ __global__ void __launch_bounds__(kWave) k_rm_ends_wave(QueryArgs a, uint64_t* _
                                                         uint64_t* __restrict__ nint,
                                                         unsigned long long* __restrict__ sum,
                                                         unsigned long long* __restrict__ count,
-                                                        unsigned long long* __restrict__ alg) {
+                                                        unsigned long long* __restrict__ alg, unsigned int* ticket) {
+  if (ticket && blockIdx.x == 0 && threadIdx.x == 0) *ticket = 0;
   uint64_t visited = 0;
   for (uint64_t i = blockIdx.x; i < a.q; i += gridDim.x) {
     const uint64_t lo = a.lo[i], hi = a.hi[i];
@@ -158,100 +160,403 @@ __global__ void __launch_bounds__(kWave) k_rm_ends_wave(QueryArgs a, uint64_t* _
   if (alg && lane_id() == 0) alg[blockIdx.x] = visited;
 }
 
-// Sum and count of one interior leaf (a leaf every key of which is in its
-// query's range), for any leaf format.
-template <bool kPlain>
-__device__ __forceinline__ LeafSum interior_leaf(const QueryArgs& a, uint64_t leaf, uint32_t u) {
-  const uint8_t* lp = a.bytes + leaf * (uint64_t)a.S;
-  const uint64_t h = a.head[leaf];
-  const uint64_t span = a.head[leaf + 1] - h;  // interior leaves always have a successor
-  if constexpr (kPlain) {
-    return span < (1ull << 28) ? leaf_sum_zf(lp, u, h) : leaf_sum_range(lp, u, 0, kNoKey);
-  } else {
-    if (a.vals) {
-      // the values: m 8-byte words ending at the leaf's end (8-byte aligned)
-      const uint32_t m = (a.fill[leaf] - u) / 8;
-      const uint64_t* w = reinterpret_cast<const uint64_t*>(lp + a.S - 8u * m);
-      uint64_t s0 = 0, s1 = 0;
-      uint32_t i = 0;
-      for (; i + 2 <= m; i += 2) {
-        s0 += w[i];
-        s1 += w[i + 1];
+// ---- whole leaves, 32 per wave ------------------------------------------------------
+// Sums and counts of whole leaves, two lanes per leaf (the wave's 32 leaves need
+// not be neighbours; lanes 2i and 2i + 1 pass the same leaf and `valid`).  A
+// leaf must have a successor, whose head bounds its key span.  The result is in
+// the even lane; the odd lane returns zeros.
+//
+// The leaf's 64-byte rounds are split between its two lanes.  A key's offset
+// from the head is the sum of the payloads of every code byte before it, each
+// shifted by 7 times its place in its code, so a lane sums its own terminators'
+// offsets from zero, and the second lane adds the first one's total to each of
+// its keys.  The shift a code carries into the second half is 7 times the run
+// of continuation bytes just before it (at most 4: within a span of 2^32 a code
+// has at most 5 bytes).  Two lanes halve the chain of dependent rounds, which
+// bounds a scan of few leaves, and give a set of 4e5 leaves twice as many waves.
+//
+// A round is loaded for the whole wave, four lanes to one lane's 64 bytes, and
+// handed over through LDS (`stage`, 4 KiB per wave): each 64-byte line is
+// requested once.  Lanes that load their own bytes, 16 at a time, ask the L1
+// for each line four times, and a wave's 64 lines have often left it in
+// between (3.4 times the set's bytes came over from L2 that way).  The slots
+// are permuted so that the 16 lanes of an LDS access cycle cover all banks.
+// The next round's loads are in flight while one is decoded.  Bound: VALU
+// issue, 7.3 instructions per byte of the decode.
+constexpr uint32_t kStageBytes = 64u * kWave;
+constexpr uint32_t kStepLeaves = kWave / 2;
+
+template <bool kZero, bool kWide>
+__device__ __forceinline__ LeafSum wave_code_sums(const QueryArgs& a, uint32_t leaf, uint64_t head, uint32_t used,
+                                                  uint8_t* stage) {
+  const uint32_t lane = (uint32_t)lane_id(), r = lane & 1u;
+  const uint32_t half = (used + 127u) >> 7;              // rounds of the first lane
+  const uint32_t own = r ? ((used + 63u) >> 6) - half : half;
+  const uint32_t start = r ? 64u * half : 0u;
+  const uint32_t R = lane63_u32(dpp_incl_max(half));
+  // this lane loads, for run 16 j + lane / 4, the chunk that goes to slot lane % 4
+  const uint8_t* src[4];
+  uint32_t cnt[4];
+  const uint32_t ol = opaque_lane();
+#pragma unroll
+  for (uint32_t j = 0; j < 4; j++) {
+    const uint32_t o = 16u * j + (ol >> 2);
+    const uint32_t lf = from_lane(leaf, o);
+    const uint32_t w = from_lane(start | (own << 16), o);
+    cnt[j] = w >> 16;
+    src[j] = a.bytes + (uint64_t)lf * a.S + (w & 0xffffu) + 16u * ((ol & 3u) ^ ((o >> 2) & 3u));
+  }
+  uint32_t before = 0;
+  if (r && own) before = *reinterpret_cast<const uint32_t*>(a.bytes + leaf * (uint64_t)a.S + start - 4);
+  uint4 nx[4];
+#pragma unroll
+  for (uint32_t j = 0; j < 4; j++) {
+    nx[j] = make_uint4(0, 0, 0, 0);
+    if (cnt[j]) nx[j] = load16(src[j]);
+  }
+  // leading ones of the four bytes' high bits, from the last byte backwards
+  const uint32_t ends = ~before & 0x80808080u;
+  uint32_t D = 0, cont = 0;
+  uint32_t sh = r ? 7u * (ends ? (uint32_t)__clz((int)ends) >> 3 : 4u) : 0u;
+  uint64_t Sc = 0;
+  uint4* const put = reinterpret_cast<uint4*>(stage) + lane;
+  const uint4* const get = reinterpret_cast<const uint4*>(stage) + 4u * lane;
+  const uint32_t perm = (lane >> 2) & 3u;
+#pragma unroll 1
+  for (uint32_t t = 0; t < R; t++) {
+#pragma unroll
+    for (uint32_t j = 0; j < 4; j++) put[kWave * j] = nx[j];
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+    uint4 w = get[perm];
+#pragma unroll
+    for (uint32_t j = 0; j < 4; j++)
+      if (t + 1 < cnt[j]) nx[j] = load16(src[j] + 64u * (t + 1));
+    if (t < own) {
+      if (t == 0 && r == 0) {
+        // the head's eight bytes: seven continuation bytes without payload
+        // and a terminator, so one key at offset 0
+        w.x = 0x80808080u;
+        w.y = 0x00808080u;
       }
-      if (i < m) s0 += w[i];
-      return LeafSum{s0 + s1, m};
+#pragma unroll
+      for (uint32_t c = 0; c < 4; c++) {
+        // one chunk's bytes at a time: the scheduler would otherwise spread all
+        // four over the registers and cost a wave of occupancy
+        const uint4 ahead = get[(c < 3 ? c + 1 : c) ^ perm];
+        __builtin_amdgcn_sched_barrier(0);
+        if constexpr (!kZero) {
+          // bytes at or past `used` (values may lie there) become 0x80
+          const int32_t nv = (int32_t)used - (int32_t)(start + 64u * t + 16u * c);
+          if (nv < 16) {
+            uint32_t x[4] = {w.x, w.y, w.z, w.w};
+#pragma unroll
+            for (int k = 0; k < 4; k++) {
+              const int32_t v = nv - 4 * k;
+              const uint32_t keep = v >= 4 ? 0xffffffffu : (v <= 0 ? 0u : ((1u << (8 * v)) - 1u));
+              x[k] = (x[k] & keep) | (0x80808080u & ~keep);
+            }
+            w = make_uint4(x[0], x[1], x[2], x[3]);
+          }
+        }
+        zf_chunk<kWide>(w, D, sh, Sc, cont);
+        w = ahead;
+      }
     }
-    return a.raw                ? raw_sum_all(lp, u)
-           : span >= (1ull << 28) ? leaf_sum_range(lp, u, 0, kNoKey)
-                                  : leaf_sum_fast(lp, u, h);
+    __builtin_amdgcn_wave_barrier();  // the next round's writes follow every lane's reads
+  }
+  uint32_t keys = 64u * own - cont;
+  if constexpr (kZero) {
+    // bytes past `used` are zero; each decoded as a zero delta, one more copy of the last key
+    const uint32_t from = max(used, start), end = start + 64u * own;
+    const uint32_t zeros = own && end > from ? end - from : 0u;
+    keys -= zeros;
+    Sc -= (uint64_t)zeros * D;
+  }
+  constexpr int kXor1 = 1 | (0 << 2) | (3 << 4) | (2 << 6);  // DPP quad permutation: the pair's other lane
+  const uint32_t D0 = dpp32<kXor1>(D);
+  uint64_t s = Sc + (uint64_t)keys * (head + (r ? D0 : 0u));
+  s += dpp64<kXor1>(s);
+  keys += dpp32<kXor1>(keys);
+  return r ? LeafSum{0, 0} : LeafSum{s, keys};
+}
+
+// Sums of 8-byte words of 32 leaves (lane 2i, and 2i + 1 alike: m words at byte
+// `at` of `leaf`), eight lanes per leaf and eight leaves at a time.
+__device__ __forceinline__ LeafSum wave_word_sums(const QueryArgs& a, uint32_t leaf, uint32_t at, uint32_t m) {
+  const uint32_t l = opaque_lane();
+  LeafSum out{0, 0};
+#pragma unroll 1
+  for (uint32_t it = 0; it < 4; it++) {
+    const uint32_t from = 16u * it + 2u * (l >> 3);
+    const uint64_t lf = from_lane(leaf, from);
+    const uint32_t n = from_lane(m, from);
+    const uint64_t* w = reinterpret_cast<const uint64_t*>(a.bytes + lf * a.S + from_lane(at, from));
+    uint64_t s = 0;
+    uint32_t i = l & 7u;
+    for (; i + 24 < n; i += 32) s += (w[i] + w[i + 8]) + (w[i + 16] + w[i + 24]);
+    for (; i < n; i += 8) s += w[i];
+    constexpr int kXor1 = 1 | (0 << 2) | (3 << 4) | (2 << 6), kXor2 = 2 | (3 << 2) | (0 << 4) | (1 << 6);
+    s += dpp64<kXor1>(s);
+    s += dpp64<kXor2>(s);
+    s += dpp64<0x141>(s);  // the row's other quad of the eight
+    const uint64_t mine = from_lane(s, 4u * (l & 14u));
+    if ((l >> 4) == it && !(l & 1u)) out = LeafSum{mine, m};
+  }
+  return out;
+}
+
+template <bool kPlain>
+__device__ __forceinline__ LeafSum wave_leaf_sums(const QueryArgs& a, uint32_t leaf, bool valid, uint8_t* stage,
+                                                  uint32_t& visited) {
+  const uint32_t r = (uint32_t)lane_id() & 1u;
+  const uint32_t u = valid ? a.used[leaf] : 0u;
+  if (!r) visited += u;
+  if constexpr (!kPlain) {
+    if (a.vals || a.raw) {
+      // 8-byte words: the values at the leaf's end, or the keys from its start
+      const uint32_t m = !valid ? 0u : (a.vals ? (a.fill[leaf] - u) / 8 : u / 8);
+      return wave_word_sums(a, leaf, a.vals ? a.S - 8u * m : 0u, m);
+    }
+  }
+  const uint64_t h = u ? a.head[leaf] : 0;
+  const uint64_t span = u ? a.head[leaf + 1] - h : 0;
+  // three classes of leaves, each decoded at once: 32-bit sums of a chunk's
+  // offsets, 64-bit sums, and keys walked in 64 bits by one lane
+  LeafSum x = wave_code_sums<kPlain, false>(a, leaf, h, span < (1ull << 28) ? u : 0u, stage);
+  if (__ballot(span >= (1ull << 28))) {
+    const bool wide = span >= (1ull << 28) && span < (1ull << 32);
+    const LeafSum y = wave_code_sums<kPlain, true>(a, leaf, h, wide ? u : 0u, stage);
+    if (wide) x = y;
+    if (span >= (1ull << 32) && !r) x = leaf_sum_range(a.bytes + leaf * (uint64_t)a.S, u, 0, kNoKey);
+  }
+  return x;
+}
+
+// Per-leaf prefix sums, for a batch of queries that visits more interior leaves
+// than the set has: every leaf is then summed once and a query's interior is
+// the difference of two prefixes, exact in wrapping 64-bit arithmetic.  A block
+// takes one run of `range` leaves, its waves 32 leaves at a time.
+//   ps / pc: exclusive prefix of the leaf sums / counts inside the 32 leaves;
+//   ss / sc: the 32 leaves' totals, then their exclusive prefix in the run;
+//   ts / tc: the runs' totals, then their exclusive prefix.
+// ps NULL: no memory for it, visit leaf by leaf.  10^6 Zipf(1.2) queries on
+// 10^8 keys visit 1.4e10 / 270 leaves: 7.28 ms leaf by leaf.
+struct LeafPrefix {
+  uint64_t *ps, *ss, *ts, *sc, *tc;
+  uint32_t* pc;
+  unsigned int* ticket;  // blocks done; zeroed by the end-leaf kernel
+  uint32_t range;        // a multiple of 32
+};
+// Up to this many queries the last block of the prefix pass applies the
+// prefixes itself, which saves the launch of k_rm_prefix_apply (2.5 us, also
+// when the visits were few) but costs every block an agent-scope release, a
+// write-back of its XCD's L2 (25 us in all on a full grid, 110 us when every
+// wave did one).
+constexpr uint64_t kPrefixInline = 64;
+constexpr uint32_t kPrefixRuns = 2048;  // blocks of the prefix pass, at most
+
+__device__ __forceinline__ LeafSum prefix_at(const LeafPrefix& lp, const uint64_t* ts, const uint64_t* tc,
+                                              uint64_t f) {
+  const uint32_t run = (uint32_t)f / lp.range;
+  return LeafSum{lp.ps[f] + lp.ss[f / kStepLeaves] + ts[run], lp.pc[f] + lp.sc[f / kStepLeaves] + tc[run]};
+}
+
+__device__ __forceinline__ void prefix_apply(const LeafPrefix& lp, const uint64_t* ts, const uint64_t* tc,
+                                             uint64_t first, uint64_t n, uint64_t i, unsigned long long* sum,
+                                             unsigned long long* count) {
+  const LeafSum e = prefix_at(lp, ts, tc, first + n), b = prefix_at(lp, ts, tc, first);
+  sum[i] += e.sum - b.sum;
+  count[i] += e.count - b.count;
+}
+
+// Exclusive scan of v[0, n) and w[0, n) in place by a block of 256 threads;
+// returns the totals.
+__device__ __forceinline__ LeafSum block_scan_pairs(uint64_t* v, uint64_t* w, uint64_t n, uint64_t (*red)[4]) {
+  const uint32_t tid = threadIdx.x, wid = tid / kWave;
+  LeafSum run{0, 0};
+  for (uint64_t base = 0; base < n; base += 1024) {
+    const uint64_t i0 = base + 4 * tid;
+    uint64_t x[4], y[4], s = 0, c = 0;
+#pragma unroll
+    for (int j = 0; j < 4; j++) {
+      x[j] = i0 + j < n ? v[i0 + j] : 0;
+      y[j] = i0 + j < n ? w[i0 + j] : 0;
+    }
+#pragma unroll
+    for (int j = 0; j < 4; j++) {
+      s += x[j];
+      c += y[j];
+    }
+    const uint64_t is = wave_incl_scan(s), ic = wave_incl_scan(c);
+    __syncthreads();
+    if (lane_id() == kWave - 1) {
+      red[0][wid] = is;
+      red[1][wid] = ic;
+    }
+    __syncthreads();
+    uint64_t ps = run.sum + is - s, pc = run.count + ic - c;
+#pragma unroll
+    for (uint32_t k = 0; k < 4; k++) {
+      if (k < wid) {
+        ps += red[0][k];
+        pc += red[1][k];
+      }
+      run.sum += red[0][k];
+      run.count += red[1][k];
+    }
+#pragma unroll
+    for (int j = 0; j < 4; j++) {
+      if (i0 + j < n) {
+        v[i0 + j] = ps;
+        w[i0 + j] = pc;
+      }
+      ps += x[j];
+      pc += y[j];
+    }
+  }
+  return run;
+}
+
+// The end of the prefix pass, after a block's waves have written their leaves:
+// the run's prefix, and for few queries, in the last block to finish, the rest.
+__device__ __forceinline__ void leaf_prefix_finish(const QueryArgs& a, const LeafPrefix& lp,
+                                                   const uint64_t* __restrict__ ioff,
+                                                   const uint64_t* __restrict__ first_int,
+                                                   unsigned long long* __restrict__ sum,
+                                                   unsigned long long* __restrict__ count, uint64_t f0, uint64_t f1) {
+  __shared__ uint64_t red[2][4];
+  __shared__ bool last;
+  const uint32_t tid = threadIdx.x;
+  __threadfence_block();
+  __syncthreads();
+  const uint64_t g0 = f0 / kStepLeaves, g1 = (f1 + kStepLeaves - 1) / kStepLeaves;
+  const LeafSum t = f0 < f1 ? block_scan_pairs(lp.ss + g0, lp.sc + g0, g1 - g0, red) : LeafSum{0, 0};
+  if (tid == 0) {
+    lp.ts[blockIdx.x] = t.sum;
+    lp.tc[blockIdx.x] = t.count;
+  }
+  if (a.q > kPrefixInline) return;
+  __syncthreads();
+  if (tid == 0) {
+    __threadfence();  // after the barrier: the whole block's writes
+    last = atomicAdd(lp.ticket, 1u) + 1u == gridDim.x;
+  }
+  __syncthreads();
+  if (!last) return;
+  __threadfence();
+  block_scan_pairs(lp.ts, lp.tc, gridDim.x, red);
+  __threadfence_block();
+  __syncthreads();
+  for (uint64_t i = tid; i < a.q; i += 256) {
+    const uint64_t n = ioff[i + 1] - ioff[i];
+    if (n) prefix_apply(lp, lp.ts, lp.tc, first_int[i], n, i, sum, count);
   }
 }
 
-// Interior visits, flattened over all queries.  The visits are cut into steps
-// of 64, and waves take groups of `chunk` consecutive steps, group g by wave
-// g mod (number of waves).  At a step, lane l decodes visit base + l, so the
-// wave's loads fall on 64 neighbouring leaves, and the waves running at the
-// same time sweep one region of the leaf array together.  (Giving each lane
-// `chunk` consecutive leaves instead spreads one load instruction over 64 *
-// chunk leaves, and the memory system delivers markedly fewer bytes per second
-// for that pattern.)  The query of a step's first visit is found by one binary
-// search over the visit offsets, with wave-uniform (scalar) loads; each lane
-// then walks forward to its own visit's query.  Partial sums are exact
-// integers, so they may be combined in any order:
-//  * while every lane's visit belongs to the same query, each lane adds its
+// Interior visits, flattened over all queries.  When they outnumber the leaves,
+// every leaf is summed once into the prefixes above, a block taking one run of
+// leaves.  Otherwise waves take groups of consecutive visits, group g by wave g mod (number of waves): `chunk` steps of
+// 64 leaves, fewer when that would leave waves idle.  Part of a group: 32 visits,
+// two lanes each, so the wave's loads fall on neighbouring leaves, and the waves
+// running at the same time sweep one region of the leaf array together.  The
+// query of a group's first visit is found by one binary search over the visit
+// offsets, with wave-uniform (scalar) loads; each lane then walks forward to its
+// own visit's query, and the next part continues from there.  Partial sums are
+// exact integers, so they may be combined in any order:
+//  * while every visit of a part belongs to the same query, each lane adds its
 //    leaf to a running share; the shares are summed across the wave and
 //    flushed with one pair of 64-bit atomics when the query changes;
-//  * a step whose lanes span several queries is reduced at once by query
+//  * a part whose lanes span several queries is reduced at once by query
 //    (visits ascend with the lane, so equal queries sit in runs of lanes), one
 //    pair of atomics per run -- a query spanning millions of leaves would
 //    otherwise serialise on one address.
 //
-// kPlain: compressed leaves without values (zero past `used`), decoded with
-// leaf_sum_zf; this instance also keeps the register count of the other
-// formats' decoders out of the hot kernel.
+// kPlain: compressed leaves without values (zero past `used`); this instance
+// also keeps the register count of the other formats' decoders out of the hot
+// kernel.
 template <bool kPlain>
-__global__ void __launch_bounds__(256) k_rm_interior(QueryArgs a, const uint64_t* __restrict__ ioff,
+__global__ void __launch_bounds__(256, 4) k_rm_interior(QueryArgs a, const uint64_t* __restrict__ ioff,
                                                      const uint64_t* __restrict__ first_int, uint32_t chunk,
                                                      unsigned long long* __restrict__ sum,
                                                      unsigned long long* __restrict__ count,
-                                                     unsigned long long* __restrict__ alg) {
-  const uint64_t V = ioff[a.q];
-  const uint64_t G = (uint64_t)kWave * chunk;
-  const uint64_t ngroups = (V + G - 1) / G;
-  const uint64_t nwaves = (uint64_t)gridDim.x * blockDim.x / kWave;
-  const uint64_t wave = (uint64_t)__builtin_amdgcn_readfirstlane((int)(((uint64_t)blockIdx.x * blockDim.x + threadIdx.x) / kWave));
+                                                     unsigned long long* __restrict__ alg, LeafPrefix lp) {
+  __shared__ __align__(16) uint8_t stages[256 / kWave][kStageBytes];
+  uint8_t* const stage = stages[threadIdx.x / kWave];
   const int lane = lane_id();
-  uint64_t visited = 0;
-  uint64_t cq = ~0ull, cs = 0, cn = 0;  // carried query (wave-uniform) and this lane's share
+  const uint64_t V = uniform64(ioff[a.q]);
+  const bool by_prefix = lp.ps && V > a.L;
+  uint32_t visited = 0;  // used bytes this lane's leaves hold
+  // this wave's items (leaves or visits): groups of G from g * G on, every `step`-th group
+  uint64_t G, g, step, end;
+  uint64_t f0 = 0, f1 = 0;
+  if (by_prefix) {
+    f0 = min(a.L, (uint64_t)blockIdx.x * lp.range);
+    f1 = min(a.L, f0 + lp.range);
+    G = kStepLeaves;
+    g = f0 / kStepLeaves + (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
+    step = 256 / kWave;
+    end = f0 < f1 ? f1 : 0;
+  } else {
+    step = (uint64_t)gridDim.x * (256 / kWave);
+    g = (uint64_t)blockIdx.x * (256 / kWave) + (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
+    const uint64_t share = (V + step - 1) / step;
+    G = max(1ull, min((uint64_t)kWave * chunk, (share + kStepLeaves - 1) / kStepLeaves * kStepLeaves));
+    end = V;
+  }
+  uint64_t cq = ~0ull, cs = 0;  // carried query (wave-uniform) and this lane's share of its sum
+  uint32_t cn = 0;              // and count
   auto flush_carry = [&]() {
     if (cq != ~0ull) {
-      const uint64_t ts = wave_sum<uint64_t>(cs), tn = wave_sum<uint64_t>(cn);
+      const uint64_t ts = wave_sum<uint64_t>(cs), tn = wave_sum<uint64_t>((uint64_t)cn);
       if (lane == 0 && tn) {
         atomicAdd(&sum[cq], (unsigned long long)ts);
         atomicAdd(&count[cq], (unsigned long long)tn);
       }
     }
     cq = ~0ull;
-    cs = cn = 0;
+    cs = 0;
+    cn = 0;
   };
-  for (uint64_t g = wave; g < ngroups; g += nwaves) {
-    const uint64_t Wend = min((g + 1) * G, V);
-    for (uint64_t base = g * G; base < Wend; base += kWave) {
-      const uint64_t v = base + lane;
-      uint64_t vq = ~0ull, s = 0, n = 0;
-      if (v < Wend) {
-        uint64_t qi = upper_bound_u64(ioff, a.q + 1, base) - 1;
-        while (ioff[qi + 1] <= v) qi++;
+  for (; g * G < end; g += step) {
+    const uint64_t Wend = min((g + 1) * G, end);
+    // the query of the group's first visit; then of the part before
+    uint64_t q0 = by_prefix ? 0 : uniform64(upper_bound_u64(ioff, a.q + 1, g * G) - 1);
+    for (uint64_t base = g * G; base < Wend; base += kStepLeaves) {
+      const uint64_t v = base + (lane >> 1);
+      uint64_t vq = ~0ull;
+      uint32_t leaf = (uint32_t)v;
+      if (!by_prefix && v < Wend) {
+        uint64_t qi = q0;
+        // a few steps forward, then (many queries without interior leaves in
+        // between) a search
+        for (int steps = 0; ioff[qi + 1] <= v; qi++)
+          if (++steps > 8) {
+            qi += upper_bound_u64(ioff + qi, a.q + 1 - qi, v) - 1;
+            break;
+          }
         vq = qi;
-        const uint64_t leaf = first_int[qi] + (v - ioff[qi]);
-        const uint32_t u = a.used[leaf];
-        const LeafSum r = interior_leaf<kPlain>(a, leaf, u);
-        s = r.sum;
-        n = r.count;
-        visited += u;
+        leaf = (uint32_t)(first_int[qi] + (v - ioff[qi]));
       }
-      const uint64_t q0 = ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(vq >> 32)) << 32) |
-                          (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)vq);
+      // nothing lies after the last leaf: no prefix needs its sum
+      const LeafSum x = wave_leaf_sums<kPlain>(a, leaf, v < Wend && leaf + 1ull < a.L, stage, visited);
+      uint64_t s = x.sum;
+      uint32_t n = (uint32_t)x.count;
+      if (by_prefix) {
+        const uint64_t is = wave_incl_scan(s);
+        const uint32_t ic = wave_incl_scan(n);
+        if (!(lane & 1) && v < Wend) {
+          lp.ps[v] = is - s;
+          lp.pc[v] = ic - n;
+        }
+        if (lane == kWave - 1) {
+          lp.ss[base / kStepLeaves] = is;
+          lp.sc[base / kStepLeaves] = ic;
+        }
+        continue;
+      }
+      q0 = uniform64(vq);
       const bool uni = __ballot(vq != q0) == 0;
       if (uni && q0 == cq) {
         cs += s;
@@ -265,29 +570,56 @@ __global__ void __launch_bounds__(256) k_rm_interior(QueryArgs a, const uint64_t
         cn = n;
         continue;
       }
-      // several queries in this step: segmented inclusive scan over runs of equal vq
+      // several queries in this part: segmented inclusive scan over runs of equal vq
+      const uint32_t ol = opaque_lane();
 #pragma unroll
-      for (int d = 1; d < kWave; d <<= 1) {
-        const uint64_t qu = __shfl_up(vq, d, kWave);
-        const uint64_t su = __shfl_up(s, d, kWave);
-        const uint64_t nu = __shfl_up(n, d, kWave);
-        if (lane >= d && qu == vq) {
+      for (uint32_t d = 1; d < kWave; d <<= 1) {
+        const uint64_t qu = from_lane(vq, ol - d);
+        const uint64_t su = from_lane(s, ol - d);
+        const uint32_t nu = from_lane(n, ol - d);
+        if (ol >= d && qu == vq) {
           s += su;
           n += nu;
         }
       }
-      const uint64_t qn = __shfl_down(vq, 1, kWave);
-      const bool run_end = lane == kWave - 1 || qn != vq;
+      const uint64_t qn = from_lane(vq, ol + 1);  // every lane takes part
+      const bool run_end = ol == kWave - 1 || qn != vq;
       if (run_end && vq != ~0ull && n) {
         atomicAdd(&sum[vq], (unsigned long long)s);
         atomicAdd(&count[vq], (unsigned long long)n);
       }
     }
   }
-  flush_carry();
+  if (by_prefix)
+    leaf_prefix_finish(a, lp, ioff, first_int, sum, count, f0, f1);
+  else
+    flush_carry();
   if (alg) {
-    const uint64_t t = wave_sum(visited);
+    const uint64_t t = wave_sum((uint64_t)visited);
     if (lane_id() == 0) alg[((uint64_t)blockIdx.x * blockDim.x + threadIdx.x) / kWave] = t;
+  }
+}
+
+// After a prefix pass of more than kPrefixInline queries (the same test as in
+// k_rm_interior): every query's interior from the prefixes.  Each block scans
+// the runs' totals for itself.
+__global__ void __launch_bounds__(256) k_rm_prefix_apply(QueryArgs a, const uint64_t* __restrict__ ioff,
+                                                         const uint64_t* __restrict__ first_int, LeafPrefix lp,
+                                                         uint32_t runs, unsigned long long* __restrict__ sum,
+                                                         unsigned long long* __restrict__ count) {
+  if (ioff[a.q] <= a.L) return;
+  __shared__ uint64_t ts[kPrefixRuns], tc[kPrefixRuns], red[2][4];
+  for (uint32_t i = threadIdx.x; i < runs; i += 256) {
+    ts[i] = lp.ts[i];
+    tc[i] = lp.tc[i];
+  }
+  __syncthreads();
+  block_scan_pairs(ts, tc, runs, red);
+  __syncthreads();
+  for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < a.q;
+       i += (uint64_t)gridDim.x * blockDim.x) {
+    const uint64_t n = ioff[i + 1] - ioff[i];
+    if (n) prefix_apply(lp, ts, tc, first_int[i], n, i, sum, count);
   }
 }
 

@@ -99,16 +99,11 @@ __device__ __forceinline__ LeafSum leaf_sum_fast(const uint8_t* __restrict__ lea
   return r;
 }
 
-// Keeps the loads above it above it: without this the compiler sinks each
-// round's loads down to their use in the next round, so that every round waits
-// for its own loads instead of finding them done.
-__device__ __forceinline__ void issue_now() { asm volatile("" ::: "memory"); }
-
-// One byte (byte J of word x) of leaf_sum_zf: the running offset D (key minus
-// head) grows by the byte's payload at its shift; a terminator's D is returned
-// for the sum, a continuation byte returns 0.  The continuation mask is one
-// sign-extending extract, written so that the compiler keeps it: left to
-// itself it rebuilds the mask from a compare and two selects per byte.
+// One byte (byte J of word x) of wave_leaf_sums: the running offset D grows by
+// the byte's payload at its shift; a terminator's D is returned for the sum, a
+// continuation byte returns 0.  The continuation mask is one sign-extending
+// extract, written so that the compiler keeps it: left to itself it rebuilds
+// the mask from a compare and two selects per byte.
 template <int J>
 __device__ __forceinline__ uint32_t zf_byte(uint32_t x, uint32_t& D, uint32_t& sh) {
   uint32_t cm;  // all ones on a continuation byte
@@ -118,9 +113,11 @@ __device__ __forceinline__ uint32_t zf_byte(uint32_t x, uint32_t& D, uint32_t& s
   return D & ~cm;
 }
 
-// One 16-byte chunk of leaf_sum_zf.  Offsets stay below 2^28, so the chunk's
-// 16 terminator offsets sum below 2^32 and are folded into the 64-bit total
-// once.  `cont` counts continuation bytes.
+// One 16-byte chunk of wave_leaf_sums.  `cont` counts continuation bytes.
+// kWide: offsets may reach 2^32, so every terminator's is added in 64 bits;
+// otherwise they stay below 2^28, the chunk's 16 sum below 2^32 and are folded
+// into the 64-bit total once.
+template <bool kWide>
 __device__ __forceinline__ void zf_chunk(const uint4 q, uint32_t& D, uint32_t& sh, uint64_t& Sc, uint32_t& cont) {
   const uint32_t w[4] = {q.x, q.y, q.z, q.w};
   uint32_t s = 0;
@@ -131,69 +128,15 @@ __device__ __forceinline__ void zf_chunk(const uint4 q, uint32_t& D, uint32_t& s
     const uint32_t t1 = zf_byte<1>(x, D, sh);
     const uint32_t t2 = zf_byte<2>(x, D, sh);
     const uint32_t t3 = zf_byte<3>(x, D, sh);
-    s += (t0 + t1) + (t2 + t3);
+    if constexpr (kWide) {
+      Sc += ((uint64_t)t0 + t1) + ((uint64_t)t2 + t3);
+      __builtin_amdgcn_sched_barrier(0);  // few registers: this instance is rarely the one that runs
+    } else {
+      s += (t0 + t1) + (t2 + t3);
+    }
     cont += (uint32_t)__popc(x & 0x80808080u);
   }
-  Sc += s;
-}
-
-// Sum and count of every key of a leaf read in place, for leaves whose key span
-// is below 2^28 and whose bytes past `used` are zero (the leaf layout's zero
-// fill; not key-value leaves, whose values sit at the leaf's end).  The leaf is
-// read in whole 64-byte rounds (S is a multiple of 64) with no bounds tests:
-//  * each zero byte past `used` decodes as a zero delta, one more copy of the
-//    last key; there are exactly 64 * rounds - used of them, taken back out of
-//    the sum at the end;
-//  * the key count is `used` minus the continuation bytes, once the head's
-//    eight bytes are replaced by seven payload-free continuation bytes and a
-//    terminator (the head: one key at offset 0);
-//  * every round's four loads are issued unconditionally (past the last round
-//    they reread it), so the next round is in flight while one is decoded.
-__device__ __forceinline__ LeafSum leaf_sum_zf(const uint8_t* __restrict__ leaf, uint32_t used, uint64_t head) {
-  if (used == 0) return LeafSum{0, 0};
-  const uint32_t lastr = (used - 1u) & ~63u;  // first byte of the last round
-  uint32_t D = 0, sh = 0, cont = 0;
-  uint64_t Sc = 0;
-  const uint4* pa = reinterpret_cast<const uint4*>(leaf);
-  uint4 a0 = pa[0], a1 = pa[1], a2 = pa[2], a3 = pa[3];
-  const uint4* pb = reinterpret_cast<const uint4*>(leaf + min(64u, lastr));
-  uint4 b0 = pb[0], b1 = pb[1], b2 = pb[2], b3 = pb[3];
-  issue_now();
-  a0.x = 0x80808080u;
-  a0.y = 0x00808080u;
-  zf_chunk(a0, D, sh, Sc, cont);
-  zf_chunk(a1, D, sh, Sc, cont);
-  zf_chunk(a2, D, sh, Sc, cont);
-  zf_chunk(a3, D, sh, Sc, cont);
-  // ping-pong between two register sets: no copies between rounds
-  for (uint32_t c = 64; c < used;) {
-    pa = reinterpret_cast<const uint4*>(leaf + min(c + 64u, lastr));
-    a0 = pa[0];
-    a1 = pa[1];
-    a2 = pa[2];
-    a3 = pa[3];
-    issue_now();
-    zf_chunk(b0, D, sh, Sc, cont);
-    zf_chunk(b1, D, sh, Sc, cont);
-    zf_chunk(b2, D, sh, Sc, cont);
-    zf_chunk(b3, D, sh, Sc, cont);
-    c += 64;
-    if (c >= used) break;
-    pb = reinterpret_cast<const uint4*>(leaf + min(c + 64u, lastr));
-    b0 = pb[0];
-    b1 = pb[1];
-    b2 = pb[2];
-    b3 = pb[3];
-    issue_now();
-    zf_chunk(a0, D, sh, Sc, cont);
-    zf_chunk(a1, D, sh, Sc, cont);
-    zf_chunk(a2, D, sh, Sc, cont);
-    zf_chunk(a3, D, sh, Sc, cont);
-    c += 64;
-  }
-  const uint32_t zeros = ((used + 63u) & ~63u) - used;
-  const uint64_t cnt = used - cont;
-  return LeafSum{cnt * head + (Sc - (uint64_t)zeros * D), cnt};
+  if constexpr (!kWide) Sc += s;
 }
 
 // General path: 64-bit decode; counts and sums keys in [lo, hi).  Stops early
@@ -293,29 +236,8 @@ __device__ __forceinline__ LeafSum raw_sum_range(const uint8_t* __restrict__ lea
   return r;
 }
 
-// Sum and count of every key of an uncompressed leaf, one lane (16-byte loads,
-// four in flight).
-__device__ __forceinline__ LeafSum raw_sum_all(const uint8_t* __restrict__ leaf, uint32_t used) {
-  const uint4* w = reinterpret_cast<const uint4*>(leaf);
-  const uint32_t m = used / 8, nw = m / 2;
-  uint64_t s0 = 0, s1 = 0;
-  uint32_t i = 0;
-  for (; i + 4 <= nw; i += 4) {
-    const uint4 a = w[i], b = w[i + 1], c = w[i + 2], d = w[i + 3];
-    s0 += (((uint64_t)a.y << 32) | a.x) + (((uint64_t)a.w << 32) | a.z) + (((uint64_t)b.y << 32) | b.x) +
-          (((uint64_t)b.w << 32) | b.z);
-    s1 += (((uint64_t)c.y << 32) | c.x) + (((uint64_t)c.w << 32) | c.z) + (((uint64_t)d.y << 32) | d.x) +
-          (((uint64_t)d.w << 32) | d.z);
-  }
-  for (; i < nw; i++) {
-    const uint4 a = w[i];
-    s0 += (((uint64_t)a.y << 32) | a.x) + (((uint64_t)a.w << 32) | a.z);
-  }
-  if (m & 1u) s1 += reinterpret_cast<const uint64_t*>(leaf)[m - 1];
-  return LeafSum{s0 + s1, m};
-}
-
-// The same for a whole wave on one leaf (keys i = lane, lane + 64, ...).
+// Sum and count of the keys in [lo, hi) of an uncompressed leaf, a whole wave on
+// one leaf (keys i = lane, lane + 64, ...).
 __device__ __forceinline__ LeafSum wave_raw_sum_range(const uint8_t* __restrict__ leaf, uint32_t used, uint64_t lo,
                                                       uint64_t hi) {
   const uint64_t* k = reinterpret_cast<const uint64_t*>(leaf);
