@@ -1894,6 +1894,19 @@ cpma_status cpma_export_code_bytes(const cpma* cs, uint32_t* clen, void* stream)
 
 static QueryArgs query_args(const cpma* s);
 
+// Lookups a wave takes at a time, and the grid: 64 keep the head search cheap
+// (a lane each), fewer spread a small batch over the chip's waves (a wave decodes
+// four leaves at once, so 64 lookups are a chain of sixteen).
+static uint32_t lookups_per_wave(const cpma* s, uint64_t n) {
+  const uint64_t waves = (uint64_t)s->num_cus * 16;
+  uint32_t per = 4;
+  while (per < 64 && (uint64_t)per * waves < n) per *= 2;
+  return per;
+}
+static uint32_t lookup_grid(const cpma* s, uint64_t n, uint32_t per) {
+  return grid_for((n + per - 1) / per, 256 / kWave, (uint32_t)s->num_cus * 16);
+}
+
 cpma_status cpma_apply_updates(cpma* s, uint32_t nreq, const int32_t* kind, const uint64_t* const* keys,
                                const uint64_t* n, cpma_mem mem, uint64_t* result, void* stream) {
   if (!s || (nreq && (!kind || !keys || !n || !result)) || s->cfg.uncompressed || s->kv()) return CPMA_ERR_INVALID;
@@ -2033,9 +2046,10 @@ cpma_status cpma_apply_updates(cpma* s, uint32_t nreq, const int32_t* kind, cons
                          dim3(kWave), 8ull * s->S, st, qa, (const uint64_t*)s->kdedup.as<uint64_t>(),
                          (const uint32_t*)s->leafid.as<uint32_t>(), s->fz_member.as<uint8_t>());
     } else {
-      hipLaunchKernelGGL(k_fuse_member, dim3(grid_for(m, 256, (uint32_t)s->num_cus * 16)), dim3(256), 0, st, qa,
-                         (const uint64_t*)s->kdedup.as<uint64_t>(), (const unsigned long long*)fctr,
-                         s->fz_member.as<uint8_t>());
+      const uint32_t per = lookups_per_wave(s, m);
+      hipLaunchKernelGGL(k_contains, dim3(lookup_grid(s, m, per)), dim3(256), 0, st, qa,
+                         (const uint64_t*)s->kdedup.as<uint64_t>(), s->fz_member.as<uint8_t>(), per,
+                         (const unsigned long long*)fctr);
     }
     hipLaunchKernelGGL(k_fuse_credit, dim3(grid_for(m, 256)), dim3(256), 0, st, skeys, svals, m,
                        (const uint32_t*)s->segpos.as<uint32_t>(), (const uint8_t*)s->fz_member.as<uint8_t>(),
@@ -2184,11 +2198,8 @@ static cpma_status range_map_impl(const cpma* cs, const uint64_t* lo, const uint
     ensure(s->qvoff, (q + 1) * 8);
     PhaseMark pq = phase_begin(s, CPMA_PHASE_QUERY, st);
     // statistics: one byte-count slot per wave of the end and interior kernels
-    // few queries: a wave per query (key sums only)
-    const bool wave_ends = q <= (uint64_t)s->num_cus * 64 && !values;
-    const uint32_t egrid = wave_ends ? grid_for(q, 1, (uint32_t)s->num_cus * 64)
-                                     : grid_for(q, 256, (uint32_t)s->num_cus * 16);
-    const uint64_t ewaves = wave_ends ? egrid : 4ull * egrid;
+    const uint32_t per = lookups_per_wave(s, 2 * q), egrid = lookup_grid(s, 2 * q, per);
+    const uint64_t ewaves = 4ull * egrid;
     const uint32_t blocks = interior_blocks(s, a);
     const uint64_t nslots = ewaves + 4ull * blocks;
     const LeafPrefix lp = leaf_prefix(s, q, blocks, st);
@@ -2197,12 +2208,8 @@ static cpma_status range_map_impl(const cpma* cs, const uint64_t* lo, const uint
       ensure(s->qparts, 8 * nslots);
       qalg = s->qparts.as<unsigned long long>();
     }
-    if (wave_ends)
-      hipLaunchKernelGGL(k_rm_ends_wave, dim3(egrid), dim3(kWave), 0, st, a, s->qfirst.as<uint64_t>(),
-                         s->qnvis.as<uint64_t>(), dsum, dcount, qalg, lp.ticket);
-    else
-      hipLaunchKernelGGL(k_rm_ends, dim3(egrid), dim3(256), 0, st, a, s->qfirst.as<uint64_t>(),
-                         s->qnvis.as<uint64_t>(), dsum, dcount, qalg, lp.ticket);
+    hipLaunchKernelGGL(k_rm_ends, dim3(egrid), dim3(256), 0, st, a, s->qfirst.as<uint64_t>(),
+                       s->qnvis.as<uint64_t>(), dsum, dcount, qalg, lp.ticket, per);
     HIPCHK(hipGetLastError());
     scan<uint64_t>(s, s->qvoff.as<uint64_t>(), q, st, LoadFn<uint64_t>{s->qnvis.as<uint64_t>()});
     PhaseMark ps = phase_begin(s, CPMA_PHASE_RANGE_SCAN, st);
@@ -2258,8 +2265,8 @@ cpma_status cpma_get(const cpma* cs, const uint64_t* keys, uint64_t q, cpma_mem 
       dv = s->qsum.as<uint64_t>();
       df = s->qout.as<uint8_t>();
     }
-    hipLaunchKernelGGL(k_kv_get, dim3(grid_for(q, 256, (uint32_t)s->num_cus * 16)), dim3(256), 0, st, a, dk, dv,
-                       df);
+    const uint32_t per = lookups_per_wave(s, q);
+    hipLaunchKernelGGL(k_kv_get, dim3(lookup_grid(s, q, per)), dim3(256), 0, st, a, dk, dv, df, per);
     HIPCHK(hipGetLastError());
     if (mem == CPMA_MEM_HOST) {
       HIPCHK(hipMemcpyAsync(values, dv, q * 8, hipMemcpyDeviceToHost, st));
@@ -2327,15 +2334,9 @@ cpma_status cpma_range_map_noalloc(const cpma* cs, const uint64_t* lo, const uin
     unsigned long long* dsum = (unsigned long long*)sum;
     unsigned long long* dcount = (unsigned long long*)count;
     // the same kernels as cpma_range_map, without statistics
-    const bool wave_ends = q <= (uint64_t)s->num_cus * 64;
-    const uint32_t egrid = wave_ends ? grid_for(q, 1, (uint32_t)s->num_cus * 64)
-                                     : grid_for(q, 256, (uint32_t)s->num_cus * 16);
-    if (wave_ends)
-      hipLaunchKernelGGL(k_rm_ends_wave, dim3(egrid), dim3(kWave), 0, st, a, first, nvis, dsum, dcount,
-                         (unsigned long long*)nullptr, (unsigned int*)nullptr);
-    else
-      hipLaunchKernelGGL(k_rm_ends, dim3(egrid), dim3(256), 0, st, a, first, nvis, dsum, dcount,
-                         (unsigned long long*)nullptr, (unsigned int*)nullptr);
+    const uint32_t per = lookups_per_wave(s, 2 * q);
+    hipLaunchKernelGGL(k_rm_ends, dim3(lookup_grid(s, 2 * q, per)), dim3(256), 0, st, a, first, nvis, dsum, dcount,
+                       (unsigned long long*)nullptr, (unsigned int*)nullptr, per);
     HIPCHK(hipGetLastError());
     HIPCHK(scan_exclusive<uint64_t>(LoadFn<uint64_t>{nvis}, q, voff, tmp, st));
     launch_interior(a, interior_blocks(s, a), st, voff, first, s->cfg.range_chunk, dsum, dcount, nullptr,
@@ -2366,8 +2367,9 @@ cpma_status cpma_contains(const cpma* cs, const uint64_t* keys, uint64_t q, cpma
       dout = s->qout.as<uint8_t>();
     }
     PhaseMark pq = phase_begin(s, CPMA_PHASE_QUERY, st);
-    hipLaunchKernelGGL(k_contains, dim3(grid_for(q, 256, (uint32_t)s->num_cus * 16)), dim3(256), 0, st, a, dk,
-                       dout);
+    const uint32_t per = lookups_per_wave(s, q);
+    hipLaunchKernelGGL(k_contains, dim3(lookup_grid(s, q, per)), dim3(256), 0, st, a, dk, dout, per,
+                       (const unsigned long long*)nullptr);
     HIPCHK(hipGetLastError());
     phase_end(s, pq, st);
     if (mem == CPMA_MEM_HOST) {

@@ -31,21 +31,8 @@ __global__ void __launch_bounds__(256) k_fuse_kinds(const uint64_t* __restrict__
   }
 }
 
-// Membership before the sequence of each distinct key (nd of them, on the device).
-__global__ void __launch_bounds__(256) k_fuse_member(QueryArgs a, const uint64_t* __restrict__ keys,
-                                                     const unsigned long long* __restrict__ nd,
-                                                     uint8_t* __restrict__ member) {
-  const uint64_t q = *nd;
-  for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < q;
-       i += (uint64_t)gridDim.x * blockDim.x) {
-    const uint64_t x = keys[i];
-    const uint64_t leaf = locate_leaf(a.head, a.L, x);
-    const LeafSum r = leaf_sum_range(a.bytes + leaf * (uint64_t)a.S, a.used[leaf], x, x + 1);
-    member[i] = r.count ? 1 : 0;
-  }
-}
-
-// The same per leaf for large batches: leaf f's distinct keys are
+// Membership before the sequence of each distinct key, per leaf (large batches;
+// k_contains otherwise): leaf f's distinct keys are
 // keys[sbeg[f] .. sbeg[f + 1]); one wave decodes the leaf once into LDS
 // (dynamic, 8 bytes per possible key: S - 7 codes plus the head) and binary-
 // searches each of them there.

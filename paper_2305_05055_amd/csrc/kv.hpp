@@ -247,35 +247,4 @@ __global__ void k_kv_compact(const uint64_t* __restrict__ a, const uint32_t* __r
   }
 }
 
-// One lane walks a key-value leaf's codes (clen bytes) and returns, for the
-// keys in [lo, hi), the sum of their values (mod 2^64) and their count; with
-// hi = lo + 1 and `found`, the value of key lo.
-__device__ __forceinline__ LeafSum kv_leaf_values(const uint8_t* __restrict__ leaf, uint32_t clen,
-                                                  const uint64_t* __restrict__ vals, uint64_t lo, uint64_t hi) {
-  LeafSum r{0, 0};
-  if (clen < 8) return r;
-  uint64_t key = 0;
-  for (int i = 7; i >= 0; i--) key = (key << 8) | leaf[i];
-  uint32_t idx = 0, pos = 8;
-  while (true) {
-    if (key >= hi) break;
-    if (key >= lo) {
-      r.sum += vals[idx];
-      r.count++;
-    }
-    if (pos >= clen) break;
-    uint64_t d = 0;
-    uint32_t sh = 0;
-    uint8_t c;
-    do {
-      c = leaf[pos++];
-      if (sh < 64) d |= (uint64_t)(c & 0x7fu) << sh;
-      sh += 7;
-    } while (c & 0x80u);
-    key += d;
-    idx++;
-  }
-  return r;
-}
-
 }  // namespace cpma_dev

@@ -1,0 +1,346 @@
+// Point lookups in leaves, four per wave at a time: how many keys of a leaf lie
+// below x, their sum, and whether x is there (contains, get and the end leaves
+// of range_map: Sections "Compressed Packed Memory Array", "Point queries", and
+// "Packed Memory Array", "Design and operations").
+//
+// A row of 16 lanes decodes one leaf, 16 bytes per lane and 256 bytes per
+// round, and stops after the round in which the keys reach x.  One lane per
+// leaf, the obvious split, asks the L1 for 64 separate lines with every 16-byte
+// load and walks its leaf in a chain of a dozen rounds, and a wave waits for the
+// longest of its 64 walks.  1e6 membership tests on 1e8 keys: 389 -> 200 us; the
+// partial end leaves of 1e6 ranges: 816 -> 460 us; get of 1e6 keys of a key-value
+// set (byte loads before): 727 -> 151 us.  Bound: VALU issue of the byte walk
+// (about 135 instructions per round).
+#pragma once
+#include "scan_lane.hpp"
+#include "update.hpp"
+
+namespace cpma_dev {
+
+struct QueryArgs {
+  const uint64_t* lo;
+  const uint64_t* hi;
+  uint64_t q;
+  const uint64_t* head;
+  const uint8_t* bytes;
+  const uint32_t* used;
+  uint64_t L;
+  uint32_t S;
+  uint32_t raw;  // uncompressed leaves (raw 8-byte keys)
+  // key-value leaves: `used` above is each leaf's code bytes, `fill` its filled
+  // bytes (codes and values); vals: sum values instead of keys
+  const uint32_t* fill;
+  uint32_t vals;
+  uint32_t zero_fill;  // bytes past `used` are zero in place (every set without values)
+};
+
+// ---- DPP within rows of 16 lanes ---------------------------------------------------
+template <typename T>
+__device__ __forceinline__ T row_incl_scan(T v) {
+  if constexpr (sizeof(T) == 4) {
+    v += dpp32<0x111>(v);
+    v += dpp32<0x112>(v);
+    v += dpp32<0x114>(v);
+    v += dpp32<0x118>(v);
+  } else {
+    v += dpp64<0x111>(v);
+    v += dpp64<0x112>(v);
+    v += dpp64<0x114>(v);
+    v += dpp64<0x118>(v);
+  }
+  return v;
+}
+// Lane 15 of the row, to all its lanes.
+__device__ __forceinline__ uint32_t row_last(uint32_t v) { return dpp32<0x15f>(v); }
+__device__ __forceinline__ uint64_t row_last(uint64_t v) { return dpp64<0x15f>(v); }
+
+// One lane's 16 bytes of a round, with what is not a code of the leaf turned
+// into continuation bytes without payload: the first seven bytes of the head
+// (its eighth becomes a terminator: one key at offset 0) and the bytes at or past
+// `used` (zero fill, or values).
+__device__ __forceinline__ uint4 lookup_bytes(uint4 q, uint32_t pos0, uint32_t used) {
+  uint32_t w[4] = {q.x, q.y, q.z, q.w};
+  if (pos0 == 0) {
+    w[0] = 0x80808080u;
+    w[1] = 0x00808080u;
+  }
+  const int32_t nv = (int32_t)used - (int32_t)pos0;
+  if (nv < 16) {
+#pragma unroll
+    for (int k = 0; k < 4; k++) {
+      const int32_t v = nv - 4 * k;
+      const uint32_t keep = v >= 4 ? 0xffffffffu : (v <= 0 ? 0u : ((1u << (8 * v)) - 1u));
+      w[k] = (w[k] & keep) | (0x80808080u & ~keep);
+    }
+  }
+  return make_uint4(w[0], w[1], w[2], w[3]);
+}
+
+// The keys that end in 16 bytes, as offsets from what precedes them: f(offset,
+// mask) per byte, mask all ones on a continuation byte, at which no key ends.
+// sh: the shift the first byte's code has reached.  Returns the offset reached.
+template <typename KT, class F>
+__device__ __forceinline__ KT walk_bytes(const uint4 q, uint32_t sh, F&& f) {
+  const uint32_t w[4] = {q.x, q.y, q.z, q.w};
+  KT run = 0;
+#pragma unroll
+  for (int j = 0; j < 16; j++) {
+    const uint32_t x = w[j >> 2];
+    uint32_t cm;
+    asm("v_bfe_i32 %0, %1, %2, 1" : "=v"(cm) : "v"(x), "i"(8 * (j & 3) + 7));
+    run += (KT)__builtin_amdgcn_ubfe(x, 8 * (j & 3), 7) << (sh & (8u * sizeof(KT) - 1u));
+    sh = (sh + 7u) & cm;
+    f(run, cm);
+  }
+  return run;
+}
+
+// Trailing continuation bytes of 16 bytes (KT 32 bits: at most 4 matter).
+template <typename KT>
+__device__ __forceinline__ uint32_t tail_run(const uint4 w) {
+  const uint32_t e3 = ~w.w & 0x80808080u;
+  uint32_t tc = e3 ? (uint32_t)__clz((int)e3) >> 3 : 4u;
+  if constexpr (sizeof(KT) == 8) {
+    const uint32_t e2 = ~w.z & 0x80808080u, e1 = ~w.y & 0x80808080u;
+    if (!e3) tc += e2 ? (uint32_t)__clz((int)e2) >> 3 : 4u + (e1 ? (uint32_t)__clz((int)e1) >> 3 : 4u);
+  }
+  return tc;
+}
+
+// Where a lookup's walk reaches its key: the 16 bytes, the offset before them and
+// the shift their first code has reached.
+struct Reach {
+  uint4 bytes;
+  uint64_t at;
+  uint32_t sh, pad;
+};
+constexpr uint32_t kReachBytes = sizeof(Reach) * kWave;  // LDS per wave
+
+struct Lookup {
+  uint64_t cnt;  // keys of the leaf below x
+  uint64_t sum;  // their sum, or the sum of their values
+  bool eq;       // x is a key of the leaf
+};
+
+// Four leaves' walks, one per row.  KT: the type of key offsets from the head, 32
+// bits when every leaf's keys span less than 2^32 - 1 (so that X is below a
+// continuation byte's all-ones mask).  The 16 bytes in which a row's offset
+// reaches X go to `reach`; the lanes before them only need their totals (kSum: and
+// the sum of their keys' offsets).  Returns the rows' lanes that reached X.
+template <typename KT, bool kSum>
+__device__ __forceinline__ uint64_t row_walk(const uint8_t* __restrict__ leaf, uint4 w, uint32_t used, KT X,
+                                             Reach* reach, uint32_t& cnt, uint64_t& sum) {
+  const uint32_t l16 = (uint32_t)lane_id() & 15u;
+  KT base = 0;        // offset reached before the round (the row's lanes alike)
+  uint32_t tail = 0;  // this lane's trailing continuation bytes in the round before
+  uint64_t found = 0;
+  for (uint32_t pos = 0;; pos += 256) {
+    const uint32_t pos0 = pos + 16u * l16;
+    w = lookup_bytes(w, pos0, used);
+    // the run carried in: the lane before's; for the row's first lane the last
+    // lane's of the round before (row rotation by one)
+    const uint32_t tc = tail_run<KT>(w);
+    const uint32_t wrap = dpp32<0x121>(tail), prev = dpp32<0x111>(tc);
+    const uint32_t sh = 7u * (l16 ? prev : wrap);
+    tail = tc;
+    uint64_t s = 0;
+    uint32_t s32 = 0;
+    const KT run = walk_bytes<KT>(w, sh, [&](KT off, uint32_t cm) {
+      if constexpr (kSum) s32 += (uint32_t)off & ~cm;
+    });
+    if constexpr (kSum) {
+      // 16 offsets below 2^28 sum below 2^32; larger ones are added again in 64 bits
+      s = s32;
+      if (run >= (KT)(1u << 28)) {
+        s = 0;
+        walk_bytes<KT>(w, sh, [&](KT off, uint32_t cm) { s += (uint64_t)(off & ~(KT)(int64_t)(int32_t)cm); });
+      }
+    }
+    const KT incl = row_incl_scan<KT>(run);
+    const KT at = base + (incl - run), end = base + incl;
+    base += row_last(incl);
+    if constexpr (kSum) {
+      if (end < X) {
+        const uint32_t c = 16u - (uint32_t)(__popc(w.x & 0x80808080u) + __popc(w.y & 0x80808080u) +
+                                            __popc(w.z & 0x80808080u) + __popc(w.w & 0x80808080u));
+        cnt += c;
+        sum += s + (uint64_t)c * (uint64_t)at;
+      }
+    }
+    const bool here = end >= X && (at < X || pos0 == 0);
+    if (here) *reach = Reach{w, (uint64_t)at, sh, 0};
+    found |= __ballot(here);
+    const bool more = pos + 256 < used && base < X;
+    if (!__ballot(more)) return found;
+    // a finished row goes on over bytes without keys
+    w = make_uint4(0x80808080u, 0x80808080u, 0x80808080u, 0x80808080u);
+    if (more && pos + 256 + 16u * l16 < used) w = load16(leaf + pos + 256 + 16u * l16);
+  }
+}
+
+// Up to 64 lookups of one wave: lane l's lookup is key x in leaf `leaf` (valid:
+// the lane has one; the lanes that do come first).  leaf must be the leaf x
+// belongs to, or the one before when x is the next leaf's head.  kSum / kEq: what
+// besides the count is wanted (kEq alone: not even the count, unless kCnt).
+// Every lane then finishes its own lookup in the 16 bytes where it reached x: the
+// per-key comparisons run once per 64 lookups instead of once per four.
+template <bool kCnt, bool kSum, bool kEq>
+__device__ __forceinline__ Lookup wave_lookup(const QueryArgs& a, bool valid, uint64_t leaf, uint64_t x,
+                                              Reach* reach) {
+  const uint32_t l = (uint32_t)lane_id(), l16 = l & 15u;
+  const uint64_t head = valid ? a.head[leaf] : kNoKey;
+  const uint64_t next = valid && leaf + 1 < a.L ? a.head[leaf + 1] : kNoKey;
+  // x below the head (only below every key) and an empty leaf: nothing to read;
+  // nor for the reserved key, which no leaf holds (its offset can look like a
+  // continuation byte's)
+  const uint32_t used = valid && x >= head && head != kNoKey && !(kEq && x == kNoKey) ? a.used[leaf] : 0u;
+  const uint64_t X = used ? x - head : 0;
+  const bool wide = used && next - head >= 0xffffffffull;
+  const uint32_t nit = ((uint32_t)__popcll(__ballot(valid)) + 3u) / 4u;
+  const bool any_wide = __ballot(wide) != 0;
+  Lookup out{0, 0, false};
+  bool reached = false;
+  // the next lookups' first round is loaded before the current ones are decoded
+  uint32_t n_used = 0, n_leaf = 0;
+  uint4 n_w = make_uint4(0, 0, 0, 0);
+  auto fetch = [&](uint32_t it) {
+    const uint32_t from = 4u * it + (opaque_lane() >> 4);
+    n_used = from_lane(used, from);
+    n_leaf = from_lane((uint32_t)leaf, from);
+    if (16u * l16 < n_used) n_w = load16(a.bytes + (uint64_t)n_leaf * a.S + 16u * l16);
+  };
+  if (!a.raw) fetch(0);
+#pragma unroll 1
+  for (uint32_t it = 0; it < nit; it++) {
+    const uint32_t from = 4u * it + (opaque_lane() >> 4);
+    const uint64_t Xr = from_lane(X, from);
+    uint64_t sum = 0, found = 0;
+    uint32_t cnt = 0;
+    bool eq = false;
+    if (a.raw) {
+      const uint32_t m = from_lane(used, from) / 8;
+      const uint64_t hd = from_lane(head, from);
+      const uint64_t* k = reinterpret_cast<const uint64_t*>(a.bytes + (uint64_t)from_lane((uint32_t)leaf, from) * a.S);
+      for (uint32_t i = l16; i < m; i += 16) {
+        const uint64_t d = k[i] - hd;
+        cnt += d < Xr ? 1u : 0u;
+        if constexpr (kSum) sum += d < Xr ? d : 0ull;
+        if constexpr (kEq) eq |= d == Xr;
+      }
+    } else {
+      const uint32_t ur = n_used;
+      const uint8_t* lp = a.bytes + (uint64_t)n_leaf * a.S;
+      const uint4 w = n_w;
+      if (it + 1 < nit) fetch(it + 1);
+      if (any_wide)
+        found = row_walk<uint64_t, kCnt || kSum>(lp, w, ur, Xr, reach + from, cnt, sum);
+      else
+        found = row_walk<uint32_t, kCnt || kSum>(lp, w, ur, (uint32_t)Xr, reach + from, cnt, sum);
+    }
+    // to the lanes whose lookups these were
+    const uint32_t ol = opaque_lane(), src = 16u * (ol & 3u);
+    const bool mine = (ol >> 2) == it;
+    if constexpr (kCnt || kSum) {
+      const uint32_t c = from_lane(row_last(row_incl_scan(cnt)), src);
+      if (mine) out.cnt = c;
+    }
+    if constexpr (kSum) {
+      const uint64_t t = from_lane(row_last(row_incl_scan(sum)), src);
+      if (mine) out.sum = t;
+    }
+    if (mine) reached = ((found >> src) & 0xffffu) != 0;
+    if constexpr (kEq) {
+      const uint64_t em = __ballot(eq);
+      if (mine) out.eq = ((em >> src) & 0xffffu) != 0;
+    }
+  }
+  if (!a.raw) {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+    if (reached && used) {
+      const Reach m = reach[l];
+      auto finish = [&](auto zero) {
+        using KT = decltype(zero);
+        const KT lim = (KT)(X - m.at);
+        uint64_t add = 0;
+        uint32_t c = 0;
+        bool hit = false;
+        walk_bytes<KT>(m.bytes, m.sh, [&](KT off, uint32_t cm) {
+          const KT k = off | (KT)(int64_t)(int32_t)cm;  // a continuation byte is no key: above every x
+          if constexpr (kCnt || kSum) c += k < lim ? 1u : 0u;
+          if constexpr (kSum) add += k < lim ? (uint64_t)k : 0ull;
+          if constexpr (kEq) hit |= k == lim;
+        });
+        out.cnt += c;
+        out.sum += add + (uint64_t)c * m.at;
+        out.eq = hit;
+      };
+      if (any_wide)
+        finish((uint64_t)0);
+      else
+        finish((uint32_t)0);
+    }
+    __builtin_amdgcn_wave_barrier();  // the slots may be written again
+  }
+  if constexpr (kSum) {
+    if (!a.vals) {
+      out.sum += out.cnt * head;
+    } else {
+      // the values of the keys below x: the first of the leaf's m values
+      const uint32_t m = used ? (a.fill[leaf] - used) / 8 : 0u;
+#pragma unroll 1
+      for (uint32_t it = 0; it < nit; it++) {
+        const uint32_t from = 4u * it + (opaque_lane() >> 4);
+        const uint32_t c = from_lane((uint32_t)out.cnt, from);
+        const uint64_t* v = reinterpret_cast<const uint64_t*>(
+            a.bytes + (uint64_t)from_lane((uint32_t)leaf, from) * a.S + a.S - 8u * from_lane(m, from));
+        uint64_t s = 0;
+        for (uint32_t i = l16; i < c; i += 16) s += v[i];
+        const uint32_t ol = opaque_lane();
+        const uint64_t t = from_lane(row_last(row_incl_scan(s)), 16u * (ol & 3u));
+        if ((ol >> 2) == it) out.sum = t;
+      }
+    }
+  }
+  return out;
+}
+
+// Leaf of x for each row of 16 lanes (x alike in a row): a 16-ary search of the
+// heads, five dependent loads for a million leaves instead of twenty.
+__device__ __forceinline__ uint64_t row_locate_leaf(const uint64_t* __restrict__ head, uint64_t L, uint64_t x,
+                                                    bool active) {
+  uint64_t lo = 0, hi = active ? L : 0;  // the first head above x lies in [lo, hi]
+  const uint32_t l16 = (uint32_t)lane_id() & 15u, row = (uint32_t)lane_id() & 48u;
+  while (__ballot(lo < hi)) {
+    const uint64_t step = (hi - lo + 15) / 16;
+    const uint64_t idx = lo + l16 * step;
+    const bool le = lo < hi && idx < hi && head[idx] <= x;
+    const uint32_t t = (uint32_t)__popc((uint32_t)(__ballot(le) >> row) & 0xffffu);  // a prefix of the pivots
+    if (lo < hi) {
+      if (t == 0) {
+        hi = lo;
+      } else {
+        const uint64_t last = lo + (uint64_t)(t - 1) * step;
+        lo = last + 1;
+        hi = min(hi, last + step);
+      }
+    }
+  }
+  return lo ? lo - 1 : 0;
+}
+
+// The leaf of every lane's x (valid lanes first).  Up to four keys: a 16-ary
+// search by a row each, whose chain of loads is a quarter as long; more: a
+// binary search per lane, which asks for far fewer lines in all.
+__device__ __forceinline__ uint64_t wave_locate(const QueryArgs& a, bool valid, uint64_t x) {
+  if (__popcll(__ballot(valid)) <= 4) {
+    const uint32_t row = opaque_lane() >> 4;
+    const bool act = from_lane(valid ? 1u : 0u, row) != 0;
+    const uint64_t f = row_locate_leaf(a.head, a.L, from_lane(x, row), act);
+    return from_lane(f, 16u * (opaque_lane() & 3u));
+  }
+  return valid ? locate_leaf(a.head, a.L, x) : 0;
+}
+
+}  // namespace cpma_dev

@@ -5,159 +5,58 @@
 // runs on the uncompressed leaf heads and the scan decodes every leaf it passes
 // (Section "Compressed Packed Memory Array", "Point queries").  A batch of
 // queries becomes a flat list of leaf visits (query q visits leaves
-// leaf(lo_q) .. leaf(hi_q - 1)).  The two end leaves of each query are scanned
-// with comparisons by one lane per query; the interior leaves are flattened over
+// leaf(lo_q) .. leaf(hi_q - 1)).  The partial leaves at each query's ends are
+// looked up; the leaves taken whole are flattened over
 // all queries and split into fixed-size chunks, so long and short ranges balance
 // across the GPU in one launch.
 #pragma once
+#include "lookup.hpp"
 #include "scan_lane.hpp"
 #include "update.hpp"
-#include "kv.hpp"
 
 namespace cpma_dev {
 
-struct QueryArgs {
-  const uint64_t* lo;
-  const uint64_t* hi;
-  uint64_t q;
-  const uint64_t* head;
-  const uint8_t* bytes;
-  const uint32_t* used;
-  uint64_t L;
-  uint32_t S;
-  uint32_t raw;  // uncompressed leaves (raw 8-byte keys)
-  // key-value leaves: `used` above is each leaf's code bytes, `fill` its filled
-  // bytes (codes and values); vals: sum values instead of keys
-  const uint32_t* fill;
-  uint32_t vals;
-  uint32_t zero_fill;  // bytes past `used` are zero in place (every set without values)
-};
-
-// The values of a key-value leaf (m = (fill - codes) / 8 words at its end).
-__device__ __forceinline__ const uint64_t* leaf_vals(const QueryArgs& a, uint64_t leaf, uint32_t codes) {
-  const uint32_t m = (a.fill[leaf] - codes) / 8;
-  return reinterpret_cast<const uint64_t*>(a.bytes + leaf * (uint64_t)a.S + a.S - 8u * m);
-}
-
-// Keys of [lo, hi) in one leaf, one lane, for either leaf format.
-__device__ __forceinline__ LeafSum leaf_range_any(const QueryArgs& a, uint64_t leaf, uint32_t used, uint64_t lo,
-                                                  uint64_t hi) {
-  const uint8_t* p = a.bytes + leaf * (uint64_t)a.S;
-  if (a.vals) return kv_leaf_values(p, used, leaf_vals(a, leaf, used), lo, hi);
-  return a.raw ? raw_sum_range(p, used, lo, hi) : leaf_sum_range(p, used, lo, hi);
-}
-
-// End leaves of every query (the leaf of lo and the leaf of hi - 1), scanned with
-// comparisons by one lane per query; the result initialises sum / count.  The
-// leaves strictly between them are the query's interior visits.
+// End leaves of every query.  With f and l the leaves of lo and of hi - 1, the
+// keys of [lo, hi) are those of leaves f .. l - 1 and the ones of leaf l below hi,
+// without the ones of leaf f below lo; the result initialises sum / count with
+// the two partial leaves (in wrapping 64-bit arithmetic), and leaves f .. l - 1
+// are the query's interior visits.  Two lookups per query, each stopping where
+// it reaches its key.  A wave takes `per` lookups (4 .. 64) at a time: as many as
+// it has lanes for when there are plenty, four when that leaves waves idle.
 __global__ void __launch_bounds__(256) k_rm_ends(QueryArgs a, uint64_t* __restrict__ first_int,
                                                  uint64_t* __restrict__ nint,
                                                  unsigned long long* __restrict__ sum,
                                                  unsigned long long* __restrict__ count,
-                                                 unsigned long long* __restrict__ alg, unsigned int* ticket) {
+                                                 unsigned long long* __restrict__ alg, unsigned int* ticket,
+                                                 uint32_t per) {
+  __shared__ Reach reach[256 / kWave][kWave];
+  Reach* const mine = reach[threadIdx.x / kWave];
   if (ticket && blockIdx.x == 0 && threadIdx.x == 0) *ticket = 0;  // for k_rm_interior's prefix pass
+  const uint32_t wave = blockIdx.x * (256 / kWave) + threadIdx.x / kWave, nwaves = gridDim.x * (256 / kWave);
+  const uint32_t lane = (uint32_t)lane_id();
   uint64_t visited = 0;
-  for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < a.q;
-       i += (uint64_t)gridDim.x * blockDim.x) {
-    const uint64_t lo = a.lo[i], hi = a.hi[i];
-    uint64_t f = 0, n = 0;
-    LeafSum r{0, 0};
-    if (lo < hi) {
-      f = locate_leaf(a.head, a.L, lo);
-      const uint64_t l = locate_leaf(a.head, a.L, hi - 1);
-      const uint32_t uf = a.used[f];
-      r = leaf_range_any(a, f, uf, lo, hi);
-      visited += uf;
-      if (l != f) {
-        const uint32_t ul = a.used[l];
-        const LeafSum r2 = leaf_range_any(a, l, ul, lo, hi);
-        r.sum += r2.sum;
-        r.count += r2.count;
-        visited += ul;
-      }
-      n = (l > f + 1) ? l - f - 1 : 0;
+  for (uint64_t base = (uint64_t)wave * per; base < 2 * a.q; base += (uint64_t)nwaves * per) {
+    const uint64_t i = (base + lane) >> 1;
+    const bool valid = lane < per && i < a.q;
+    const uint64_t lo = valid ? a.lo[i] : 0, hi = valid ? a.hi[i] : 0;
+    const bool some = lo < hi;
+    // the even lane looks lo up, the odd one hi in the leaf of hi - 1
+    const uint64_t leaf = wave_locate(a, valid, lane & 1 ? (some ? hi - 1 : 0) : lo);
+    const Lookup r = wave_lookup<true, true, false>(a, valid, leaf, lane & 1 ? hi : lo, mine);
+    constexpr int kXor1 = 1 | (0 << 2) | (3 << 4) | (2 << 6);
+    const uint64_t leaf_l = dpp64<kXor1>(leaf), sum_l = dpp64<kXor1>(r.sum), cnt_l = dpp64<kXor1>(r.cnt);
+    if (valid && !(lane & 1)) {
+      first_int[i] = leaf;
+      nint[i] = some ? leaf_l - leaf : 0;
+      sum[i] = some ? sum_l - r.sum : 0;
+      count[i] = some ? cnt_l - r.cnt : 0;
+      if (alg && some) visited += a.used[leaf_l];
     }
-    first_int[i] = f + 1;
-    nint[i] = n;
-    sum[i] = r.sum;
-    count[i] = r.count;
   }
   if (alg) {  // statistics: one slot per wave (no shared counter), summed by k_fold_sum
     const uint64_t t = wave_sum(visited);
-    if (lane_id() == 0) alg[((uint64_t)blockIdx.x * blockDim.x + threadIdx.x) / kWave] = t;
+    if (lane == 0) alg[wave] = t;
   }
-}
-
-// Few queries: one wave per query.  The leaf of a key comes from a 64-ary
-// search of the heads (64 pivots compared per step, so a few steps for millions
-// of leaves), and the two end leaves are decoded by the whole wave.
-__device__ __forceinline__ uint64_t wave_locate_leaf(const uint64_t* __restrict__ head, uint64_t L, uint64_t x) {
-  uint64_t lo = 0, hi = L;  // the first head above x lies in [lo, hi]
-  const uint32_t lane = (uint32_t)lane_id();
-  while (lo < hi) {
-    const uint64_t step = (hi - lo + kWave - 1) / kWave;
-    const uint64_t idx = lo + lane * step;
-    const bool le = idx < hi && head[idx] <= x;
-    const uint32_t t = (uint32_t)__popcll(__ballot(le));  // pivots at or below x form a prefix
-    if (t == 0) {
-      hi = lo;
-    } else {
-      const uint64_t last = lo + (uint64_t)(t - 1) * step;
-      lo = last + 1;
-      hi = min(hi, last + step);
-    }
-  }
-  return lo ? lo - 1 : 0;
-}
-
-__device__ __forceinline__ LeafSum wave_leaf_sum_range(const uint8_t* __restrict__ leaf, uint32_t used, uint64_t lo,
-                                                       uint64_t hi) {
-  uint64_t s = 0, n = 0;
-  wave_decode_leaf(leaf, used, [&](uint32_t, uint64_t k, uint64_t) {
-    if (k >= lo && k < hi) {
-      s += k;
-      n++;
-    }
-  });
-  return LeafSum{wave_sum(s), wave_sum(n)};
-}
-
-__global__ void __launch_bounds__(kWave) k_rm_ends_wave(QueryArgs a, uint64_t* __restrict__ first_int,
-                                                        uint64_t* __restrict__ nint,
-                                                        unsigned long long* __restrict__ sum,
-                                                        unsigned long long* __restrict__ count,
-                                                        unsigned long long* __restrict__ alg, unsigned int* ticket) {
-  if (ticket && blockIdx.x == 0 && threadIdx.x == 0) *ticket = 0;
-  uint64_t visited = 0;
-  for (uint64_t i = blockIdx.x; i < a.q; i += gridDim.x) {
-    const uint64_t lo = a.lo[i], hi = a.hi[i];
-    uint64_t f = 0, n = 0;
-    LeafSum r{0, 0};
-    if (lo < hi) {
-      f = wave_locate_leaf(a.head, a.L, lo);
-      const uint64_t l = wave_locate_leaf(a.head, a.L, hi - 1);
-      const uint32_t uf = a.used[f];
-      r = a.raw ? wave_raw_sum_range(a.bytes + f * (uint64_t)a.S, uf, lo, hi)
-                : wave_leaf_sum_range(a.bytes + f * (uint64_t)a.S, uf, lo, hi);
-      visited += uf;
-      if (l != f) {
-        const uint32_t ul = a.used[l];
-        const LeafSum r2 = a.raw ? wave_raw_sum_range(a.bytes + l * (uint64_t)a.S, ul, lo, hi)
-                                 : wave_leaf_sum_range(a.bytes + l * (uint64_t)a.S, ul, lo, hi);
-        r.sum += r2.sum;
-        r.count += r2.count;
-        visited += ul;
-      }
-      n = (l > f + 1) ? l - f - 1 : 0;
-    }
-    if (lane_id() == 0) {
-      first_int[i] = f + 1;
-      nint[i] = n;
-      sum[i] = r.sum;
-      count[i] = r.count;
-    }
-  }
-  if (alg && lane_id() == 0) alg[blockIdx.x] = visited;
 }
 
 // ---- whole leaves, 32 per wave ------------------------------------------------------
@@ -638,30 +537,46 @@ __global__ void __launch_bounds__(1024) k_fold_sum(const unsigned long long* __r
   }
 }
 
-// Values of key-value leaves: one lane per key -- locate the leaf, walk its
-// codes to the key; found[i] = whether it is present, val[i] its value (0 if not).
+// Values of key-value leaves: found[i] = whether keys[i] is present, val[i] its
+// value (0 if not).  per: as in k_rm_ends.
 __global__ void __launch_bounds__(256) k_kv_get(QueryArgs a, const uint64_t* __restrict__ keys,
-                                                uint64_t* __restrict__ val, uint8_t* __restrict__ found) {
-  for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < a.q;
-       i += (uint64_t)gridDim.x * blockDim.x) {
-    const uint64_t x = keys[i];
-    const uint64_t leaf = locate_leaf(a.head, a.L, x);
-    const uint32_t codes = a.used[leaf];
-    const LeafSum r = kv_leaf_values(a.bytes + leaf * (uint64_t)a.S, codes, leaf_vals(a, leaf, codes), x, x + 1);
-    val[i] = r.sum;
-    found[i] = r.count ? 1 : 0;
+                                                uint64_t* __restrict__ val, uint8_t* __restrict__ found,
+                                                uint32_t per) {
+  __shared__ Reach reach[256 / kWave][kWave];
+  Reach* const mine = reach[threadIdx.x / kWave];
+  const uint32_t wave = blockIdx.x * (256 / kWave) + threadIdx.x / kWave, nwaves = gridDim.x * (256 / kWave);
+  for (uint64_t base = (uint64_t)wave * per; base < a.q; base += (uint64_t)nwaves * per) {
+    const uint64_t i = base + lane_id();
+    const bool valid = (uint32_t)lane_id() < per && i < a.q;
+    const uint64_t x = valid ? keys[i] : 0;
+    const uint64_t leaf = wave_locate(a, valid, x);
+    const Lookup r = wave_lookup<true, false, true>(a, valid, leaf, x, mine);
+    if (valid) {
+      uint64_t v = 0;
+      if (r.eq) {
+        const uint32_t m = (a.fill[leaf] - a.used[leaf]) / 8;
+        v = reinterpret_cast<const uint64_t*>(a.bytes + leaf * (uint64_t)a.S + a.S - 8u * m)[r.cnt];
+      }
+      val[i] = v;
+      found[i] = r.eq ? 1 : 0;
+    }
   }
 }
 
-// Membership: one lane per key -- locate the leaf, scan it for [x, x + 1).
+// Membership.  n: the number of keys on the device (NULL: a.q).
 __global__ void __launch_bounds__(256) k_contains(QueryArgs a, const uint64_t* __restrict__ keys,
-                                                  uint8_t* __restrict__ out) {
-  for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < a.q;
-       i += (uint64_t)gridDim.x * blockDim.x) {
-    const uint64_t x = keys[i];
-    const uint64_t leaf = locate_leaf(a.head, a.L, x);
-    const LeafSum r = leaf_range_any(a, leaf, a.used[leaf], x, x + 1);
-    out[i] = r.count ? 1 : 0;
+                                                  uint8_t* __restrict__ out, uint32_t per,
+                                                  const unsigned long long* __restrict__ n) {
+  __shared__ Reach reach[256 / kWave][kWave];
+  Reach* const mine = reach[threadIdx.x / kWave];
+  const uint32_t wave = blockIdx.x * (256 / kWave) + threadIdx.x / kWave, nwaves = gridDim.x * (256 / kWave);
+  const uint64_t q = n ? (uint64_t)*n : a.q;
+  for (uint64_t base = (uint64_t)wave * per; base < q; base += (uint64_t)nwaves * per) {
+    const uint64_t i = base + lane_id();
+    const bool valid = (uint32_t)lane_id() < per && i < q;
+    const uint64_t x = valid ? keys[i] : 0;
+    const Lookup r = wave_lookup<false, false, true>(a, valid, wave_locate(a, valid, x), x, mine);
+    if (valid) out[i] = r.eq ? 1 : 0;
   }
 }
 

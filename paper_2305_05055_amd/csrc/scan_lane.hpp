@@ -203,53 +203,4 @@ __device__ __forceinline__ LeafSum leaf_sum_range(const uint8_t* __restrict__ le
   return r;
 }
 
-// ---- uncompressed leaves (the plain PMA) ---------------------------------------
-// The uncompressed variant keeps the same leaves, tree and byte-density bounds,
-// but a leaf holds its keys as raw little-endian 8-byte words packed to the
-// left (used = 8 x keys, zero fill after them), with no delta codes (Section
-// "Packed Memory Array"; the ablation of Section "Evaluation on
-// microbenchmarks" that isolates what compression buys).
-
-// Sum and count of the keys in [lo, hi) of an uncompressed leaf, one lane.
-__device__ __forceinline__ LeafSum raw_sum_range(const uint8_t* __restrict__ leaf, uint32_t used, uint64_t lo,
-                                                 uint64_t hi) {
-  LeafSum r{0, 0};
-  const uint64_t* k = reinterpret_cast<const uint64_t*>(leaf);
-  const uint32_t m = used / 8;
-  for (uint32_t i = 0; i < m; i += 2) {
-    const uint4 w = *reinterpret_cast<const uint4*>(k + i);
-    const uint64_t a = ((uint64_t)w.y << 32) | w.x;
-    const uint64_t b = ((uint64_t)w.w << 32) | w.z;
-    if (a >= hi) break;
-    if (a >= lo) {
-      r.sum += a;
-      r.count++;
-    }
-    if (i + 1 < m) {
-      if (b >= hi) break;
-      if (b >= lo) {
-        r.sum += b;
-        r.count++;
-      }
-    }
-  }
-  return r;
-}
-
-// Sum and count of the keys in [lo, hi) of an uncompressed leaf, a whole wave on
-// one leaf (keys i = lane, lane + 64, ...).
-__device__ __forceinline__ LeafSum wave_raw_sum_range(const uint8_t* __restrict__ leaf, uint32_t used, uint64_t lo,
-                                                      uint64_t hi) {
-  const uint64_t* k = reinterpret_cast<const uint64_t*>(leaf);
-  uint64_t s = 0, n = 0;
-  for (uint32_t i = lane_id(); i < used / 8; i += kWave) {
-    const uint64_t x = k[i];
-    if (x >= lo && x < hi) {
-      s += x;
-      n++;
-    }
-  }
-  return LeafSum{wave_sum(s), wave_sum(n)};
-}
-
 }  // namespace cpma_dev

@@ -22,6 +22,27 @@ struct ArgKeys {
   uint64_t k[kArgKeys];
 };
 
+// Leaf of x by a 64-ary search of the heads (64 pivots compared per step, so a
+// few steps for millions of leaves), the whole wave on one key.
+__device__ __forceinline__ uint64_t wave_locate_leaf(const uint64_t* __restrict__ head, uint64_t L, uint64_t x) {
+  uint64_t lo = 0, hi = L;  // the first head above x lies in [lo, hi]
+  const uint32_t lane = (uint32_t)lane_id();
+  while (lo < hi) {
+    const uint64_t step = (hi - lo + kWave - 1) / kWave;
+    const uint64_t idx = lo + lane * step;
+    const bool le = idx < hi && head[idx] <= x;
+    const uint32_t t = (uint32_t)__popcll(__ballot(le));  // pivots at or below x form a prefix
+    if (t == 0) {
+      hi = lo;
+    } else {
+      const uint64_t last = lo + (uint64_t)(t - 1) * step;
+      lo = last + 1;
+      hi = min(hi, last + step);
+    }
+  }
+  return lo ? lo - 1 : 0;
+}
+
 // Exclusive scan of one value per thread over the workgroup; returns the
 // thread's offset, *total the sum.
 __device__ __forceinline__ uint32_t block_scan_u32(uint32_t v, uint32_t* wsum, uint32_t* total) {
