@@ -127,6 +127,10 @@ struct cpma {
   // a small batch's merge totals, left for the single-block path check to fold
   const unsigned long long* fin_parts = nullptr;
   uint32_t fin_nn = 0, fin_nw = 0;
+  // the current batch's merge, for giant slices found by it (giant_k: its keys, 0: none possible)
+  MergeArgs giant_args{};
+  uint64_t giant_k = 0;
+  uint32_t giant_n = 0;  // giant leaves of the current update, in the arena until a redistribution
   cpma_config cfg{};
   uint32_t S = 1024;
   uint64_t L = 0, n = 0;
@@ -140,7 +144,7 @@ struct cpma {
   DevBuf kin, kb0, kb1, kdedup, leafid, segpos, seg_leaf, seg_begin, seg_desc, heavy, spill, scan_tmp, ovf, arena,
       stage, pyr, win, wargs, cnt, koff, win_id, welem, P, ccost, ncost, lstart, planU, plan_used,
       spare_bytes, spare_used, spare_head, fg_level, fg_deg, fg_p, fg_c, fg_acc,
-      win_of_leaf, fail, qa, qb, qfirst, qnvis, qvoff, qsum, qcount, qout, qprefix, lastk, lckpt, ne_rank, ne_list, chain_pfx,
+      win_of_leaf, fail, qa, qb, qfirst, qnvis, qvoff, qsum, qcount, qout, qprefix, giant, lastk, lckpt, ne_rank, ne_list, chain_pfx,
       srec, wide, srcinfo, parts, qparts, fz_meta, fz_v0, fz_v1, fz_byte, fz_member, fz_code, fz_ctr, fz_res,
       ctr_buf, info_buf, qalg_buf, clen, spare_clen, vstage, kvals, kvdedup;
   // key-value sets: the current update batch's values (device, repeat-free and
@@ -184,7 +188,7 @@ struct cpma {
             &qout,      &lastk,     &ne_rank,   &ne_list,     &chain_pfx,  &srec,        &wide,       &srcinfo,
             &parts,     &qparts,    &fz_meta,   &fz_v0,       &fz_v1,      &fz_byte,     &fz_member,  &fz_code,
             &fz_ctr,    &fz_res,    &ctr_buf,   &info_buf,    &qalg_buf,   &lckpt,      &clen,        &spare_clen,
-            &vstage,    &kvals,     &kvdedup,   &qprefix};
+            &vstage,    &kvals,     &kvdedup,   &qprefix,  &giant};
   }
 
   Bounds bounds(uint64_t Lx) const {
@@ -697,14 +701,55 @@ SrcLeaves src_leaves(cpma* s) {
   return sl;
 }
 
+// Giant slices of a batch of at most kbound keys, and their pieces, at most; and
+// the piecewise merge's arrays in s->giant.
+struct GiantSizes {
+  uint64_t slices, pieces;
+};
+GiantSizes giant_sizes(uint64_t kbound) {
+  const uint64_t n = kbound / (kGiantSlice + 1);
+  return GiantSizes{n, kbound / kGiantPiece + n + 1};
+}
+size_t giant_bytes(uint64_t kbound) {
+  const GiantSizes z = giant_sizes(kbound);
+  return 8 * (z.slices + 1) + 32 * (z.pieces + 2);
+}
+// s->giant: the list of giant segments and their first pieces, then per piece its
+// bytes, their scan, the key before it, its keys and their scan.
+GiantArgs giant_arrays(cpma* s, uint32_t n, uint64_t** scan, uint32_t** key_scan) {
+  const GiantSizes z = giant_sizes(s->giant_k);
+  GiantArgs g;
+  g.list = s->giant.as<uint32_t>();
+  g.n = n;
+  g.first = s->giant.as<uint32_t>() + z.slices;
+  g.bytes = reinterpret_cast<uint64_t*>(s->giant.as<uint32_t>() + 2 * (z.slices + 1));
+  *scan = g.bytes + z.pieces;
+  g.scan = *scan;
+  g.prev = *scan + z.pieces + 1;
+  g.keys = reinterpret_cast<uint32_t*>(g.prev + z.pieces);
+  *key_scan = g.keys + z.pieces;
+  return g;
+}
+uint32_t* giant_list(cpma* s, uint64_t kbound) {
+  return kbound > kGiantSlice ? s->giant.as<uint32_t>() : nullptr;
+}
+
 // Pack (copy 1): decode the source leaves of every window into the staging
 // buffer.  Returns the number of staged keys K.
 uint64_t pack_windows(cpma* s, const WinArgs& wa, uint64_t nsrc, hipStream_t st) {
   ensure(s->cnt, nsrc * sizeof(uint64_t));
   ensure(s->koff, (nsrc + 1) * sizeof(uint64_t));
   const SrcLeaves sl = src_leaves(s);
+  GiantLeaves gl{};
+  GiantArgs ga{};
+  if (s->giant_n) {
+    uint64_t* scanned;
+    uint32_t* key_scan;
+    ga = giant_arrays(s, s->giant_n, &scanned, &key_scan);
+    gl = GiantLeaves{ga.list, s->giant_args.seg_leaf, ga.first, key_scan, ga.n};
+  }
   hipLaunchKernelGGL(k_win_count, dim3(grid_for(nsrc, 1, 1u << 20)), dim3(kWave), 0, st, wa, sl, nsrc,
-                     s->cnt.as<uint64_t>());
+                     s->cnt.as<uint64_t>(), gl);
   HIPCHK(hipGetLastError());
   scan<uint64_t>(s, s->koff.as<uint64_t>(), nsrc, st, LoadFn<uint64_t>{s->cnt.as<uint64_t>()});
   uint64_t K = 0;
@@ -717,7 +762,11 @@ uint64_t pack_windows(cpma* s, const WinArgs& wa, uint64_t nsrc, hipStream_t st)
   if (s->kv()) ensure(s->vstage, std::max<uint64_t>(K, 1) * sizeof(uint64_t));
   hipLaunchKernelGGL(k_win_pack, dim3(grid_for(nsrc, 1, 1u << 20)), dim3(kWave), 0, st, wa, sl, nsrc,
                      (const uint64_t*)s->koff.as<uint64_t>(), s->stage.as<uint64_t>(), s->win_id.as<uint32_t>(),
-                     s->ccost.as<uint8_t>(), s->kv() ? s->vstage.as<uint64_t>() : (uint64_t*)nullptr);
+                     s->ccost.as<uint8_t>(), gl, s->kv() ? s->vstage.as<uint64_t>() : (uint64_t*)nullptr);
+  if (gl.n)
+    hipLaunchKernelGGL(k_giant_pack, dim3(grid_for(s->giant_k / kGiantPiece + gl.n, 1, 1u << 16)), dim3(kWave), 0, st,
+                       wa, sl, s->giant_args, ga, gl.key_scan, (const uint64_t*)s->koff.as<uint64_t>(),
+                       s->stage.as<uint64_t>(), s->win_id.as<uint32_t>(), s->ccost.as<uint8_t>());
   HIPCHK(hipGetLastError());
   return K;
 }
@@ -821,6 +870,7 @@ bool redistribute(cpma* s, std::vector<Win> wins, hipStream_t st, uint64_t* move
     if (!any) {
       encode_spread(s, wa, ndst, s->bytes.as<uint8_t>(), s->used.as<uint32_t>(), s->head.as<uint64_t>(), st,
                     s->kv() ? s->clen.as<uint32_t>() : nullptr);
+      s->giant_n = 0;  // every overflowing leaf is spread now
       // algorithmic bytes: every window leaf read (at most S) and rewritten
       // whole with its used count and head
       *moved = ndst * (2ull * s->S + 12);
@@ -844,6 +894,7 @@ void swap_in_spare(cpma* s, uint64_t Lt) {
   std::swap(s->head, s->spare_head);
   if (s->kv()) std::swap(s->clen, s->spare_clen);
   s->L = Lt;
+  s->giant_n = 0;
 }
 
 // Spreads the K staged keys (sorted, one window) evenly over a fresh array of Lt
@@ -1194,6 +1245,31 @@ uint64_t take_merge(cpma* s, const Counters& c, int merged) {
   return c.delta;
 }
 
+// Merges the n giant slices the merge kernels left, piece by piece, after the
+// counters have been read: the batches that have none pay nothing for them.  The
+// totals are in the (cleared) counters.
+void merge_giants(cpma* s, uint32_t n, hipStream_t st) {
+  const GiantSizes z = giant_sizes(s->giant_k);
+  if (n > z.slices) throw Fail{CPMA_ERR_DEVICE};
+  PhaseMark ph = phase_begin(s, CPMA_PHASE_HEAVY, st);
+  uint64_t* scanned;
+  uint32_t* key_scan;
+  const GiantArgs g = giant_arrays(s, n, &scanned, &key_scan);
+  const uint64_t bound = s->giant_k / kGiantPiece + n;  // every slice rounds up by at most one
+  zero_counters(s, st);
+  hipLaunchKernelGGL(k_giant_plan, dim3(1), dim3(kHeavyThreads), 0, st, s->giant_args, g);
+  const uint32_t grid = (uint32_t)std::min<uint64_t>(bound, (uint64_t)s->num_cus * 16);
+  const uint32_t smem = giant_smem(s->S);
+  hipLaunchKernelGGL(k_giant_merge<false>, dim3(grid), dim3(kHeavyThreads), smem, st, s->giant_args, g, bound);
+  HIPCHK(hipGetLastError());
+  scan<uint64_t>(s, scanned, bound, st, LoadFn<uint64_t>{g.bytes});
+  scan<uint32_t>(s, key_scan, bound, st, LoadFn<uint32_t>{g.keys});
+  hipLaunchKernelGGL(k_giant_merge<true>, dim3(grid), dim3(kHeavyThreads), smem, st, s->giant_args, g, bound);
+  HIPCHK(hipGetLastError());
+  phase_end(s, ph, st);
+  s->giant_n = n;
+}
+
 // Counting + redistribution until every node of the implicit tree is within its
 // bounds.
 // merged: -1 after a build; 0 / 1 right after a delete / insert merge, whose
@@ -1234,8 +1310,8 @@ uint64_t rebalance(cpma* s, hipStream_t st, int merged = -1, uint64_t small_k = 
     if (!c.path_unsafe) return delta;  // the pyramid now holds the new sums
     s->pyr_valid = false;
   }
+  bool after_merge = merged >= 0 && !taken;  // the counters hold totals not taken yet
   for (int round = 0; round < 256; round++) {
-    const bool after_merge = round == 0 && merged >= 0 && !taken;
     PhaseMark pc = phase_begin(s, CPMA_PHASE_COUNT, st);
     Pyramid P = make_pyramid(s, s->L);
     build_pyramid(s, P, s->used.as<uint32_t>(), s->L, st);
@@ -1250,7 +1326,14 @@ uint64_t rebalance(cpma* s, hipStream_t st, int merged = -1, uint64_t small_k = 
     phase_end(s, pc, st, 4ull * s->L + 16ull * nodes);
     read_counters(s, st);
     const Counters c = *s->hctr;
-    if (after_merge) delta = take_merge(s, c, merged);
+    if (after_merge) {
+      delta += take_merge(s, c, merged);
+      if (c.ngiant) {
+        merge_giants(s, c.ngiant, st);
+        continue;  // count again, with their sizes
+      }
+      after_merge = false;
+    }
     if (c.root_viol) {
       PhaseMark pr = phase_begin(s, CPMA_PHASE_REDIST, st);
       const uint64_t moved = resize(s, c.root_sum, c.root_viol, st);
@@ -1304,18 +1387,24 @@ uint64_t rebalance(cpma* s, hipStream_t st, int merged = -1, uint64_t small_k = 
 // resize, checking every node of the new tree before it writes.  Returns the
 // merge's delta.
 uint64_t rebuild(cpma* s, hipStream_t st, int merged) {
-  PhaseMark pc = phase_begin(s, CPMA_PHASE_COUNT, st);
-  Pyramid P = make_pyramid(s, s->L);
-  build_pyramid(s, P, s->used.as<uint32_t>(), s->L, st);
-  ensure(s->win, std::max<uint64_t>(s->L, 1) * sizeof(uint64_t));
-  const uint64_t nodes = (P.H == 0) ? 1 : P.off[P.H] + P.cnt[P.H];
-  hipLaunchKernelGGL(k_select, dim3(grid_for(nodes, 256, 1u << 16)), dim3(256), 0, st, s->bounds(s->L), P,
-                     (const uint32_t*)s->used.as<uint32_t>(), s->win.as<uint64_t>(), s->dctr);
-  HIPCHK(hipGetLastError());
-  phase_end(s, pc, st, 4ull * s->L + 16ull * nodes);
-  read_counters(s, st);
-  const Counters c = *s->hctr;
-  const uint64_t delta = take_merge(s, c, merged);
+  uint64_t delta = 0;
+  Counters c;
+  for (;;) {
+    PhaseMark pc = phase_begin(s, CPMA_PHASE_COUNT, st);
+    Pyramid P = make_pyramid(s, s->L);
+    build_pyramid(s, P, s->used.as<uint32_t>(), s->L, st);
+    ensure(s->win, std::max<uint64_t>(s->L, 1) * sizeof(uint64_t));
+    const uint64_t nodes = (P.H == 0) ? 1 : P.off[P.H] + P.cnt[P.H];
+    hipLaunchKernelGGL(k_select, dim3(grid_for(nodes, 256, 1u << 16)), dim3(256), 0, st, s->bounds(s->L), P,
+                       (const uint32_t*)s->used.as<uint32_t>(), s->win.as<uint64_t>(), s->dctr);
+    HIPCHK(hipGetLastError());
+    phase_end(s, pc, st, 4ull * s->L + 16ull * nodes);
+    read_counters(s, st);
+    c = *s->hctr;
+    delta += take_merge(s, c, merged);
+    if (!c.ngiant) break;
+    merge_giants(s, c.ngiant, st);
+  }
   PhaseMark pr = phase_begin(s, CPMA_PHASE_REDIST, st);
   if (s->n == 0) {
     spread_fresh(s, 0, 1, st);
@@ -1351,7 +1440,7 @@ MergeGrids merge_grids(const cpma* s, uint64_t kbound) {
   m.wgrid = std::max(1u, (uint32_t)std::min<uint64_t>(segs, (uint64_t)s->num_cus * 320));
   m.lwaves = std::max(1u, m.lgrid) * (256 / kWave);
   // heavy merge of spilled slices: at most kbound / (kWaveSlice + 1) of them,
-  // a few LDS-bound waves per CU
+  // a few LDS-bound blocks per CU
   m.hgrid_spill =
       (uint32_t)std::min<uint64_t>(std::max<uint64_t>(1, kbound / (kWaveSlice + 1)), (uint64_t)s->num_cus * 4);
   m.part_slots = 2ull * m.wgrid + 2ull * m.lwaves + std::max(m.hgrid_spill, 1024u);
@@ -1390,6 +1479,11 @@ void reserve_batch(cpma* s, uint64_t kbound, bool insert) {
   }
   ensure(s->stage, stage_cap * sizeof(uint64_t));
   ensure(s->parts, 16ull * merge_grids(s, kbound).part_slots);
+  if (insert && !s->kv() && kbound > kGiantSlice) {
+    // piecewise merge: the list of giant segments, their first pieces, and the
+    // pieces' byte counts with their scan
+    ensure(s->giant, giant_bytes(kbound));
+  }
   ensure(s->scan_tmp, scan_scratch_elems(kl + 1) * sizeof(uint64_t));
   reserve_after_merge(s, kbound, insert);
 }
@@ -1482,6 +1576,9 @@ uint64_t apply_batch(cpma* s, const uint64_t* B, uint64_t kbound, bool insert, h
   }
   phase_end(s, pl, st, 24ull * kbound);
   MergeArgs a = merge_args(s, B, insert);
+  s->giant_n = 0;
+  s->giant_args = a;
+  s->giant_k = insert && !small && !s->cfg.uncompressed && !s->kv() ? kbound : 0;
   const MergeGrids mg = merge_grids(s, kbound);
   const uint32_t lgrid = mg.lgrid, wgrid = mg.wgrid, lwaves = mg.lwaves, hgrid_spill = mg.hgrid_spill;
   // per-wave totals: each launch owns a run of slot pairs, main-merge launches
@@ -1517,8 +1614,8 @@ uint64_t apply_batch(cpma* s, const uint64_t* B, uint64_t kbound, bool insert, h
     if (insert && kbound > kWaveSlice) {
       // a slice of more than kWaveSlice keys spills to the heavy merge
       a.part = slots(hgrid_spill, false);
-      hipLaunchKernelGGL(k_merge_heavy, dim3(hgrid_spill), dim3(kWave), heavy_smem(s->S, kHeavyLds), st, a,
-                         kHeavyLds, 1);
+      hipLaunchKernelGGL(k_merge_heavy, dim3(hgrid_spill), dim3(kHeavyThreads), heavy_smem(s->S, kHeavyLds), st, a,
+                         kHeavyLds, 1, (uint32_t*)nullptr);
     }
     HIPCHK(hipGetLastError());
     phase_end(s, pmg, st);
@@ -1532,8 +1629,8 @@ uint64_t apply_batch(cpma* s, const uint64_t* B, uint64_t kbound, bool insert, h
     hipLaunchKernelGGL(k_merge_wave<uint64_t>, dim3(wgrid), dim3(kWave), 0, st, a);
     if (insert) {  // long insert slices, one wave each
       a.part = slots(hgrid_spill, false);
-      hipLaunchKernelGGL(k_merge_heavy, dim3(hgrid_spill), dim3(kWave), heavy_smem(s->S, kHeavyLds), st, a,
-                         kHeavyLds, 1);
+      hipLaunchKernelGGL(k_merge_heavy, dim3(hgrid_spill), dim3(kHeavyThreads), heavy_smem(s->S, kHeavyLds), st, a,
+                         kHeavyLds, 1, giant_list(s, kbound));
     }
     HIPCHK(hipGetLastError());
     phase_end(s, ph, st);
@@ -1546,7 +1643,8 @@ uint64_t apply_batch(cpma* s, const uint64_t* B, uint64_t kbound, bool insert, h
       const uint32_t hgrid = (uint32_t)std::min<uint64_t>(std::max<uint64_t>(1, kbound / kLaneHeavy), 1024);
       PhaseMark ph = phase_begin(s, CPMA_PHASE_HEAVY, st);
       a.part = slots(hgrid, false);
-      hipLaunchKernelGGL(k_merge_heavy, dim3(hgrid), dim3(kWave), heavy_smem(s->S, 0), st, a, 0u, 0);
+      hipLaunchKernelGGL(k_merge_heavy, dim3(hgrid), dim3(kHeavyThreads), heavy_smem(s->S, 0), st, a, 0u, 0,
+                         giant_list(s, kbound));
       HIPCHK(hipGetLastError());
       phase_end(s, ph, st);
     }
@@ -1575,6 +1673,7 @@ bool wants_rebuild(const cpma* s, uint64_t k) {
 // Host keys (src null) come in `ak`, at most kArgKeys of them.
 uint64_t apply_small(cpma* s, const uint64_t* src, uint64_t k, bool insert, hipStream_t st,
                      const ArgKeys* ak = nullptr) {
+  s->giant_n = 0;
   reserve_batch(s, k, insert);
   static const ArgKeys kNoArgKeys{};
   if (k <= kWaveSlice && s->S <= kWaveMaxS && !s->cfg.uncompressed && !s->kv() && !s->stats_on &&

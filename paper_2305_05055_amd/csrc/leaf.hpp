@@ -121,6 +121,87 @@ __device__ __forceinline__ uint32_t wave_decode_leaf(const uint8_t* __restrict__
   return run_cnt;
 }
 
+// Bytes [from, to) of a leaf image that begin and end at code boundaries: emit
+// (index, key, delta) for their keys, the first one's delta counted from `prev`
+// (head: the bytes start with the leaf's head).
+template <class Emit>
+__device__ __forceinline__ void wave_decode_piece(const uint8_t* __restrict__ src, uint64_t from, uint64_t to, bool head,
+                                                  uint64_t prev, Emit&& emit) {
+  const int lane = lane_id();
+  uint64_t run_key = head ? 0 : prev, carry_acc = 0;
+  uint32_t run_cnt = 0, carry_sh = 0;
+  for (uint64_t base = from & ~15ull; base < to; base += 16u * kWave) {
+    const uint64_t pos0 = base + 16u * lane;
+    uint4 w = make_uint4(0, 0, 0, 0);
+    if (pos0 < to) w = *reinterpret_cast<const uint4*>(src + pos0);
+    uint32_t words[4] = {w.x, w.y, w.z, w.w};
+    // bytes before the piece become continuation bytes that carry nothing: the
+    // code that follows them starts in the lane at shift 0 again
+    LaneCodes c;
+    c.tmask = 0;
+    c.first_raw = 0;
+    uint64_t acc = 0;
+    uint32_t sh = 0;
+    bool seen = false;
+#pragma unroll
+    for (int i = 0; i < 16; i++) {
+      const uint64_t pos = pos0 + (uint32_t)i;
+      const uint32_t b = (words[i >> 2] >> (8 * (i & 3))) & 0xffu;
+      const bool valid = pos < to && pos >= (head ? 8 : from);
+      if (valid && sh < 64) acc |= (uint64_t)(b & 0x7fu) << sh;
+      const bool term = valid && !(b & 0x80u);
+      c.v[i] = term ? acc : 0ull;
+      if (term) {
+        if (!seen) c.first_raw = acc;
+        seen = true;
+        c.tmask |= 1u << i;
+        acc = 0;
+        sh = 0;
+      } else if (valid) {
+        sh += 7;
+      }
+    }
+    if (head && pos0 == 0) {
+      c.v[7] = ((uint64_t)words[1] << 32) | words[0];
+      c.tmask |= 1u << 7;
+    }
+    uint64_t cin_acc = dpp_prev64(acc);
+    uint32_t cin_sh = dpp_prev32(sh);
+    if (lane == 0) {
+      cin_acc = carry_acc;
+      cin_sh = carry_sh;
+    }
+    uint64_t corr = 0;
+    if (c.tmask != 0 && !(head && pos0 == 0)) {
+      const uint64_t fixed = cin_acc | (cin_sh < 64 ? (c.first_raw << cin_sh) : 0ull);
+      corr = fixed - c.first_raw;
+    }
+    uint64_t lsum = corr;
+#pragma unroll
+    for (int i = 0; i < 16; i++) lsum += c.v[i];
+    const uint32_t lcnt = (uint32_t)__popc(c.tmask);
+    const uint64_t incl_sum = wave_incl_scan(lsum);
+    const uint32_t incl_cnt = wave_incl_scan(lcnt);
+    uint64_t key = run_key + (incl_sum - lsum);
+    uint64_t pend = corr;
+    uint32_t idx = run_cnt + (incl_cnt - lcnt);
+#pragma unroll
+    for (int i = 0; i < 16; i++) {
+      if (c.tmask & (1u << i)) {
+        const uint64_t d = c.v[i] + pend;
+        pend = 0;
+        key += d;
+        emit(idx, key, d);
+        idx++;
+      }
+    }
+    run_key += lane63_u64(incl_sum);
+    run_cnt += lane63_u32(incl_cnt);
+    carry_acc = lane63_u64(acc);
+    carry_sh = lane63_u32(sh);
+  }
+}
+
 // Single-chunk variant (leaf size <= 1024): the caller has already loaded the
 // lane's 16 bytes w (zeros past `used`).
 template <class Emit>
@@ -244,20 +325,6 @@ __device__ __forceinline__ uint32_t wave_count_keys(const uint8_t* __restrict__ 
     }
   }
   return wave_sum(cnt);
-}
-
-// Encoded size of keys get(0..m): 8 bytes for the head, then one code per delta.
-template <class Get>
-__device__ __forceinline__ uint64_t wave_encoded_size(Get&& get, uint32_t m) {
-  const int lane = lane_id();
-  uint64_t tot = 0;
-  for (uint32_t base = 0; base < m; base += kWave) {
-    const uint32_t i = base + lane;
-    uint32_t c = 0;
-    if (i < m) c = (i == 0) ? 8u : vlen(get(i) - get(i - 1));
-    tot += wave_sum(c);
-  }
-  return tot;
 }
 
 // Writes the encoding of get(0..m) to dst (LDS or global, byte granular).

@@ -26,6 +26,8 @@ struct Counters {
   unsigned long long alg_bytes_h;   // algorithmic HBM bytes of the follow-up merges (statistics)
   unsigned int reserved;            // a small batch held the reserved key (nothing was changed)
   unsigned int path_unsafe;         // a node on a touched path left its bounds (small-batch count)
+  unsigned int ngiant;              // segments left to the piecewise merge
+  unsigned int pad;
 };
 
 __device__ __forceinline__ uint64_t lower_bound_u64(const uint64_t* a, uint64_t n, uint64_t x) {
@@ -43,6 +45,18 @@ __device__ __forceinline__ uint64_t upper_bound_u64(const uint64_t* a, uint64_t 
   uint64_t lo = 0, hi = n;
   while (lo < hi) {
     uint64_t mid = (lo + hi) >> 1;
+    if (a[mid] <= x)
+      lo = mid + 1;
+    else
+      hi = mid;
+  }
+  return lo;
+}
+
+__device__ __forceinline__ uint32_t upper_bound_u32(const uint32_t* a, uint32_t n, uint32_t x) {
+  uint32_t lo = 0, hi = n;
+  while (lo < hi) {
+    const uint32_t mid = (lo + hi) >> 1;
     if (a[mid] <= x)
       lo = mid + 1;
     else
@@ -271,64 +285,6 @@ __device__ __forceinline__ uint32_t lds_lower_bound(const KT* A, uint32_t n, KT 
   return lo;
 }
 
-// Exclusive prefix sum in place over F[0..n) (one wave).
-__device__ __forceinline__ void wave_scan_inplace(uint32_t* F, uint32_t n) {
-  uint32_t run = 0;
-  for (uint32_t base = 0; base < n; base += kWave) {
-    const uint32_t i = base + lane_id();
-    const uint32_t v = i < n ? F[i] : 0u;
-    const uint32_t incl = wave_incl_scan(v);
-    if (i < n) F[i] = run + incl - v;
-    run += lane63_u32(incl);
-  }
-}
-
-// Writes keys get(0..m) into leaf `leaf`: in place if they fit, else into the
-// overflow arena (the paper's out-of-place memory for an overflowing leaf,
-// cleaned up by the redistribution).  Only the first max(old_used, new size)
-// bytes are rewritten: the rest of the leaf is already zero.  Updates used /
-// head / ovf and returns the bytes written.
-template <class Get>
-__device__ uint64_t wave_store_leaf(const MergeArgs& a, uint64_t seg, uint64_t leaf, Get&& get, uint32_t m,
-                                    uint8_t* buf, uint32_t old_used) {
-  const int lane = lane_id();
-  uint8_t* dst = a.bytes + leaf * (uint64_t)a.S;
-  if (m == 0) {
-    wave_zero(dst, (old_used + 15u) & ~15u);
-    if (lane == 0) {
-      a.used[leaf] = 0;
-      a.head[leaf] = kNoKey;
-    }
-    return old_used;
-  }
-  const uint64_t T = wave_encoded_size(get, m);
-  uint64_t written;
-  if (T <= a.S) {
-    const uint32_t len = ((uint32_t)max((uint64_t)old_used, T) + 15u) & ~15u;
-    wave_zero(buf, len);
-    __syncthreads();
-    wave_encode_bytes(get, m, buf);
-    __syncthreads();
-    wave_copy16(dst, buf, len);
-    written = len;
-  } else {
-    const uint64_t need = (T + 15) & ~15ull;
-    const uint64_t off = arena_region(a, seg);
-    if (off + need > a.arena_cap) {
-      if (lane == 0) atomicOr(&a.ctr->error, 1u);
-      return 0;
-    }
-    wave_encode_bytes(get, m, a.arena + off);
-    if (lane == 0) a.ovf[leaf] = off;
-    written = T;
-  }
-  if (lane == 0) {
-    a.used[leaf] = (uint32_t)T;
-    a.head[leaf] = get(0);
-  }
-  return written;
-}
-
 // ---- counting phase: byte sums of every node of the implicit tree ----------------
 constexpr int kPyrThreads = 256;
 constexpr int kPyrLowLevels = 9;  // levels 1..9 per block of 512 leaves
@@ -457,12 +413,41 @@ __device__ __forceinline__ const uint8_t* kv_values(const uint8_t* base, uint32_
   return u > S ? base + ((clen + 7u) & ~7u) : base + S - (u - clen);
 }
 
+// The giant leaves of the update (see merge_heavy.hpp), which k_win_count takes from
+// their pieces and k_win_pack leaves to k_giant_pack; n = 0: none.
+struct GiantLeaves {
+  const uint32_t* list;      // segments
+  const uint32_t* seg_leaf;
+  const uint32_t* first;     // each giant's first piece
+  const uint32_t* key_scan;  // exclusive scan of the pieces' keys
+  uint32_t n;
+};
+// The giant (its index, ~0: none) whose leaf this is, by one wave.
+__device__ __forceinline__ uint32_t find_giant(const uint32_t* list, uint32_t n, const uint32_t* seg_leaf,
+                                               uint64_t leaf) {
+  for (uint32_t base = 0; base < n; base += kWave) {
+    const uint32_t i = base + (uint32_t)lane_id();
+    const uint64_t hit = __ballot(i < n && seg_leaf[list[i]] == leaf);
+    if (hit) return base + (uint32_t)__ffsll((unsigned long long)hit) - 1u;
+  }
+  return ~0u;
+}
+
+constexpr uint32_t kGiantMinBytes = 4096;  // a giant leaf holds more distinct keys than this
+
 __global__ void __launch_bounds__(kWave) k_win_count(WinArgs wa, SrcLeaves src, uint64_t nflat,
-                                                     uint64_t* __restrict__ cnt) {
+                                                     uint64_t* __restrict__ cnt, GiantLeaves gl) {
   for (uint64_t f = blockIdx.x; f < nflat; f += gridDim.x) {
     const uint32_t w = find_window(wa.src_flat, wa.W, f);
     const uint64_t leaf = wa.src_begin[w] + (f - wa.src_flat[w]);
     const uint32_t u = src.used[leaf];
+    if (gl.n && u > kGiantMinBytes) {
+      const uint32_t gi = find_giant(gl.list, gl.n, gl.seg_leaf, leaf);
+      if (gi != ~0u) {
+        if (lane_id() == 0) cnt[f] = gl.key_scan[gl.first[gi + 1]] - gl.key_scan[gl.first[gi]];
+        continue;
+      }
+    }
     const uint32_t c = wa.raw ? u / 8 : (wa.vbytes ? (u - src.clen[leaf]) / 8 : wave_count_keys(src.ptr(leaf, u), u));
     if (lane_id() == 0) cnt[f] = c;
   }
@@ -475,12 +460,13 @@ __global__ void __launch_bounds__(kWave) k_win_pack(WinArgs wa, SrcLeaves src, u
                                                     const uint64_t* __restrict__ koff,
                                                     uint64_t* __restrict__ stage,
                                                     uint32_t* __restrict__ win_id,
-                                                    uint8_t* __restrict__ ccost,
+                                                    uint8_t* __restrict__ ccost, GiantLeaves gl,
                                                     uint64_t* __restrict__ vstage = nullptr) {
   for (uint64_t f = blockIdx.x; f < nflat; f += gridDim.x) {
     const uint32_t w = find_window(wa.src_flat, wa.W, f);
     const uint64_t leaf = wa.src_begin[w] + (f - wa.src_flat[w]);
     const uint32_t u = src.used[leaf];
+    if (gl.n && u > kGiantMinBytes && find_giant(gl.list, gl.n, gl.seg_leaf, leaf) != ~0u) continue;
     uint64_t* out = stage + koff[f];
     uint32_t* wid = win_id + koff[f];
     uint8_t* cc = ccost + koff[f];
