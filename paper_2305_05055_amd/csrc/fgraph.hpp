@@ -26,34 +26,56 @@ struct FgArgs {
   uint32_t nv;  // vertex ids are < nv; keys with a larger id are ignored
 };
 
-// Keys of one leaf in the lane's registers: kk[i] is valid where bit i of tmask
-// is set (the code ending at byte i of the lane's 16 bytes).
+// Keys of one leaf in the lane's registers: kk[i] is valid where bit i of the
+// result is set (a code or the head ends at byte i of the lane's 16 bytes).
+//
+// A key is the head plus the payload of every code byte before it, each byte's
+// 7 bits shifted by 7 times its place in its code, so a running sum of shifted
+// payloads over the bytes, read at a code's last byte, is that key's offset; the
+// shift a code carries in is 7 times the lane before's run of trailing
+// continuation bytes, and one wave scan of the lanes' totals gives every lane its
+// start.
 __device__ __forceinline__ uint32_t wave_leaf_keys(const uint8_t* __restrict__ src, uint32_t used,
                                                    uint64_t (&kk)[16]) {
   const int lane = lane_id();
   const uint32_t pos0 = 16u * lane;
   uint4 w = make_uint4(0, 0, 0, 0);
   if (pos0 < used) w = *reinterpret_cast<const uint4*>(src + pos0);
-  LaneCodes c;
-  lane_parse(w, pos0, used, c);
-  const uint64_t cin_acc = dpp_prev64(c.tail_acc);
-  const uint32_t cin_sh = dpp_prev32(c.tail_sh);
-  uint64_t corr = 0;
-  if (c.tmask != 0 && pos0 != 0) {
-    const uint64_t fixed = cin_acc | (cin_sh < 64 ? (c.first_raw << cin_sh) : 0ull);
-    corr = fixed - c.first_raw;
+  const uint32_t nvalid = pos0 < used ? min(16u, used - pos0) : 0u;
+  uint32_t vm = nvalid >= 16u ? 0xffffu : ((1u << nvalid) - 1u);
+  uint64_t lead = 0;  // the head, in lane 0
+  if (lane == 0) {
+    vm &= 0xff00u;  // the head is not a code
+    if (used >= 8u) lead = ((uint64_t)w.y << 32) | w.x;
+    w.x = 0;
+    w.y = 0;
   }
-  uint64_t lsum = corr;
+  uint32_t words[4] = {w.x, w.y, w.z, w.w};
+  if (nvalid < 16u) {  // values may lie past `used`
 #pragma unroll
-  for (int i = 0; i < 16; i++) lsum += c.v[i];
-  const uint64_t incl = wave_incl_scan(lsum);
-  uint64_t key = incl - lsum + corr;
-#pragma unroll
-  for (int i = 0; i < 16; i++) {
-    key += c.v[i];
-    kk[i] = key;
+    for (int k = 0; k < 4; k++) {
+      const int32_t v = (int32_t)nvalid - 4 * k;
+      words[k] &= v >= 4 ? 0xffffffffu : (v <= 0 ? 0u : ((1u << (8 * v)) - 1u));
+    }
   }
-  return c.tmask;
+  const uint32_t msb = msb_nibble(words[0]) | (msb_nibble(words[1]) << 4) | (msb_nibble(words[2]) << 8) |
+                       (msb_nibble(words[3]) << 12);
+  const uint32_t cm = vm & msb;  // continuation bytes
+  uint32_t sh = 7u * dpp_prev32((uint32_t)__clz((int)~(cm << 16)));
+  uint64_t run = lead;
+#pragma unroll
+  for (int j = 0; j < 16; j++) {
+    const uint32_t x = words[j >> 2];
+    uint32_t c;
+    asm("v_bfe_i32 %0, %1, %2, 1" : "=v"(c) : "v"(x), "i"(8 * (j & 3) + 7));
+    run += (uint64_t)__builtin_amdgcn_ubfe(x, 8 * (j & 3), 7) << (sh & 63u);
+    kk[j] = run;
+    sh = (sh + 7u) & c;
+  }
+  const uint64_t ex = wave_incl_scan(run) - run;
+#pragma unroll
+  for (int j = 0; j < 16; j++) kk[j] += ex;
+  return (vm & ~msb) | (lane == 0 && used >= 8u ? 1u << 7 : 0u);
 }
 
 __device__ __forceinline__ uint32_t src_of(uint64_t k) { return (uint32_t)(k >> 32); }
