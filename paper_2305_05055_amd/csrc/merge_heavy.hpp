@@ -346,7 +346,8 @@ __global__ void __launch_bounds__(kHeavyThreads) k_giant_merge(MergeArgs a, Gian
     __syncthreads();
     const uint32_t m = r1 - r0 + nnew;
     const bool has_pred = c0 > 0;
-    const uint64_t pred = has_pred ? max(Bs[c0 - 1], r0 ? A[r0 - 1] : 0ull) : 0ull;
+    uint64_t pred = has_pred ? Bs[c0 - 1] : 0;
+    if (has_pred && r0 && A[r0 - 1] > pred) pred = A[r0 - 1];
     const HeavyRun run = heavy_plan(M, m, has_pred, pred, wsum);
     if (!kWrite) {
       if (tid == 0) {

@@ -401,7 +401,7 @@ __global__ void __launch_bounds__(256, 4) k_rm_interior(QueryArgs a, const uint6
     step = (uint64_t)gridDim.x * (256 / kWave);
     g = (uint64_t)blockIdx.x * (256 / kWave) + (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
     const uint64_t share = (V + step - 1) / step;
-    G = max(1ull, min((uint64_t)kWave * chunk, (share + kStepLeaves - 1) / kStepLeaves * kStepLeaves));
+    G = max<uint64_t>(1, min<uint64_t>((uint64_t)kWave * chunk, (share + kStepLeaves - 1) / kStepLeaves * kStepLeaves));
     end = V;
   }
   uint64_t cq = ~0ull, cs = 0;  // carried query (wave-uniform) and this lane's share of its sum

@@ -65,3 +65,13 @@ def test_several(cp, orc, S, rebuild):
     expect = run(c, keys, batch, orc)
     run(c, expect, np.concatenate(parts)[::-1] + np.uint64(1), orc)
     c.close()
+
+
+@pytest.mark.parametrize("k", [20000, 100000])
+def test_wide_keys(cp, orc, k):
+    """Keys above 2^53: the code at a piece's start counts from the exact key
+    before it, an old key or a batch key."""
+    keys = orc.build_set(synth.uniform_keys(5000, 7400, bits=63))
+    c = cp.CPMA(keys)
+    run(c, keys, synth.uniform_keys(k, 7401, bits=64), orc)
+    c.close()
