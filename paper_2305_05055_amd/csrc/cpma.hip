@@ -324,6 +324,70 @@ void scan(cpma* s, T* out, uint64_t n, hipStream_t st, F fn) {
   HIPCHK(scan_exclusive<T>(fn, n, out, s->scan_tmp.as<T>(), st));
 }
 
+// k_validate on a block per 4 iterations of a wave's loads, 256 to 1024 of
+// them: every block ends with atomics on one struct, about 7 ns each once they
+// queue up (1e6 keys: 3907 blocks 30 us, 256 blocks 12).
+void launch_validate(const uint64_t* keys, uint64_t k, BatchInfo* info, hipStream_t st) {
+  const uint64_t most = std::min<uint64_t>(std::max<uint64_t>(k >> 14, 256), 1024);
+  const uint32_t grid = (uint32_t)std::min<uint64_t>((k + 1023) / 1024, most);
+  hipLaunchKernelGGL(k_validate, dim3(grid), dim3(256), 0, st, keys, k, info);
+}
+
+uint32_t sort_blocks(uint64_t k) {
+  const uint64_t tile = (uint64_t)kSortThreads * (k <= kSortSmallKeys ? kSortItemsSmall : kSortItems);
+  return (uint32_t)((k + tile - 1) / tile);
+}
+
+// s->cnt for the digit counts of k keys.
+void sort_hist_buffer(cpma* s, uint64_t k) { ensure(s->cnt, ((uint64_t)sort_blocks(k) * 256 + 1) * sizeof(uint32_t)); }
+
+// LSD radix passes (8-bit digits, `passes` of them) over k keys from src,
+// alternating between kb0 and kb1; with kv every key carries a 32-bit value
+// (fz_v0, fz_v1) that the first pass makes from its position and vgen.  Returns
+// where the sorted keys are, their values in *vout.  hist0: the first digit's
+// counts are already in s->cnt.
+const uint64_t* lsd_sort(cpma* s, const uint64_t* src, uint64_t k, int passes, hipStream_t st, bool hist0 = false,
+                         bool kv = false, const uint8_t* vgen = nullptr, const uint32_t** vsorted = nullptr) {
+  const bool small = k <= kSortSmallKeys;
+  const uint32_t nblk = sort_blocks(k);
+  const bool sums = nblk <= kSortSumTiles;  // the scatter adds the counts up itself
+  sort_hist_buffer(s, k);
+  if (!sums) ensure(s->koff, ((uint64_t)nblk * 256 + 1) * sizeof(uint32_t));
+  ensure(s->kb0, k * sizeof(uint64_t));
+  ensure(s->kb1, k * sizeof(uint64_t));
+  if (kv) {
+    ensure(s->fz_v0, k * sizeof(uint32_t));
+    ensure(s->fz_v1, k * sizeof(uint32_t));
+  }
+  const uint64_t* in = src;
+  const uint32_t* vin = nullptr;
+  for (int p = 0; p < passes; p++) {
+    uint64_t* out = (p & 1) ? s->kb1.as<uint64_t>() : s->kb0.as<uint64_t>();
+    uint32_t* vout = (p & 1) ? s->fz_v1.as<uint32_t>() : s->fz_v0.as<uint32_t>();
+    if (p > 0 || !hist0) {  // else the first pass's counts came with the validation
+      hipLaunchKernelGGL(small ? k_radix_hist<kSortItemsSmall> : k_radix_hist<kSortItems>, dim3(nblk),
+                         dim3(kSortThreads), 0, st, in, (uint32_t)k, 8 * p, s->cnt.as<uint32_t>());
+      HIPCHK(hipGetLastError());
+    }
+    const uint32_t* off = s->cnt.as<uint32_t>();
+    if (!sums) {
+      scan<uint32_t>(s, s->koff.as<uint32_t>(), (uint64_t)nblk * 256, st, LoadFn<uint32_t>{s->cnt.as<uint32_t>()});
+      off = s->koff.as<uint32_t>();
+    }
+    if (kv)
+      hipLaunchKernelGGL(small ? k_radix_scatter_kv<kSortItemsSmall> : k_radix_scatter_kv<kSortItems>, dim3(nblk),
+                         dim3(kSortThreads), 0, st, in, out, (uint32_t)k, 8 * p, off, vin, vgen, vout);
+    else
+      hipLaunchKernelGGL(small ? k_radix_scatter<kSortItemsSmall> : k_radix_scatter<kSortItems>, dim3(nblk),
+                         dim3(kSortThreads), 0, st, in, out, (uint32_t)k, 8 * p, off);
+    HIPCHK(hipGetLastError());
+    in = out;
+    vin = vout;
+  }
+  if (vsorted) *vsorted = vin;
+  return in;
+}
+
 // MSD split of an unsorted batch into buckets small enough for one block's
 // LDS, then every bucket sorted there with its repeats removed (src -> kb0 ->
 // kb1), then the buckets' first occurrences packed into kdedup (their number
@@ -446,9 +510,7 @@ const uint64_t* prepare_batch(cpma* s, const uint64_t* keys, uint64_t k, cpma_me
   // validation reads every key once; below the MSD split's size it also
   // counts the first radix digit per sort tile (used if the batch turns out
   // unsorted)
-  const uint32_t nblk = (uint32_t)((k + kSortTile - 1) / kSortTile);
-  ensure(s->cnt, ((uint64_t)nblk * 256 + 1) * sizeof(uint32_t));
-  ensure(s->koff, ((uint64_t)nblk * 256 + 1) * sizeof(uint32_t));
+  sort_hist_buffer(s, k);
   // batches of the MSD split's size: with the bit length of the last such
   // batch, validation also counts the split's buckets and the bucket starts
   // are scanned before the one read-back
@@ -466,9 +528,10 @@ const uint64_t* prepare_batch(cpma* s, const uint64_t* keys, uint64_t k, cpma_me
     HIPCHK(hipGetLastError());
     msd_offsets(s, guess, st, true);
   } else if (!hist0) {
-    hipLaunchKernelGGL(k_validate, dim3(grid_for(k, 256, 4096)), dim3(256), 0, st, src, k, s->dinfo);
+    launch_validate(src, k, s->dinfo, st);
   } else {
-    hipLaunchKernelGGL(k_validate_hist, dim3(nblk), dim3(kSortThreads), 0, st, src, (uint32_t)k, s->dinfo,
+    hipLaunchKernelGGL(k <= kSortSmallKeys ? k_validate_hist<kSortItemsSmall> : k_validate_hist<kSortItems>,
+                       dim3(sort_blocks(k)), dim3(kSortThreads), 0, st, src, (uint32_t)k, s->dinfo,
                        s->cnt.as<uint32_t>());
   }
   HIPCHK(hipGetLastError());
@@ -512,35 +575,23 @@ const uint64_t* prepare_batch(cpma* s, const uint64_t* keys, uint64_t k, cpma_me
         }
       }
     }
-    const uint64_t* in = src;
-    for (int p = 0; p < passes; p++) {
-      uint64_t* out = (p & 1) ? s->kb1.as<uint64_t>() : s->kb0.as<uint64_t>();
-      if (p > 0 || !hist0)  // else the first pass's counts came with the validation
-        hipLaunchKernelGGL(k_radix_hist, dim3(nblk), dim3(kSortThreads), 0, st, in, (uint32_t)k, 8 * p,
-                           s->cnt.as<uint32_t>());
-      HIPCHK(hipGetLastError());
-      scan<uint32_t>(s, s->koff.as<uint32_t>(), (uint64_t)nblk * 256, st,
-                     LoadFn<uint32_t>{s->cnt.as<uint32_t>()});
-      hipLaunchKernelGGL(k_radix_scatter, dim3(nblk), dim3(kSortThreads), 0, st, in, out, (uint32_t)k,
-                         8 * p, (const uint32_t*)s->koff.as<uint32_t>());
-      HIPCHK(hipGetLastError());
-      in = out;
-    }
-    if (passes) {
-      sorted = in;
-      sort_bytes = 24ull * k * (uint64_t)passes;
-    }
+    sorted = lsd_sort(s, src, k, passes, st, hist0);
+    sort_bytes = 24ull * k * (uint64_t)passes;
   }
   ensure(s->kdedup, k * sizeof(uint64_t));
   {
     const uint32_t nt = (uint32_t)std::max<uint64_t>(1, (k + kSortTile - 1) / kSortTile);
     ensure(s->cnt, ((uint64_t)nt + 1) * sizeof(uint32_t));
-    ensure(s->koff, ((uint64_t)nt + 1) * sizeof(uint32_t));
     hipLaunchKernelGGL(k_unique_count, dim3(nt), dim3(kSortThreads), 0, st, sorted, k, s->cnt.as<uint32_t>());
     HIPCHK(hipGetLastError());
-    scan<uint32_t>(s, s->koff.as<uint32_t>(), nt, st, LoadFn<uint32_t>{s->cnt.as<uint32_t>()});
+    const uint32_t* toff = nullptr;
+    if (nt > kSortSumTiles) {
+      ensure(s->koff, ((uint64_t)nt + 1) * sizeof(uint32_t));
+      scan<uint32_t>(s, s->koff.as<uint32_t>(), nt, st, LoadFn<uint32_t>{s->cnt.as<uint32_t>()});
+      toff = s->koff.as<uint32_t>();
+    }
     hipLaunchKernelGGL(k_unique_write, dim3(nt), dim3(kSortThreads), 0, st, sorted, k,
-                       (const uint32_t*)s->koff.as<uint32_t>(), nt, s->kdedup.as<uint64_t>(), &s->dctr->kprime);
+                       (const uint32_t*)s->cnt.as<uint32_t>(), toff, s->kdedup.as<uint64_t>(), &s->dctr->kprime);
     HIPCHK(hipGetLastError());
   }
   phase_end(s, pm, st, sort_bytes + 24ull * k);
@@ -569,7 +620,7 @@ const uint64_t* kv_prepare(cpma* s, const uint64_t* keys, const uint64_t* vals, 
   }
   hipLaunchKernelGGL((k_fill<uint32_t>), dim3(1), dim3(64), 0, st, reinterpret_cast<uint32_t*>(s->dinfo),
                      (uint64_t)(sizeof(BatchInfo) / 4), 0u);
-  hipLaunchKernelGGL(k_validate, dim3(grid_for(k, 256, 4096)), dim3(256), 0, st, src, k, s->dinfo);
+  launch_validate(src, k, s->dinfo, st);
   HIPCHK(hipGetLastError());
   HIPCHK(hipMemcpyAsync(s->hinfo, s->dinfo, sizeof(BatchInfo), hipMemcpyDeviceToHost, st));
   HIPCHK(hipStreamSynchronize(st));
@@ -577,31 +628,8 @@ const uint64_t* kv_prepare(cpma* s, const uint64_t* keys, const uint64_t* vals, 
   PhaseMark pm = phase_begin(s, CPMA_PHASE_SORT, st);
   const int bits = 64 - __builtin_clzll(s->hinfo->or_all | 1);
   const int passes = (bits + 7) / 8;
-  ensure(s->kb0, k * sizeof(uint64_t));
-  ensure(s->kb1, k * sizeof(uint64_t));
-  ensure(s->fz_v0, k * sizeof(uint32_t));
-  ensure(s->fz_v1, k * sizeof(uint32_t));
-  ensure(s->fz_byte, k);
-  hipLaunchKernelGGL((k_fill<uint8_t>), dim3(grid_for(k, 256, 4096)), dim3(256), 0, st, s->fz_byte.as<uint8_t>(), k,
-                     (uint8_t)0);  // the first pass's values are the positions
-  const uint32_t nblk = (uint32_t)((k + kSortTile - 1) / kSortTile);
-  ensure(s->cnt, ((uint64_t)nblk * 256 + 1) * sizeof(uint32_t));
-  ensure(s->koff, ((uint64_t)nblk * 256 + 1) * sizeof(uint32_t));
-  const uint64_t* kin = src;
-  const uint32_t* vin = nullptr;
-  for (int p = 0; p < passes; p++) {
-    uint64_t* kout = (p & 1) ? s->kb1.as<uint64_t>() : s->kb0.as<uint64_t>();
-    uint32_t* vout = (p & 1) ? s->fz_v1.as<uint32_t>() : s->fz_v0.as<uint32_t>();
-    hipLaunchKernelGGL(k_radix_hist, dim3(nblk), dim3(kSortThreads), 0, st, kin, (uint32_t)k, 8 * p,
-                       s->cnt.as<uint32_t>());
-    HIPCHK(hipGetLastError());
-    scan<uint32_t>(s, s->koff.as<uint32_t>(), (uint64_t)nblk * 256, st, LoadFn<uint32_t>{s->cnt.as<uint32_t>()});
-    hipLaunchKernelGGL(k_radix_scatter_kv, dim3(nblk), dim3(kSortThreads), 0, st, kin, kout, (uint32_t)k, 8 * p,
-                       (const uint32_t*)s->koff.as<uint32_t>(), vin, (const uint8_t*)s->fz_byte.as<uint8_t>(), vout);
-    HIPCHK(hipGetLastError());
-    kin = kout;
-    vin = vout;
-  }
+  const uint32_t* vin = nullptr;  // the values are the positions
+  const uint64_t* kin = lsd_sort(s, src, k, passes, st, false, true, nullptr, &vin);
   ensure(s->segpos, (k + 1) * sizeof(uint32_t));
   ensure(s->kdedup, k * sizeof(uint64_t));
   ensure(s->kvdedup, k * sizeof(uint64_t));
@@ -2086,7 +2114,7 @@ cpma_status cpma_apply_updates(cpma* s, uint32_t nreq, const int32_t* kind, cons
     // validation before anything changes
     hipLaunchKernelGGL((k_fill<uint32_t>), dim3(1), dim3(64), 0, st, reinterpret_cast<uint32_t*>(s->dinfo),
                        (uint64_t)(sizeof(BatchInfo) / 4), 0u);
-    hipLaunchKernelGGL(k_validate, dim3(grid_for(m, 256, 4096)), dim3(256), 0, st, src, m, s->dinfo);
+    launch_validate(src, m, s->dinfo, st);
     HIPCHK(hipGetLastError());
     HIPCHK(hipMemcpyAsync(s->hinfo, s->dinfo, sizeof(BatchInfo), hipMemcpyDeviceToHost, st));
     HIPCHK(hipStreamSynchronize(st));
@@ -2100,30 +2128,8 @@ cpma_status cpma_apply_updates(cpma* s, uint32_t nreq, const int32_t* kind, cons
     const int bits = 64 - __builtin_clzll(s->hinfo->or_all | 1);
     const int passes = (bits + 7) / 8;
     ensure(s->kb0, (m + 1) * sizeof(uint64_t));
-    ensure(s->kb1, m * sizeof(uint64_t));
-    ensure(s->fz_v0, m * sizeof(uint32_t));
-    ensure(s->fz_v1, m * sizeof(uint32_t));
-    const uint32_t nblk = (uint32_t)((m + kSortTile - 1) / kSortTile);
-    ensure(s->cnt, ((uint64_t)nblk * 256 + 1) * sizeof(uint32_t));
-    ensure(s->koff, ((uint64_t)nblk * 256 + 1) * sizeof(uint32_t));
-    const uint64_t* kin = src;
-    const uint32_t* vin = nullptr;
-    for (int p = 0; p < passes; p++) {
-      uint64_t* kout = (p & 1) ? s->kb1.as<uint64_t>() : s->kb0.as<uint64_t>();
-      uint32_t* vout = (p & 1) ? s->fz_v1.as<uint32_t>() : s->fz_v0.as<uint32_t>();
-      hipLaunchKernelGGL(k_radix_hist, dim3(nblk), dim3(kSortThreads), 0, st, kin, (uint32_t)m, 8 * p,
-                         s->cnt.as<uint32_t>());
-      HIPCHK(hipGetLastError());
-      scan<uint32_t>(s, s->koff.as<uint32_t>(), (uint64_t)nblk * 256, st, LoadFn<uint32_t>{s->cnt.as<uint32_t>()});
-      hipLaunchKernelGGL(k_radix_scatter_kv, dim3(nblk), dim3(kSortThreads), 0, st, kin, kout, (uint32_t)m, 8 * p,
-                         (const uint32_t*)s->koff.as<uint32_t>(), vin, (const uint8_t*)s->fz_byte.as<uint8_t>(),
-                         vout);
-      HIPCHK(hipGetLastError());
-      kin = kout;
-      vin = vout;
-    }
-    const uint64_t* skeys = kin;
-    const uint32_t* svals = vin;
+    const uint32_t* svals = nullptr;
+    const uint64_t* skeys = lsd_sort(s, src, m, passes, st, false, true, s->fz_byte.as<uint8_t>(), &svals);
 
     // distinct keys, their membership, per-item credits and net changes
     ensure(s->segpos, (m + 1) * sizeof(uint32_t));
@@ -3039,7 +3045,7 @@ extern "C" cpma_status cpma_autotune(const uint64_t* keys, uint64_t n, cpma_mem 
     BatchInfo* di = sc.get<BatchInfo>(1);
     hipLaunchKernelGGL((k_fill<uint32_t>), dim3(1), dim3(64), 0, st, reinterpret_cast<uint32_t*>(di),
                        (uint64_t)(sizeof(BatchInfo) / 4), 0u);
-    hipLaunchKernelGGL(k_validate, dim3(grid_for(n, 256, 4096)), dim3(256), 0, st, dk, n, di);
+    launch_validate(dk, n, di, st);
     HIPCHK(hipGetLastError());
     BatchInfo bi;
     HIPCHK(hipMemcpyAsync(&bi, di, sizeof(bi), hipMemcpyDeviceToHost, st));

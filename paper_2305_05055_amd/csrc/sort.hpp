@@ -12,6 +12,24 @@ constexpr int kSortThreads = 256;
 constexpr int kSortItems = 16;
 constexpr uint32_t kSortTile = kSortThreads * kSortItems;  // keys per block
 
+// Batches of up to kSortSmallKeys split into tiles of a quarter of that size:
+// 1e5 keys then occupy 98 CUs instead of 25 and a block counts and ranks 4
+// rounds instead of 16, each of which costs a dependent LDS round trip (1e5
+// keys: count 5.8 -> 2.6 us, scatter 9.6 -> 6.7).  The limit is the size whose
+// small tiles still add their offsets up themselves (below): past it 16 items
+// rank 1e6 keys in 15 us, where 977 small tiles would need the scans again.
+constexpr int kSortItemsSmall = 4;
+constexpr uint64_t kSortSmallKeys = 3u << 17;
+
+// Offsets of an LSD pass.  Up to kSortSumTiles tiles every scatter block adds
+// up the other tiles' digit counts itself (16-bit counts [tile][digit], 512
+// bytes a tile, from L2) instead of three launches scanning the counts of all
+// tiles ([digit][tile], one offset each).  The sums cost 2.5 us in a scatter
+// over 245 tiles (13.9 -> 16.5), the scans 7.5 us and three launches; each
+// block reads all counts, so their traffic grows with the square of the
+// tiles: 75 MB at 384, where they meet.
+constexpr uint32_t kSortSumTiles = 384;
+
 // Validation pass over a batch: OR of all keys (radix pass count), whether a
 // reserved key occurs, and whether the batch is already non-decreasing.
 struct BatchInfo {
@@ -75,9 +93,19 @@ __global__ void __launch_bounds__(256) k_validate(const uint64_t* __restrict__ k
   }
 }
 
+// Writes a tile's count of one digit where the scatter looks for it (see
+// kSortSumTiles; a tile's counts fit 16 bits).
+__device__ __forceinline__ void store_hist(uint32_t* __restrict__ ghist, uint32_t digit, uint32_t c) {
+  if (gridDim.x <= kSortSumTiles)
+    reinterpret_cast<uint16_t*>(ghist)[blockIdx.x * 256 + digit] = (uint16_t)c;
+  else
+    ghist[(uint64_t)digit * gridDim.x + blockIdx.x] = c;
+}
+
 // Validation and the first radix pass's histogram in one read: one block per
 // sort tile (item i = base + 256 r + tid), the tile's digit-0 counts written as
 // k_radix_hist writes them, the batch flags as k_validate sets them.
+template <int kItems>
 __global__ void __launch_bounds__(kSortThreads) k_validate_hist(const uint64_t* __restrict__ keys, uint32_t k,
                                                                 BatchInfo* info, uint32_t* __restrict__ ghist) {
   __shared__ uint32_t h[256];
@@ -85,18 +113,18 @@ __global__ void __launch_bounds__(kSortThreads) k_validate_hist(const uint64_t* 
   __shared__ uint32_t fl[kSortThreads / kWave];
   h[threadIdx.x] = 0;
   __syncthreads();
-  const uint32_t base = blockIdx.x * kSortTile;
+  const uint32_t base = blockIdx.x * (kItems * kSortThreads);
   const bool last_lane = lane_id() == kWave - 1;
   uint64_t orv = 0;
   uint32_t res = 0, uns = 0;
-  uint64_t x[kSortItems];
+  uint64_t x[kItems];
 #pragma unroll
-  for (int r = 0; r < kSortItems; r++) {
+  for (int r = 0; r < kItems; r++) {
     const uint32_t i = base + r * kSortThreads + threadIdx.x;
     x[r] = i < k ? keys[i] : 0;
   }
 #pragma unroll
-  for (int r = 0; r < kSortItems; r++) {
+  for (int r = 0; r < kItems; r++) {
     const uint32_t i = base + r * kSortThreads + threadIdx.x;
     uint64_t nx = dpp_next64(x[r]);
     if (last_lane && i + 1 < k) nx = keys[i + 1];
@@ -115,7 +143,7 @@ __global__ void __launch_bounds__(kSortThreads) k_validate_hist(const uint64_t* 
     fl[wid] = (uint32_t)flags;
   }
   __syncthreads();
-  ghist[(uint64_t)threadIdx.x * gridDim.x + blockIdx.x] = h[threadIdx.x];
+  store_hist(ghist, threadIdx.x, h[threadIdx.x]);
   if (threadIdx.x == 0) {
     uint64_t o = 0;
     uint32_t f = 0;
@@ -133,25 +161,30 @@ __global__ void __launch_bounds__(kSortThreads) k_validate_hist(const uint64_t* 
   }
 }
 
+template <int kItems>
 __global__ void __launch_bounds__(kSortThreads) k_radix_hist(const uint64_t* __restrict__ in,
                                                              uint32_t n, int shift,
                                                              uint32_t* __restrict__ ghist) {
   __shared__ uint32_t h[256];
   h[threadIdx.x] = 0;
   __syncthreads();
-  const uint32_t base = blockIdx.x * kSortTile;
-#pragma unroll 4
-  for (int r = 0; r < kSortItems; r++) {
-    uint32_t i = base + r * kSortThreads + threadIdx.x;
-    if (i < n) atomicAdd(&h[(in[i] >> shift) & 255u], 1u);
+  const uint32_t base = blockIdx.x * (kItems * kSortThreads);
+  uint64_t x[kItems];
+#pragma unroll
+  for (int r = 0; r < kItems; r++) {
+    const uint32_t i = base + r * kSortThreads + threadIdx.x;
+    x[r] = i < n ? in[i] : 0;
   }
+#pragma unroll
+  for (int r = 0; r < kItems; r++)
+    if (base + r * kSortThreads + threadIdx.x < n) atomicAdd(&h[(x[r] >> shift) & 255u], 1u);
   __syncthreads();
-  ghist[(uint64_t)threadIdx.x * gridDim.x + blockIdx.x] = h[threadIdx.x];
+  store_hist(ghist, threadIdx.x, h[threadIdx.x]);
 }
 
-// Scatter of one tile (kSortTile keys) with stable ranks, written out in digit
+// Scatter of one tile (kItems x 256 keys) with stable ranks, written out in digit
 // order.  Wave w ranks its own contiguous quarter of the tile (round r, lane l
-// holds key w * 1024 + 64 r + l): a lane's rank among equal digits in a round
+// holds key w * 64 kItems + 64 r + l): a lane's rank among equal digits in a round
 // comes from eight ballots, and wave-private digit counters in LDS carry it
 // across rounds, so no barrier is needed while ranking.  The tile is then
 // placed in LDS in digit order and written with consecutive threads on
@@ -159,11 +192,74 @@ __global__ void __launch_bounds__(kSortThreads) k_radix_hist(const uint64_t* __r
 //
 // With kKV every key carries a 32-bit value that moves with it (the values
 // take a second LDS tile).  A pass without input values (vin null) makes them:
-// value i is i | vgen[i] << 31.
+// value i is i | vgen[i] << 31, or i without vgen.
 constexpr int kScatterWaves = kSortThreads / kWave;
 static_assert(kSortItems * kScatterWaves == kWave, "one wave scans the (round, wave) counts of a tile");
+static_assert(kSortItemsSmall * kSortThreads * 8 >= kScatterWaves * 256 * 4, "the tile's LDS takes the digit totals");
 
-template <bool kKV>
+// This tile's first output position of every digit from all tiles' 16-bit
+// counts [tile][digit]: a half wave reads a tile's 512 bytes, eight digits a
+// lane, and the block's eight half waves take every eighth tile with eight
+// loads in flight.  All threads of the block; the LDS passed in is free again
+// after the last barrier here (gbase is read after the caller's next one).
+__device__ __forceinline__ void radix_offsets(const uint32_t* __restrict__ counts, uint32_t (*tot)[256],
+                                              uint32_t (*pre)[256], uint32_t* gbase, uint32_t* wsum) {
+  const int tid = threadIdx.x, lane = lane_id(), wid = tid / kWave;
+  const uint32_t nt = gridDim.x, me = blockIdx.x;
+  const uint32_t half = (uint32_t)tid / 32, hl = (uint32_t)tid % 32;
+  const uint4* c4 = reinterpret_cast<const uint4*>(counts) + hl;
+  constexpr uint32_t kU = 8, kHalves = kSortThreads / 32;
+  uint32_t ts[8] = {}, ps[8] = {};
+  for (uint32_t t0 = half; t0 < nt; t0 += kU * kHalves) {
+    uint4 c[kU];
+#pragma unroll
+    for (uint32_t u = 0; u < kU; u++) {
+      const uint32_t t = t0 + u * kHalves;
+      c[u] = t < nt ? c4[(uint64_t)t * 32] : make_uint4(0, 0, 0, 0);
+    }
+#pragma unroll
+    for (uint32_t u = 0; u < kU; u++) {
+      const uint32_t before = t0 + u * kHalves < me ? ~0u : 0u;
+      const uint32_t w[4] = {c[u].x, c[u].y, c[u].z, c[u].w};
+#pragma unroll
+      for (int q = 0; q < 4; q++) {
+        ts[2 * q] += w[q] & 0xffffu;
+        ts[2 * q + 1] += w[q] >> 16;
+        ps[2 * q] += w[q] & before & 0xffffu;
+        ps[2 * q + 1] += (w[q] & before) >> 16;
+      }
+    }
+  }
+#pragma unroll
+  for (int q = 0; q < 8; q++) {
+    ts[q] += __shfl_xor(ts[q], 32);
+    ps[q] += __shfl_xor(ps[q], 32);
+  }
+  if (lane < 32) {
+    uint4* tr = reinterpret_cast<uint4*>(tot[wid]) + 2 * hl;
+    uint4* pr = reinterpret_cast<uint4*>(pre[wid]) + 2 * hl;
+    tr[0] = make_uint4(ts[0], ts[1], ts[2], ts[3]);
+    tr[1] = make_uint4(ts[4], ts[5], ts[6], ts[7]);
+    pr[0] = make_uint4(ps[0], ps[1], ps[2], ps[3]);
+    pr[1] = make_uint4(ps[4], ps[5], ps[6], ps[7]);
+  }
+  __syncthreads();
+  uint32_t t = 0, b = 0;
+#pragma unroll
+  for (int w = 0; w < kScatterWaves; w++) {
+    t += tot[w][tid];
+    b += pre[w][tid];
+  }
+  const uint32_t incl = wave_incl_scan(t);
+  if (lane == kWave - 1) wsum[wid] = incl;
+  __syncthreads();
+#pragma unroll
+  for (int w = 0; w < kScatterWaves; w++)
+    if (w < wid) b += wsum[w];
+  gbase[tid] = b + incl - t;
+}
+
+template <bool kKV, int kItems>
 __device__ __forceinline__ void radix_scatter_tile(const uint64_t* __restrict__ in, uint64_t* __restrict__ out,
                                                    uint32_t n, int shift, const uint32_t* __restrict__ goff,
                                                    const uint32_t* __restrict__ vin, const uint8_t* __restrict__ vgen,
@@ -171,13 +267,9 @@ __device__ __forceinline__ void radix_scatter_tile(const uint64_t* __restrict__ 
                                                    uint32_t (*cnt)[256], uint32_t* toff, uint32_t* gbase,
                                                    uint32_t* wsum) {
   constexpr int kW = kScatterWaves;
-  constexpr int kRounds = kSortTile / kSortThreads;  // rounds per wave (16)
+  constexpr int kRounds = kItems;  // rounds per wave
   const int tid = threadIdx.x, lane = lane_id(), wid = tid / kWave;
-#pragma unroll
-  for (int w = 0; w < kW; w++) cnt[w][tid] = 0;
-  gbase[tid] = goff[(uint64_t)tid * gridDim.x + blockIdx.x];
-  __syncthreads();
-  const uint32_t base = blockIdx.x * kSortTile;
+  const uint32_t base = blockIdx.x * (kItems * kSortThreads);
   const uint32_t wbase = base + (uint32_t)wid * (kRounds * kWave);
   const uint64_t lt_mask = (1ull << lane) - 1ull;
   uint64_t x[kRounds];
@@ -186,8 +278,16 @@ __device__ __forceinline__ void radix_scatter_tile(const uint64_t* __restrict__ 
   for (int r = 0; r < kRounds; r++) {
     const uint32_t i = wbase + (uint32_t)r * kWave + lane;
     x[r] = i < n ? in[i] : 0;
-    if constexpr (kKV) v[r] = i < n ? (vin ? vin[i] : (i | ((uint32_t)vgen[i] << 31))) : 0u;
+    if constexpr (kKV) v[r] = i < n ? (vin ? vin[i] : (i | (vgen ? (uint32_t)vgen[i] << 31 : 0u))) : 0u;
   }
+  if (gridDim.x <= kSortSumTiles) {
+    radix_offsets(goff, reinterpret_cast<uint32_t(*)[256]>(tile), cnt, gbase, wsum);
+  } else {
+    gbase[tid] = goff[(uint64_t)tid * gridDim.x + blockIdx.x];
+  }
+#pragma unroll
+  for (int w = 0; w < kW; w++) cnt[w][tid] = 0;
+  __syncthreads();
   uint32_t rk[kRounds];
 #pragma unroll
   for (int r = 0; r < kRounds; r++) {
@@ -238,7 +338,7 @@ __device__ __forceinline__ void radix_scatter_tile(const uint64_t* __restrict__ 
     }
   }
   __syncthreads();
-  const uint32_t m = min(kSortTile, n - base);
+  const uint32_t m = min((uint32_t)(kItems * kSortThreads), n - base);
   for (uint32_t i = tid; i < m; i += kSortThreads) {
     const uint64_t y = tile[i];
     const uint32_t d = (uint32_t)(y >> shift) & 255u;
@@ -247,34 +347,36 @@ __device__ __forceinline__ void radix_scatter_tile(const uint64_t* __restrict__ 
   }
 }
 
+template <int kItems>
 __global__ void __launch_bounds__(kSortThreads) k_radix_scatter(const uint64_t* __restrict__ in,
                                                                 uint64_t* __restrict__ out,
                                                                 uint32_t n, int shift,
                                                                 const uint32_t* __restrict__ goff) {
-  __shared__ uint64_t tile[kSortTile];
-  __shared__ uint32_t cnt[kScatterWaves][256];
+  __shared__ uint64_t __attribute__((aligned(16))) tile[kItems * kSortThreads];
+  __shared__ uint32_t __attribute__((aligned(16))) cnt[kScatterWaves][256];
   __shared__ uint32_t toff[256];
   __shared__ uint32_t gbase[256];
   __shared__ uint32_t wsum[kScatterWaves];
-  radix_scatter_tile<false>(in, out, n, shift, goff, nullptr, nullptr, nullptr, tile, nullptr, cnt, toff, gbase,
-                            wsum);
+  radix_scatter_tile<false, kItems>(in, out, n, shift, goff, nullptr, nullptr, nullptr, tile, nullptr, cnt, toff,
+                                    gbase, wsum);
 }
 
 // Key-value scatter (stable, so equal keys keep the order of their values'
 // positions through every pass).
+template <int kItems>
 __global__ void __launch_bounds__(kSortThreads) k_radix_scatter_kv(const uint64_t* __restrict__ in,
                                                                    uint64_t* __restrict__ out, uint32_t n, int shift,
                                                                    const uint32_t* __restrict__ goff,
                                                                    const uint32_t* __restrict__ vin,
                                                                    const uint8_t* __restrict__ vgen,
                                                                    uint32_t* __restrict__ vout) {
-  __shared__ uint64_t tile[kSortTile];
-  __shared__ uint32_t vtile[kSortTile];
-  __shared__ uint32_t cnt[kScatterWaves][256];
+  __shared__ uint64_t __attribute__((aligned(16))) tile[kItems * kSortThreads];
+  __shared__ uint32_t vtile[kItems * kSortThreads];
+  __shared__ uint32_t __attribute__((aligned(16))) cnt[kScatterWaves][256];
   __shared__ uint32_t toff[256];
   __shared__ uint32_t gbase[256];
   __shared__ uint32_t wsum[kScatterWaves];
-  radix_scatter_tile<true>(in, out, n, shift, goff, vin, vgen, vout, tile, vtile, cnt, toff, gbase, wsum);
+  radix_scatter_tile<true, kItems>(in, out, n, shift, goff, vin, vgen, vout, tile, vtile, cnt, toff, gbase, wsum);
 }
 
 // Large batches: one MSD split, then every bucket sorted inside LDS.
@@ -712,30 +814,29 @@ __global__ void k_compact_unique(const uint64_t* __restrict__ a, uint64_t n,
 }
 
 // Removal of repeats from a sorted batch in two passes over it: per tile of
-// kSortTile keys the number of first occurrences, an exclusive scan of those
-// (one small launch), then every tile writes its first occurrences to its
-// offset.  Inside a tile, item i = base + 256 r + 64 w + l (round r, wave w,
+// kSortTile keys the number of first occurrences, then every tile writes its
+// first occurrences to its offset: the earlier tiles' counts added up by the
+// block, or with toff (more than kSortSumTiles tiles) their exclusive scan.  Inside a tile, item i = base + 256 r + 64 w + l (round r, wave w,
 // lane l), so the tile's order is (r, w, l): a ballot per round gives the lane
 // offsets, and one wave scan over the 16 x 4 (round, wave) counts the rest.
-__device__ __forceinline__ bool first_occurrence(const uint64_t* __restrict__ a, uint64_t i, uint64_t x,
-                                                 uint64_t prev_lane) {
-  if (i == 0) return true;
-  const uint64_t prev = lane_id() == 0 ? a[i - 1] : prev_lane;
-  return prev != x;
-}
-
 __global__ void __launch_bounds__(kSortThreads) k_unique_count(const uint64_t* __restrict__ a, uint64_t n,
                                                                uint32_t* __restrict__ tcnt) {
   __shared__ uint32_t red[kSortThreads / kWave];
   const uint64_t base = (uint64_t)blockIdx.x * kSortTile;
   const int wid = threadIdx.x / kWave;
   uint32_t c = 0;
+  uint64_t x[kSortItems], left[kSortItems];
 #pragma unroll
   for (int r = 0; r < kSortItems; r++) {
     const uint64_t i = base + (uint64_t)r * kSortThreads + threadIdx.x;
-    const uint64_t x = i < n ? a[i] : 0;
-    const uint64_t pl = dpp_prev64(x);
-    if (i < n && first_occurrence(a, i, x, pl)) c++;
+    x[r] = i < n ? a[i] : 0;
+    left[r] = i < n && i && lane_id() == 0 ? a[i - 1] : 0;
+  }
+#pragma unroll
+  for (int r = 0; r < kSortItems; r++) {
+    const uint64_t i = base + (uint64_t)r * kSortThreads + threadIdx.x;
+    const uint64_t pl = dpp_prev64(x[r]);
+    if (i < n && (i == 0 || (lane_id() == 0 ? left[r] : pl) != x[r])) c++;
   }
   c = wave_sum(c);
   if (lane_id() == 0) red[wid] = c;
@@ -749,40 +850,60 @@ __global__ void __launch_bounds__(kSortThreads) k_unique_count(const uint64_t* _
 }
 
 __global__ void __launch_bounds__(kSortThreads) k_unique_write(const uint64_t* __restrict__ a, uint64_t n,
-                                                               const uint32_t* __restrict__ toff, uint32_t ntiles,
+                                                               const uint32_t* __restrict__ tcnt,
+                                                               const uint32_t* __restrict__ toff,
                                                                uint64_t* __restrict__ out,
                                                                unsigned long long* __restrict__ n_out) {
   constexpr int kW = kSortThreads / kWave;
   __shared__ uint32_t rc[kSortItems * kW];  // (round, wave) counts, then their exclusive offsets
+  __shared__ uint32_t rc_all;               // their sum
+  __shared__ uint32_t red[kW];
   const uint64_t base = (uint64_t)blockIdx.x * kSortTile;
   const int lane = lane_id(), wid = threadIdx.x / kWave;
   const uint64_t lt_mask = (1ull << lane) - 1ull;
-  uint64_t x[kSortItems];
+  uint64_t x[kSortItems], left[kSortItems];
   uint64_t fm[kSortItems];
 #pragma unroll
   for (int r = 0; r < kSortItems; r++) {
     const uint64_t i = base + (uint64_t)r * kSortThreads + threadIdx.x;
     x[r] = i < n ? a[i] : 0;
+    left[r] = i < n && i && lane == 0 ? a[i - 1] : 0;
   }
 #pragma unroll
   for (int r = 0; r < kSortItems; r++) {
     const uint64_t i = base + (uint64_t)r * kSortThreads + threadIdx.x;
     const uint64_t pl = dpp_prev64(x[r]);
-    fm[r] = __ballot(i < n && first_occurrence(a, i, x[r], pl));
+    fm[r] = __ballot(i < n && (i == 0 || (lane == 0 ? left[r] : pl) != x[r]));
     if (lane == 0) rc[r * kW + wid] = (uint32_t)__popcll(fm[r]);
+  }
+  // the first occurrences of the earlier tiles
+  uint64_t at = 0;
+  if (toff) {
+    at = toff[blockIdx.x];
+  } else {
+    uint32_t e = 0;
+    for (uint32_t t = threadIdx.x; t < blockIdx.x; t += kSortThreads) e += tcnt[t];
+    e = wave_sum(e);
+    if (lane == 0) red[wid] = e;
   }
   __syncthreads();
   if (wid == 0) {
     const uint32_t v = rc[lane];  // kSortItems * kW == 64 entries
-    rc[lane] = wave_incl_scan(v) - v;
+    const uint32_t incl = wave_incl_scan(v);
+    rc[lane] = incl - v;
+    if (lane == kWave - 1) rc_all = incl;
   }
   __syncthreads();
-  const uint64_t tb = toff[blockIdx.x];
+  if (!toff) {
+#pragma unroll
+    for (int w = 0; w < kW; w++) at += red[w];
+  }
+  const uint64_t tb = at;
 #pragma unroll
   for (int r = 0; r < kSortItems; r++) {
     if ((fm[r] >> lane) & 1ull) out[tb + rc[r * kW + wid] + (uint32_t)__popcll(fm[r] & lt_mask)] = x[r];
   }
-  if (blockIdx.x == 0 && threadIdx.x == 0) *n_out = toff[ntiles];
+  if (blockIdx.x + 1 == gridDim.x && threadIdx.x == 0) *n_out = tb + rc_all;
 }
 
 }  // namespace cpma_dev
