@@ -38,10 +38,10 @@ def log(*a):
 
 
 # ---- HBM traffic of the main merge kernel from rocprofv3 counter runs ------------
-MERGE_KERNEL = "k_merge_wave<unsigned int>"
-MERGE_SOURCES = ["common.hpp", "leaf.hpp", "update.hpp", "merge_wave.hpp"]
-TRAFFIC_FILE = os.path.join(ROOT, "profiles", "k_merge_wave_traffic_update_pairs1e7_n1e8.md")
-VALU_FILE = os.path.join(ROOT, "profiles", "k_merge_wave_valu_update_pairs1e7_n1e8.md")
+MERGE_KERNEL = "k_merge_splice"  # <true>: inserts, <false>: deletes
+MERGE_SOURCES = ["common.hpp", "leaf.hpp", "update.hpp", "merge_wave.hpp", "merge_splice.hpp"]
+TRAFFIC_FILE = os.path.join(ROOT, "profiles", "k_merge_splice_traffic_update_pairs1e7_n1e8.md")
+VALU_FILE = os.path.join(ROOT, "profiles", "k_merge_splice_valu_update_pairs1e7_n1e8.md")
 # VALU reference rate: 256 CUs x 4 SIMDs, one wave64 VALU instruction per SIMD
 # every 4 cycles (16 lanes), 2.4 GHz peak engine clock.  Not a ceiling: gfx950
 # issues some wave64 VALU instructions in fewer cycles.
@@ -115,7 +115,7 @@ def pmc_summary(fetch_csv, write_csv, steps, cmd_fetch, cmd_write, key):
         rows = [r for r in pmc_rows(path) if r[2] == ctr]
         copy = max(v for _, n, _, v in rows if n == "__amd_rocclr_copyBuffer")
         factor = float(1 << 30) / (copy * 1024.0)
-        merge = [v for _, n, _, v in rows if n == MERGE_KERNEL]
+        merge = [v for _, n, _, v in rows if n.split("<")[0] == MERGE_KERNEL]
         timed = merge[-(MERGES_PER_STEP * steps + TAIL_MERGES):-TAIL_MERGES]
         out[tag] = {"copy_kib": copy, "factor": factor,
                     "kib_per_launch": sum(timed) / len(timed),
@@ -150,7 +150,7 @@ def valu_summary(csv_path, kernel, pick, title, what, cmd, key):
     rows = pmc_rows(csv_path)
     avg = {}
     for ctr in ctrs:
-        timed = pick([v for _, n, c, v in rows if n == kernel and c == ctr])
+        timed = pick([v for _, n, c, v in rows if kernel in (n, n.split("<")[0]) and c == ctr])
         avg[ctr] = sum(timed) / len(timed)
         nl = len(timed)
     lines = [

@@ -21,6 +21,7 @@
 #include "update.hpp"
 #include "merge_lane.hpp"
 #include "merge_heavy.hpp"
+#include "merge_splice.hpp"
 #include "merge_wave.hpp"
 #include "fgraph.hpp"
 #include "pagerank.hpp"
@@ -1455,7 +1456,7 @@ uint64_t rebuild(cpma* s, hipStream_t st, int merged) {
 
 // Launch shapes of the merge kernels for a batch of at most kbound keys.
 struct MergeGrids {
-  uint32_t lgrid, wgrid, lwaves, hgrid_spill;
+  uint32_t lgrid, wgrid, wide_grid, lwaves, hgrid_spill;
   uint64_t part_slots;  // (keys changed, bytes) slot pairs of every launch
 };
 
@@ -1467,6 +1468,9 @@ MergeGrids merge_grids(const cpma* s, uint64_t kbound) {
   // dispatcher hands out the rest as waves finish, which evens out segments of
   // unequal work (4-5 % faster at 1e7 into 1e8 than 40 waves per CU)
   m.wgrid = std::max(1u, (uint32_t)std::min<uint64_t>(segs, (uint64_t)s->num_cus * 320));
+  // the wide list is empty for most batches, and 320 idle waves per CU cost 20 us to
+  // dispatch (32: 8 us, the last leaf's slice included); a full list still has two waves for every resident one
+  m.wide_grid = std::min(m.wgrid, (uint32_t)s->num_cus * 32);
   m.lwaves = std::max(1u, m.lgrid) * (256 / kWave);
   // heavy merge of spilled slices: at most kbound / (kWaveSlice + 1) of them,
   // a few LDS-bound blocks per CU
@@ -1639,7 +1643,7 @@ uint64_t apply_batch(cpma* s, const uint64_t* B, uint64_t kbound, bool insert, h
   } else if (small && s->S <= kWaveMaxS) {
     // every segment in one 64-bit wave pass; long insert slices in the heavy merge
     a.part = slots(wgrid, false);
-    hipLaunchKernelGGL(k_merge_wave<uint64_t>, dim3(wgrid), dim3(kWave), 0, st, a, 1);
+    hipLaunchKernelGGL(k_merge_wave, dim3(wgrid), dim3(kWave), 0, st, a, 1);
     if (insert && kbound > kWaveSlice) {
       // a slice of more than kWaveSlice keys spills to the heavy merge
       a.part = slots(hgrid_spill, false);
@@ -1650,12 +1654,12 @@ uint64_t apply_batch(cpma* s, const uint64_t* B, uint64_t kbound, bool insert, h
     phase_end(s, pmg, st);
   } else if (s->S <= kWaveMaxS) {
     a.part = slots(wgrid, true);
-    hipLaunchKernelGGL(k_merge_wave<uint32_t>, dim3(wgrid), dim3(kWave), 0, st, a);
+    hipLaunchKernelGGL(insert ? k_merge_splice<true> : k_merge_splice<false>, dim3(wgrid), dim3(kWave), 0, st, a);
     HIPCHK(hipGetLastError());
     phase_end(s, pmg, st);
     PhaseMark ph = phase_begin(s, CPMA_PHASE_HEAVY, st);
-    a.part = slots(wgrid, false);
-    hipLaunchKernelGGL(k_merge_wave<uint64_t>, dim3(wgrid), dim3(kWave), 0, st, a);
+    a.part = slots(mg.wide_grid, false);
+    hipLaunchKernelGGL(k_merge_wave, dim3(mg.wide_grid), dim3(kWave), 0, st, a);
     if (insert) {  // long insert slices, one wave each
       a.part = slots(hgrid_spill, false);
       hipLaunchKernelGGL(k_merge_heavy, dim3(hgrid_spill), dim3(kHeavyThreads), heavy_smem(s->S, kHeavyLds), st, a,

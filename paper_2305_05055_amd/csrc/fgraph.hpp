@@ -58,8 +58,7 @@ __device__ __forceinline__ uint32_t wave_leaf_keys(const uint8_t* __restrict__ s
       words[k] &= v >= 4 ? 0xffffffffu : (v <= 0 ? 0u : ((1u << (8 * v)) - 1u));
     }
   }
-  const uint32_t msb = msb_nibble(words[0]) | (msb_nibble(words[1]) << 4) | (msb_nibble(words[2]) << 8) |
-                       (msb_nibble(words[3]) << 12);
+  const uint32_t msb = msb_byte(words[0], words[1]) | msb_byte(words[2], words[3]) << 8;
   const uint32_t cm = vm & msb;  // continuation bytes
   uint32_t sh = 7u * dpp_prev32((uint32_t)__clz((int)~(cm << 16)));
   uint64_t run = lead;

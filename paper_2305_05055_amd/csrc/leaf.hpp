@@ -239,70 +239,10 @@ __device__ __forceinline__ uint32_t wave_decode_regs(const uint4 w, uint32_t use
   return lane63_u32(incl_cnt);
 }
 
-// Narrow single-chunk decode (leaf size <= 1024): every key lies within 2^32 of
-// `base`, so every delta fits 32 bits and a code has at most 5 bytes.  Keys are
-// produced as 32-bit offsets from base (head_rel = head - base).
-//
-// A key is the head plus the payload of every code byte before it, each byte's
-// 7 bits shifted by 7 times its place in its code; so a running sum of shifted
-// payloads over the bytes, read at a code's last byte, is that key's offset.
-// Per lane: the running sum over its 16 bytes (the shift a code carries in
-// from the previous lane is 7 times that lane's run of trailing continuation
-// bytes, known before parsing), then one wave scan of the lane totals gives
-// every lane its starting offset, codes that straddle lanes included.  The
-// head and bytes past `used` carry no payload.  emit(index, key offset) runs
-// for every key in order; returns the key count.
-__device__ __forceinline__ uint32_t msb_nibble(uint32_t x) {
-  x = (x >> 7) & 0x01010101u;
-  return (x | (x >> 7) | (x >> 14) | (x >> 21)) & 0xfu;
-}
-
-template <class Emit>
-__device__ __forceinline__ uint32_t wave_decode_narrow(uint4 w, uint32_t used, uint32_t head_rel, Emit&& emit) {
-  const int lane = lane_id();
-  const uint32_t pos0 = 16u * lane;
-  const uint32_t nvalid = pos0 < used ? min(16u, used - pos0) : 0u;
-  uint32_t vm = nvalid >= 16u ? 0xffffu : ((1u << nvalid) - 1u);
-  const bool hl = lane == 0 && used >= 8u;
-  if (lane == 0) {
-    vm &= 0xff00u;  // the head is not a code
-    w.x = 0;
-    w.y = 0;
-  }
-  uint32_t words[4] = {w.x, w.y, w.z, w.w};
-  if (nvalid < 16u) {
-#pragma unroll
-    for (int k = 0; k < 4; k++) {
-      const int32_t v = (int32_t)nvalid - 4 * k;
-      words[k] &= v >= 4 ? 0xffffffffu : (v <= 0 ? 0u : ((1u << (8 * v)) - 1u));
-    }
-  }
-  const uint32_t msb = msb_nibble(words[0]) | (msb_nibble(words[1]) << 4) | (msb_nibble(words[2]) << 8) |
-                       (msb_nibble(words[3]) << 12);
-  const uint32_t tm = vm & ~msb;  // code ends
-  const uint32_t cm = vm & msb;   // continuation bytes
-  const uint32_t tc = __clz(~(cm << 16));
-  uint32_t sh = 7u * dpp_prev32(tc);
-  uint32_t run = 0;
-  uint32_t kv[16];
-#pragma unroll
-  for (int j = 0; j < 16; j++) {
-    run += ((words[j >> 2] >> (8 * (j & 3))) & 0x7fu) << sh;
-    kv[j] = run;
-    sh = (sh + 7u) & (0u - ((cm >> j) & 1u));
-  }
-  const uint32_t lead = hl ? head_rel : 0u;
-  const uint32_t tot = run + lead;
-  const uint32_t lcnt = (uint32_t)__popc(tm) + (hl ? 1u : 0u);
-  const uint32_t ex = wave_incl_scan(tot) - tot;
-  const uint32_t icl = wave_incl_scan(lcnt);
-  uint32_t idx = icl - lcnt;
-  if (hl) emit(idx++, head_rel);
-  const uint32_t off = ex + lead;
-#pragma unroll
-  for (int j = 0; j < 16; j++)
-    if ((tm >> j) & 1u) emit(idx++, off + kv[j]);
-  return lane63_u32(icl);
+// The top bits of eight bytes.
+__device__ __forceinline__ uint32_t msb_byte(uint32_t lo, uint32_t hi) {
+  return __builtin_amdgcn_udot4((lo >> 7) & 0x01010101u, 0x08040201u,
+                                __builtin_amdgcn_udot4((hi >> 7) & 0x01010101u, 0x80402010u, 0u, false), false);
 }
 
 // Number of keys in a leaf image: the head plus one per byte with a clear high bit.

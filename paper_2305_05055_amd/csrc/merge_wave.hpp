@@ -1,8 +1,9 @@
-// Wave-cooperative batch merge: one wave per touched leaf (the batch-merge phase
-// of Section "Parallel Batch Updates in a PMA").  The wave decodes the leaf's
-// keys into LDS, ranks the slice's batch keys among them, and writes the merged
-// encoding with byte offsets from wave prefix sums (DPP), so every step is a
-// handful of parallel passes over at most S / 16 lanes' worth of data.
+// Wave-cooperative batch merge of segments whose keys span 2^32 or more, and of all
+// segments of a small batch: one wave per touched leaf (the batch-merge phase of
+// Section "Parallel Batch Updates in a PMA").  The wave decodes the leaf's keys into
+// LDS, ranks the slice's batch keys among them, and writes the merged encoding with
+// byte offsets from wave prefix sums (DPP), so every step is a handful of parallel
+// passes over at most S / 16 lanes' worth of data.
 //
 // Insert (slice of at most 64 keys, one per lane): new keys with the same rank r
 // (the number of old keys below them) form the group inserted before old key r.
@@ -11,8 +12,7 @@
 // ranks, byte totals and last keys go to 64-entry tables from DPP scans, and a
 // lane walking its block of old keys meets them in rank order.  Delete (any
 // slice length): present keys are flagged by rank in a bit mask, and each kept
-// key's code is recomputed against the previous kept key.  LDS per wave stays
-// near 10 KB (the decoded keys dominate), which keeps several waves per SIMD.
+// key's code is recomputed against the previous kept key.
 #pragma once
 #include "leaf.hpp"
 #include "update.hpp"
@@ -22,8 +22,7 @@ namespace cpma_dev {
 constexpr uint32_t kWaveSlice = 64;   // insert slice handled per wave
 constexpr uint32_t kWaveMaxS = 1024;  // leaf size handled per wave (16 bytes per lane)
 
-// Code length and code bytes of a delta held in the key type (32-bit offsets
-// in the narrow instance).
+// Code length and code bytes of a delta held in either type.
 __device__ __forceinline__ uint32_t vlen_t(uint32_t d) { return (32u - (uint32_t)__clz((int)(d | 1u)) + 6u) / 7u; }
 __device__ __forceinline__ uint32_t vlen_t(uint64_t d) { return vlen(d); }
 template <typename T>
@@ -35,8 +34,6 @@ __device__ __forceinline__ void vput_t(uint8_t* dst, T d) {
   }
   dst[n] = (uint8_t)d;
 }
-__device__ __forceinline__ uint32_t dpp_prev_t(uint32_t v) { return dpp_prev32(v); }
-__device__ __forceinline__ uint64_t dpp_prev_t(uint64_t v) { return dpp_prev64(v); }
 __device__ __forceinline__ uint32_t readlane_t(uint32_t v, int l) {
   return (uint32_t)__builtin_amdgcn_readlane((int)v, l);
 }
@@ -47,28 +44,24 @@ __device__ __forceinline__ uint64_t readlane_t(uint64_t v, int l) {
 
 // Key x (offset from base) as a leaf head (8 bytes) or as the code of x - pred.
 template <typename KT>
-__device__ __forceinline__ void put_key_bytes(uint8_t* dst, bool head, KT x, KT pred, uint64_t base) {
+__device__ __forceinline__ void put_key_bytes(uint8_t* dst, bool head, uint64_t x, uint64_t pred, uint64_t base) {
   if (head)
     put_le64(dst, base + (uint64_t)x);
   else
     vput_t<KT>(dst, (KT)(x - pred));
 }
 
-// KT = uint32_t: keys are stored in LDS as offsets from the segment's smallest
-// possible key (segments flagged wide are handed to the 64-bit instance), which
-// halves the dominant LDS array.  KT = uint64_t: processes the handed-over list,
-// or with all_segments every segment not routed to the heavy merge (small
-// batches: one launch instead of two).
+// Processes the list of wide segments, or with all_segments every segment not
+// routed to the heavy merge (small batches: one launch instead of two).
 //
 // The body runs as one wave with its own LDS (MergeLds); the merge kernel is one
 // wave per block, and the fused small-batch kernel runs several such waves in
 // one block, each on its own segments.  The wave's first segment is t0, it
 // takes every tstep-th one after it, and it leaves its totals in slot `slot`.
-template <typename KT>
 struct MergeLds {
   alignas(16) uint8_t out[kWaveMaxS];  // the merged leaf image
-  KT K[kWaveMaxS];                     // decoded old keys
-  KT GK[kWaveSlice];                   // group g: its last key (new predecessor of old key GR[g])
+  uint64_t K[kWaveMaxS];               // decoded old keys
+  uint64_t GK[kWaveSlice];             // group g: its last key (new predecessor of old key GR[g])
   uint32_t GR[kWaveSlice + 1];         // group g: rank; GR[ng] closes the table
   uint32_t GB[kWaveSlice];             // group g: bytes of its codes
   uint32_t GS[kWaveSlice];             // group g: output offset
@@ -89,12 +82,11 @@ __device__ __forceinline__ void merge_sync() {
   }
 }
 
-template <typename KT, bool kWaveOnly>
-__device__ __forceinline__ void merge_wave_body(MergeArgs a, int all_segments, MergeLds<KT>& L, uint64_t t0,
+template <bool kWaveOnly>
+__device__ __forceinline__ void merge_wave_body(MergeArgs a, int all_segments, MergeLds& L, uint64_t t0,
                                                 uint64_t tstep, uint64_t slot) {
-  constexpr bool kNarrow = sizeof(KT) == 4;
-  KT* const K = L.K;
-  KT* const GK = L.GK;
+  uint64_t* const K = L.K;
+  uint64_t* const GK = L.GK;
   uint32_t* const GR = L.GR;
   uint32_t* const GB = L.GB;
   uint32_t* const GS = L.GS;
@@ -102,12 +94,12 @@ __device__ __forceinline__ void merge_wave_body(MergeArgs a, int all_segments, M
   uint8_t* const out = L.out;
   const int lane = lane_id();
   const uint32_t S = a.S;
-  const bool listed = !kNarrow && !all_segments;
+  const bool listed = !all_segments;
   const uint64_t T = listed ? (uint64_t)a.ctr->nwide : (uint64_t)a.ctr->T;
   const uint32_t pos0 = 16u * lane;
   unsigned long long delta = 0, alg = 0;
   auto seg_of = [&](uint64_t t) -> uint64_t { return listed ? (uint64_t)a.wide_list[t] : t; };
-  auto skip = [&](const uint4& d) { return kNarrow ? d.w != 0 : (all_segments && d.w == 2); };
+  auto skip = [&](const uint4& d) { return all_segments && d.w == 2; };
   // Software pipeline: the next segment's descriptor, leaf bytes and batch keys
   // are loaded while the current one is merged.
   uint4 d_cur = make_uint4(0, 0, 0, 0), d_nxt = d_cur;
@@ -137,7 +129,7 @@ __device__ __forceinline__ void merge_wave_body(MergeArgs a, int all_segments, M
     const uint32_t b = d_cur.y, e = e_cur;
     const uint32_t nb = e - b;
     const uint32_t used0 = d_cur.z;
-    const bool wide = skip(d_cur);
+    const bool spilled = skip(d_cur);
     const uint4 w = w_cur;
     const uint64_t bj0 = b_cur;
     if (tn < T) {
@@ -153,26 +145,10 @@ __device__ __forceinline__ void merge_wave_body(MergeArgs a, int all_segments, M
     e_cur = e_nxt;
     w_cur = w_nxt;
     b_cur = b_nxt;
-    if (wide) continue;  // routed to the wide or spill list
-    // smallest possible key of the segment: the old head or the first slice key
-    uint64_t base = 0;
-    if (kNarrow) {
-      const uint64_t hd = ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)w.y, 0) << 32) |
-                          (uint32_t)__builtin_amdgcn_readlane((int)w.x, 0);
-      const uint64_t b0 = ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(bj0 >> 32), 0) << 32) |
-                          (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)bj0, 0);
-      base = used0 ? min(hd, b0) : b0;
-    }
+    if (spilled) continue;  // to the heavy merge
     const uint64_t* Bg = a.B + b;
     uint8_t* lp = a.bytes + leaf * (uint64_t)S;
-    uint32_t nA;
-    if constexpr (kNarrow) {
-      const uint64_t hd = ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)w.y, 0) << 32) |
-                          (uint32_t)__builtin_amdgcn_readlane((int)w.x, 0);
-      nA = wave_decode_narrow(w, used0, (uint32_t)(hd - base), [&](uint32_t i, uint32_t x) { K[i] = (KT)x; });
-    } else {
-      nA = wave_decode_regs(w, used0, [&](uint32_t i, uint64_t x, uint64_t) { K[i] = (KT)x; });
-    }
+    const uint32_t nA = wave_decode_regs(w, used0, [&](uint32_t i, uint64_t x, uint64_t) { K[i] = x; });
     wave_zero(out, S);
     // lane-contiguous block of old-key indices [i0, i1) over [0, nA] (index nA: trailing group)
     const uint32_t m = (nA + 1 + kWave - 1) / kWave;
@@ -182,16 +158,15 @@ __device__ __forceinline__ void merge_wave_body(MergeArgs a, int all_segments, M
     uint64_t arena_off = 0;
     bool to_arena = false;
     if (a.is_insert) {
-      // keys below are offsets from base (the key type of this instance)
       const bool has_b = (uint32_t)lane < nb;
-      const KT bj = has_b ? (KT)(bj0 - base) : (KT)0;
+      const uint64_t bj = has_b ? bj0 : 0;
       uint32_t r = 0xffffffffu;
       bool isnew = false;
       if (has_b) {
-        r = lds_lower_bound<KT>(K, nA, bj);
+        r = lds_lower_bound<uint64_t>(K, nA, bj);
         isnew = !(r < nA && K[r] == bj);
       }
-      const KT b_prev = dpp_prev_t(bj);
+      const uint64_t b_prev = dpp_prev64(bj);
       const uint32_t r_prev = dpp_prev32(r);
       const uint32_t new_prev = dpp_prev32(isnew ? 1u : 0u);
       const uint32_t r_next = dpp_next32(r);
@@ -199,7 +174,7 @@ __device__ __forceinline__ void merge_wave_body(MergeArgs a, int all_segments, M
       const bool same_prev = lane > 0 && new_prev && r_prev == r;
       const bool same_next = lane < kWave - 1 && new_next && r_next == r;
       bool has_pred = false;
-      KT pred = 0;
+      uint64_t pred = 0;
       if (isnew) {
         if (same_prev) {
           pred = b_prev;
@@ -209,7 +184,7 @@ __device__ __forceinline__ void merge_wave_body(MergeArgs a, int all_segments, M
           has_pred = true;
         }
       }
-      const uint32_t cost = isnew ? (has_pred ? vlen_t((KT)(bj - pred)) : 8u) : 0u;
+      const uint32_t cost = isnew ? (has_pred ? vlen(bj - pred) : 8u) : 0u;
       const uint32_t incl = dpp_incl_scan<uint32_t>(cost);
       const uint32_t ex = incl - cost;
       const bool gstart = isnew && !same_prev;
@@ -238,19 +213,19 @@ __device__ __forceinline__ void merge_wave_body(MergeArgs a, int all_segments, M
             hi = mid;
         }
       }
-      const KT k_before = (i0 > 0 && i0 <= nA) ? K[i0 - 1] : (KT)0;  // old key before the block
+      const uint64_t k_before = (i0 > 0 && i0 <= nA) ? K[i0 - 1] : 0;  // old key before the block
       // sweep 1: bytes per index (group before old key i, then old key i)
       uint32_t lt = 0;
       uint32_t p = p0;
-      KT kp = k_before;
+      uint64_t kp = k_before;
       for (uint32_t i = i0; i < i1; i++) {
         const bool gh = GR[p] == i;
         uint32_t t = gh ? GB[p] : 0u;
         if (i < nA) {
-          const KT x = K[i];
+          const uint64_t x = K[i];
           const bool hp = gh || i > 0;
-          const KT np = gh ? GK[p] : kp;
-          t += hp ? vlen_t((KT)(x - np)) : 8u;
+          const uint64_t np = gh ? GK[p] : kp;
+          t += hp ? vlen(x - np) : 8u;
           kp = x;
         }
         lt += t;
@@ -276,17 +251,17 @@ __device__ __forceinline__ void merge_wave_body(MergeArgs a, int all_segments, M
       auto write_merged = [&](auto dst) {
         uint32_t run = lincl - lt;
         uint32_t p = p0;
-        KT kp = k_before;
+        uint64_t kp = k_before;
         for (uint32_t i = i0; i < i1; i++) {
           const bool gh = GR[p] == i;
           const uint32_t gb = gh ? GB[p] : 0u;
           if (gh) GS[p] = run;
           if (i < nA) {
-            const KT x = K[i];
+            const uint64_t x = K[i];
             const bool hp = gh || i > 0;
-            const KT np = gh ? GK[p] : kp;
-            const uint32_t c = hp ? vlen_t((KT)(x - np)) : 8u;
-            put_key_bytes<KT>(dst + run + gb, !hp, x, np, base);
+            const uint64_t np = gh ? GK[p] : kp;
+            const uint32_t c = hp ? vlen(x - np) : 8u;
+            put_key_bytes<uint64_t>(dst + run + gb, !hp, x, np, 0);
             run += gb + c;
             kp = x;
           } else {
@@ -295,15 +270,15 @@ __device__ __forceinline__ void merge_wave_body(MergeArgs a, int all_segments, M
           p += gh ? 1u : 0u;
         }
         merge_sync<kWaveOnly>();
-        if (isnew) put_key_bytes<KT>(dst + GS[gid] + (ex - exfirst), !has_pred, bj, pred, base);
+        if (isnew) put_key_bytes<uint64_t>(dst + GS[gid] + (ex - exfirst), !has_pred, bj, pred, 0);
       };
       if (to_arena)
         write_merged(a.arena + arena_off);
       else
         write_merged(out);
       uint64_t firstnew = kNoKey;
-      if (nnew) firstnew = base + (uint64_t)readlane_t(bj, __ffsll((unsigned long long)newmask) - 1);
-      first_key = nA ? min(base + (uint64_t)K[0], firstnew) : firstnew;
+      if (nnew) firstnew = readlane_t(bj, __ffsll((unsigned long long)newmask) - 1);
+      first_key = nA ? min(K[0], firstnew) : firstnew;
       delta += nnew;
     } else {
       for (uint32_t i = lane; i < kWaveMaxS / 32; i += kWave) DF[i] = 0;
@@ -311,8 +286,8 @@ __device__ __forceinline__ void merge_wave_body(MergeArgs a, int all_segments, M
       for (uint32_t c0 = 0; c0 < nb; c0 += kWave) {
         const uint32_t j = c0 + lane;
         if (j < nb) {
-          const KT xr = (KT)(Bg[j] - base);
-          const uint32_t r = lds_lower_bound<KT>(K, nA, xr);
+          const uint64_t xr = Bg[j];
+          const uint32_t r = lds_lower_bound<uint64_t>(K, nA, xr);
           if (r < nA && K[r] == xr) atomicOr(&DF[r >> 5], 1u << (r & 31));
         }
       }
@@ -325,13 +300,13 @@ __device__ __forceinline__ void merge_wave_body(MergeArgs a, int all_segments, M
         else nrem++;
       }
       const uint32_t pk_in = dpp_prev32(dpp_incl_max(lastk));  // 0 = none before this block
-      const KT kin = pk_in ? K[pk_in - 1] : (KT)0;
+      const uint64_t kin = pk_in ? K[pk_in - 1] : 0;
       uint32_t pk = pk_in;
-      KT kp = kin;
+      uint64_t kp = kin;
       for (uint32_t i = i0; i < min(i1, nA); i++) {
         if (gone(i)) continue;
-        const KT x = K[i];
-        lt += pk ? vlen_t((KT)(x - kp)) : 8u;
+        const uint64_t x = K[i];
+        lt += pk ? vlen(x - kp) : 8u;
         pk = i + 1;
         kp = x;
       }
@@ -342,9 +317,9 @@ __device__ __forceinline__ void merge_wave_body(MergeArgs a, int all_segments, M
       kp = kin;
       for (uint32_t i = i0; i < min(i1, nA); i++) {
         if (gone(i)) continue;
-        const KT x = K[i];
-        put_key_bytes<KT>(out + run, pk == 0, x, kp, base);
-        run += pk ? vlen_t((KT)(x - kp)) : 8u;
+        const uint64_t x = K[i];
+        put_key_bytes<uint64_t>(out + run, pk == 0, x, kp, 0);
+        run += pk ? vlen(x - kp) : 8u;
         pk = i + 1;
         kp = x;
       }
@@ -357,7 +332,7 @@ __device__ __forceinline__ void merge_wave_body(MergeArgs a, int all_segments, M
         }
       uint32_t fkmin = fk;
       for (int d = 32; d > 0; d >>= 1) fkmin = min(fkmin, (uint32_t)__shfl_xor((int)fkmin, d, kWave));
-      first_key = (fkmin != 0xffffffffu) ? base + (uint64_t)K[fkmin] : kNoKey;
+      first_key = (fkmin != 0xffffffffu) ? K[fkmin] : kNoKey;
       delta += wave_sum(nrem);
     }
     merge_sync<kWaveOnly>();
@@ -383,10 +358,9 @@ __device__ __forceinline__ void merge_wave_body(MergeArgs a, int all_segments, M
   }
 }
 
-template <typename KT>
 __global__ void __launch_bounds__(kWave) k_merge_wave(MergeArgs a, int all_segments = 0) {
-  __shared__ MergeLds<KT> L;
-  merge_wave_body<KT, false>(a, all_segments, L, blockIdx.x, gridDim.x, blockIdx.x);
+  __shared__ MergeLds L;
+  merge_wave_body<false>(a, all_segments, L, blockIdx.x, gridDim.x, blockIdx.x);
 }
 
 }  // namespace cpma_dev

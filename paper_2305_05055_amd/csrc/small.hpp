@@ -478,7 +478,7 @@ __global__ void __launch_bounds__(kSmallThreads) k_small_update(const uint64_t* 
   static_assert(kFusedMergeWaves * kWave <= kSmallThreads, "merge waves fit in the block");
   __shared__ union {
     SmallPrepLds prep;
-    MergeLds<uint64_t> merge[kFusedMergeWaves];
+    MergeLds merge[kFusedMergeWaves];
     PathLds path;
   } lds;
   // the segment arrays the merge reads are the ones the preparation writes
@@ -487,7 +487,7 @@ __global__ void __launch_bounds__(kSmallThreads) k_small_update(const uint64_t* 
                   ma.spill_list, ma.ctr, lds.prep);
   __syncthreads();
   const uint32_t w = threadIdx.x / kWave;
-  if (w < kFusedMergeWaves) merge_wave_body<uint64_t, true>(ma, 1, lds.merge[w], w, kFusedMergeWaves, w);
+  if (w < kFusedMergeWaves) merge_wave_body<true>(ma, 1, lds.merge[w], w, kFusedMergeWaves, w);
   __syncthreads();
   path_check_body(bd, P, ma.used, ma.seg_leaf, ma.seg_desc, ma.ctr, ma.part, 0, kFusedMergeWaves, hout, lds.path);
 }
