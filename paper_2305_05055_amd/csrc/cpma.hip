@@ -2108,8 +2108,8 @@ cpma_status cpma_apply_updates(cpma* s, uint32_t nreq, const int32_t* kind, cons
       for (uint32_t r = 0; r < nreq; r++) tab[r] = GatherReq{keys[r], hoff[r], n[r]};
       ensure(s->fz_res, std::max<size_t>(8ull * nreq, sizeof(GatherReq) * (size_t)nreq));
       HIPCHK(hipMemcpyAsync(s->fz_res.p, tab, sizeof(GatherReq) * nreq, hipMemcpyHostToDevice, st));
-      hipLaunchKernelGGL(k_fuse_gather, dim3(std::min<uint32_t>(nreq, 65535u)), dim3(256), 0, st,
-                         (const GatherReq*)s->fz_res.as<GatherReq>(), nreq, dkeys);
+      hipLaunchKernelGGL(k_fuse_gather, dim3((uint32_t)((m + 1023) / 1024)), dim3(256), 0, st,
+                         (const GatherReq*)s->fz_res.as<GatherReq>(), nreq, m, dkeys);
       HIPCHK(hipGetLastError());
     }
     const uint64_t* doff = s->fz_meta.as<uint64_t>();
@@ -2126,7 +2126,7 @@ cpma_status cpma_apply_updates(cpma* s, uint32_t nreq, const int32_t* kind, cons
 
     // stable key-value sort; values carry position and kind
     ensure(s->fz_byte, m);
-    hipLaunchKernelGGL(k_fuse_kinds, dim3(std::min<uint32_t>(nreq, 65535u)), dim3(256), 0, st, doff, drdel, nreq,
+    hipLaunchKernelGGL(k_fuse_kinds, dim3((uint32_t)((m + 4095) / 4096)), dim3(256), 0, st, doff, drdel, nreq, m,
                        s->fz_byte.as<uint8_t>());
     HIPCHK(hipGetLastError());
     const int bits = 64 - __builtin_clzll(s->hinfo->or_all | 1);
@@ -2153,7 +2153,7 @@ cpma_status cpma_apply_updates(cpma* s, uint32_t nreq, const int32_t* kind, cons
                          (const uint64_t*)s->kdedup.as<uint64_t>(), (const unsigned long long*)fctr,
                          (const uint64_t*)s->head.as<uint64_t>(), s->L, s->leafid.as<uint32_t>());
       hipLaunchKernelGGL(k_fuse_member_leaf, dim3((uint32_t)std::min<uint64_t>(s->L, (uint64_t)s->num_cus * 32)),
-                         dim3(kWave), 8ull * s->S, st, qa, (const uint64_t*)s->kdedup.as<uint64_t>(),
+                         dim3(kWave), member_leaf_smem(s->S), st, qa, (const uint64_t*)s->kdedup.as<uint64_t>(),
                          (const uint32_t*)s->leafid.as<uint32_t>(), s->fz_member.as<uint8_t>());
     } else {
       const uint32_t per = lookups_per_wave(s, m);

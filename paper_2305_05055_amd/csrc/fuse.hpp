@@ -16,67 +16,138 @@
 // delete bit << 31; a stable sort by key keeps each key's occurrences in
 // request order.
 #pragma once
+#include "merge_splice.hpp"
 #include "query.hpp"
 
 namespace cpma_dev {
 
-// Kind byte (0 insert, 1 delete) of every position; one block per request.
+// Request owning position p: the last r with at(r) <= p, of nreq + 1 entries in
+// non-decreasing order (the last one the total).
+template <typename At>
+__device__ __forceinline__ uint32_t fuse_owner(At at, uint32_t nreq, uint64_t p) {
+  uint32_t lo = 0, hi = nreq + 1;
+  while (lo < hi) {
+    const uint32_t mid = (lo + hi) >> 1;
+    if (at(mid) <= p)
+      lo = mid + 1;
+    else
+      hi = mid;
+  }
+  return lo - 1;
+}
+__device__ __forceinline__ uint32_t fuse_req_of(const uint64_t* off, uint32_t nreq, uint64_t p) {
+  return fuse_owner([&](uint32_t r) { return off[r]; }, nreq, p);
+}
+
+// Requests differ in size by orders of magnitude, so the passes over their items
+// divide positions, not requests, among the threads (a block per request: 96
+// requests of 10 to 1e5 keys took 81 us to gather and 13.6 to mark; 8.9 and 8.0 now).
+
+// Kind byte (0 insert, 1 delete) of every position, 16 per thread (kinds is
+// 16-byte aligned).
 __global__ void __launch_bounds__(256) k_fuse_kinds(const uint64_t* __restrict__ off,
-                                                    const uint8_t* __restrict__ rdel, uint32_t nreq,
+                                                    const uint8_t* __restrict__ rdel, uint32_t nreq, uint64_t m,
                                                     uint8_t* __restrict__ kinds) {
-  for (uint32_t r = blockIdx.x; r < nreq; r += gridDim.x) {
-    const uint8_t k = rdel[r];
-    const uint64_t e = off[r + 1];
-    for (uint64_t i = off[r] + threadIdx.x; i < e; i += blockDim.x) kinds[i] = k;
+  const uint64_t p0 = 16 * ((uint64_t)blockIdx.x * blockDim.x + threadIdx.x);
+  if (p0 >= m) return;
+  uint32_t r = fuse_req_of(off, nreq, p0), word[4];
+  uint64_t end = off[r + 1];
+#pragma unroll
+  for (uint32_t j = 0; j < 16; j++) {
+    if (p0 + j >= end && p0 + j < m) {
+      r = fuse_req_of(off, nreq, p0 + j);
+      end = off[r + 1];
+    }
+    const uint32_t bits = (uint32_t)rdel[r] << (8 * (j & 3));
+    word[j / 4] = j & 3 ? word[j / 4] | bits : bits;
+  }
+  if (p0 + 16 <= m) {
+    *reinterpret_cast<uint4*>(kinds + p0) = make_uint4(word[0], word[1], word[2], word[3]);
+  } else {
+    for (uint32_t j = 0; p0 + j < m; j++) kinds[p0 + j] = (uint8_t)(word[j / 4] >> (8 * (j & 3)));
   }
 }
 
 // Membership before the sequence of each distinct key, per leaf (large batches;
 // k_contains otherwise): leaf f's distinct keys are
-// keys[sbeg[f] .. sbeg[f + 1]); one wave decodes the leaf once into LDS
-// (dynamic, 8 bytes per possible key: S - 7 codes plus the head) and binary-
-// searches each of them there.
+// keys[sbeg[f] .. sbeg[f + 1]); one wave decodes the leaf once into LDS (dynamic)
+// and binary-searches each of them there.  Leaves of at most 1024 bytes whose
+// keys and slice span less than 2^32 keep a 32-bit offset per byte
+// (splice_parse), others their 64-bit keys (a leaf holds at most S - 7): 68 us
+// for 27 000 leaves of 375 keys with 64-bit keys, 36 with offsets.
 __global__ void __launch_bounds__(kWave) k_fuse_member_leaf(QueryArgs a, const uint64_t* __restrict__ keys,
                                                             const uint32_t* __restrict__ sbeg,
                                                             uint8_t* __restrict__ member) {
-  extern __shared__ uint64_t K[];
+  extern __shared__ __align__(16) uint8_t smem[];
+  const uint32_t lane = lane_id();
   for (uint64_t f = blockIdx.x; f < a.L; f += gridDim.x) {
     const uint32_t b = sbeg[f], e = sbeg[f + 1];
     if (b == e) continue;
     const uint32_t u = a.used[f];
-    const uint32_t nk =
-        wave_decode_leaf(a.bytes + f * (uint64_t)a.S, u, [&](uint32_t i, uint64_t x, uint64_t) { K[i] = x; });
-    __syncthreads();
-    for (uint32_t j = b + lane_id(); j < e; j += kWave) {
-      const uint64_t x = keys[j];
-      uint32_t lo = 0, hi = nk;
-      while (lo < hi) {
-        const uint32_t mid = (lo + hi) >> 1;
-        if (K[mid] < x)
-          lo = mid + 1;
-        else
-          hi = mid;
+    const uint64_t hd = a.head[f], k0 = keys[b];
+    const uint64_t base = u && hd < k0 ? hd : k0;
+    const uint64_t above = f + 1 < a.L ? a.head[f + 1] : ~0ull;
+    const uint8_t* src = a.bytes + f * (uint64_t)a.S;
+    if (a.S <= kWaveMaxS && above - base <= 1ull << 32) {
+      uint32_t* K = reinterpret_cast<uint32_t*>(smem);
+      uint32_t* term = K + kWaveMaxS;
+      uint4 w = make_uint4(0, 0, 0, 0);
+      if (16 * lane < u) w = *reinterpret_cast<const uint4*>(src + 16 * lane);
+      const uint32_t tm = splice_parse(w, u, (uint32_t)(hd - base), K), tm2 = dpp_next32(tm);
+      if (!(lane & 1)) term[lane / 2] = tm | tm2 << 16;
+      __syncthreads();
+      for (uint32_t j = b + lane; j < e; j += kWave) {
+        const uint32_t x = (uint32_t)(keys[j] - base);
+        uint32_t v;
+        const uint32_t p = splice_find(K, u, x, &v);
+        member[j] = p < u && v == x && (p < 8 || ((term[p / 32] >> (p & 31)) & 1u)) ? 1 : 0;
       }
-      member[j] = (lo < nk && K[lo] == x) ? 1 : 0;
+    } else {
+      uint64_t* K = reinterpret_cast<uint64_t*>(smem);
+      const uint32_t nk = wave_decode_leaf(src, u, [&](uint32_t i, uint64_t x, uint64_t) { K[i] = x; });
+      __syncthreads();
+      for (uint32_t j = b + lane; j < e; j += kWave) {
+        const uint64_t x = keys[j];
+        const uint32_t lo = lds_lower_bound<uint64_t>(K, nk, x);
+        member[j] = (lo < nk && K[lo] == x) ? 1 : 0;
+      }
     }
     __syncthreads();
   }
 }
+__host__ inline uint32_t member_leaf_smem(uint32_t S) {
+  const uint32_t wide = 8 * S, narrow = 4 * kWaveMaxS + 4 * (kWaveMaxS / 32);
+  return wide > narrow || S > kWaveMaxS ? wide : narrow;
+}
 
 // Gather of requests that live in device memory: request r's n keys from src
-// to out[dst ..); one block per request.
+// to out[dst ..), m keys in all, four positions per thread.
 struct GatherReq {
   const uint64_t* src;
   uint64_t dst;
   uint64_t n;
 };
 
-__global__ void __launch_bounds__(256) k_fuse_gather(const GatherReq* __restrict__ t, uint32_t nreq,
+__global__ void __launch_bounds__(256) k_fuse_gather(const GatherReq* __restrict__ t, uint32_t nreq, uint64_t m,
                                                      uint64_t* __restrict__ out) {
-  for (uint32_t r = blockIdx.x; r < nreq; r += gridDim.x) {
-    const GatherReq g = t[r];
-    for (uint64_t i = threadIdx.x; i < g.n; i += blockDim.x) out[g.dst + i] = g.src[i];
+  const uint64_t base = (uint64_t)blockIdx.x * 1024 + threadIdx.x;
+  auto at = [&](uint32_t r) { return r < nreq ? t[r].dst : m; };
+  uint64_t end = 0, from = 0, x[4];
+  const uint64_t* src = nullptr;
+#pragma unroll
+  for (int q = 0; q < 4; q++) {
+    const uint64_t i = base + 256 * q;
+    if (i < m && i >= end) {
+      const GatherReq g = t[fuse_owner(at, nreq, i)];
+      src = g.src;
+      from = g.dst;
+      end = g.dst + g.n;
+    }
+    x[q] = i < m ? src[i - from] : 0;
   }
+#pragma unroll
+  for (int q = 0; q < 4; q++)
+    if (base + 256 * q < m) out[base + 256 * q] = x[q];
 }
 
 // Per sorted item: whether its request changes the key (credit, stored at the
@@ -134,19 +205,6 @@ __global__ void __launch_bounds__(256) k_fuse_split(const uint64_t* __restrict__
       cnt[2] = pos[nd] >> 32;
     }
   }
-}
-
-// Request owning position p: the r with off[r] <= p < off[r + 1].
-__device__ __forceinline__ uint32_t fuse_req_of(const uint64_t* off, uint32_t nreq, uint64_t p) {
-  uint32_t lo = 0, hi = nreq + 1;  // first index with off[idx] > p, minus one
-  while (lo < hi) {
-    const uint32_t mid = (lo + hi) >> 1;
-    if (off[mid] <= p)
-      lo = mid + 1;
-    else
-      hi = mid;
-  }
-  return lo - 1;
 }
 
 // Sum of the credit bytes of every request (positions are request-contiguous).
