@@ -146,7 +146,7 @@ struct cpma {
   DevBuf kin, kb0, kb1, kdedup, leafid, segpos, seg_leaf, seg_begin, seg_desc, heavy, spill, scan_tmp, ovf, arena,
       stage, pyr, win, wargs, cnt, koff, win_id, welem, P, ccost, ncost, lstart, planU, plan_used,
       spare_bytes, spare_used, spare_head, fg_level, fg_deg, fg_p, fg_c, fg_acc,
-      win_of_leaf, fail, qa, qb, qfirst, qnvis, qvoff, qsum, qcount, qout, qprefix, giant, pg_tab, pg_edge, lastk, lckpt, ne_rank, ne_list, chain_pfx,
+      win_of_leaf, fail, qa, qb, qfirst, qnvis, qvoff, qsum, qcount, qout, qprefix, giant, pg_tab, pg_edge, fg_done, lastk, lckpt, ne_rank, ne_list, chain_pfx,
       srec, wide, srcinfo, parts, qparts, fz_meta, fz_v0, fz_v1, fz_byte, fz_member, fz_code, fz_ctr, fz_res,
       ctr_buf, info_buf, qalg_buf, clen, spare_clen, vstage, kvals, kvdedup;
   // key-value sets: the current update batch's values (device, repeat-free and
@@ -190,7 +190,7 @@ struct cpma {
             &qout,      &lastk,     &ne_rank,   &ne_list,     &chain_pfx,  &srec,        &wide,       &srcinfo,
             &parts,     &qparts,    &fz_meta,   &fz_v0,       &fz_v1,      &fz_byte,     &fz_member,  &fz_code,
             &fz_ctr,    &fz_res,    &ctr_buf,   &info_buf,    &qalg_buf,   &lckpt,      &clen,        &spare_clen,
-            &vstage,    &kvals,     &kvdedup,   &qprefix,  &giant,       &pg_tab,    &pg_edge};
+            &vstage,    &kvals,     &kvdedup,   &qprefix,  &giant,       &pg_tab,    &pg_edge,   &fg_done};
   }
 
   Bounds bounds(uint64_t Lx) const {
@@ -2538,11 +2538,27 @@ uint32_t bfs_levels(cpma* s, uint32_t nv, uint32_t source, bool symmetric, uint3
   // set (its vertices have the most edges, so top-down gets dear early)
   uint64_t frontier = 1, unvisited = nv - 1;
   uint32_t cur = 0;
+  const uint64_t per_block = kBfsGroup * (256 / kWave);
+  const uint32_t sgrid = (uint32_t)((s->L + per_block - 1) / per_block);
+  uint8_t* done = nullptr;  // leaves without unvisited sources, from the first bottom-up level on
+  bool asked = false;
   for (; frontier > 0 && cur < nv; cur++) {
-    if (!symmetric || 4 * frontier <= unvisited)
-      hipLaunchKernelGGL(k_fg_bfs_step<false>, dim3(fg_grid(s)), dim3(256), 0, st, g, bb, lv, cur);
-    else
-      hipLaunchKernelGGL(k_fg_bfs_step<true>, dim3(fg_grid(s)), dim3(256), 0, st, g, bb, lv, cur);
+    if (!symmetric || 4 * frontier <= unvisited) {
+      hipLaunchKernelGGL(k_fg_bfs_step<false>, dim3(sgrid), dim3(256), 0, st, g, bb, lv, cur, (uint8_t*)nullptr);
+    } else {
+      if (!asked) {
+        asked = true;
+        try {
+          ensure(s->fg_done, s->L);
+          done = s->fg_done.as<uint8_t>();
+          hipLaunchKernelGGL((k_fill<uint8_t>), dim3(grid_for(s->L, 256, 4096)), dim3(256), 0, st, done, s->L,
+                             (uint8_t)0);
+        } catch (const Fail& f) {
+          if (f.st != CPMA_ERR_NOMEM) throw;  // without them every level tests the bitmaps only
+        }
+      }
+      hipLaunchKernelGGL(k_fg_bfs_step<true>, dim3(sgrid), dim3(256), 0, st, g, bb, lv, cur, done);
+    }
     hipLaunchKernelGGL(k_fg_level_bits, dim3(cgrid), dim3(256), 0, st, (const uint32_t*)lv, nv, cur + 1, front,
                        seen, cpart);
     hipLaunchKernelGGL(k_fg_fold_counts, dim3(1), dim3(1024), 0, st, (const unsigned long long*)cpart, cgrid,
