@@ -61,3 +61,24 @@ def test_values(cp, k):
     got, found = c.get(uniq)
     assert np.all(found)
     assert np.array_equal(got, vals[first])
+
+
+def test_skewed_batches_in_a_row(cp, orc):
+    """A second skewed batch of the same bit length goes to the radix passes after
+    one count of its buckets; the batches after it are split again."""
+    c = cp.CPMA(synth.uniform_keys(50000, 5, bits=34))
+    S = orc.build_set(synth.uniform_keys(50000, 5, bits=34))
+    r = np.random.default_rng(9)
+    top = np.uint64((1 << 34) - 1)  # every batch has the same bit length
+    for i, kind in enumerate("zzuzu"):
+        keys = synth.zipf_keys(600_000, 6 + i, bits=34) if kind == "z" else synth.uniform_keys(600_000, 6 + i, bits=34)
+        keys = np.concatenate([keys, [top]])[r.permutation(len(keys) + 1)]
+        print(f"[sort tiles] batch {i} {kind}", flush=True)
+        c.stats_select(["sort"])
+        S, added = orc.insert(S, keys)
+        assert c.insert_batch(keys) == added
+        assert c.stats()["sort"][2] / len(keys) == (144 if kind == "z" else 40), (i, kind)
+        c.stats_select([])
+        b, u, h = c.export()
+        code, msg = orc.check_image(b, u, h, c.geometry()[1], S)
+        assert code == 0, msg
