@@ -3,6 +3,7 @@
 // wave merge or for one lane): one block per slice, and for the longest slices
 // one block per piece of a slice.
 #pragma once
+#include "merge_wave.hpp"
 #include "update.hpp"
 
 namespace cpma_dev {
@@ -52,11 +53,12 @@ struct HeavyRun {
   uint32_t i0, i1, off;  // this thread's keys and its byte offset
   uint32_t total;
 };
-__device__ __forceinline__ uint32_t heavy_cost(const uint64_t* C, uint32_t i, bool has_pred, uint64_t pred) {
-  return i ? vlen(C[i] - C[i - 1]) : (has_pred ? vlen(C[0] - pred) : 8u);
+template <typename KT>
+__device__ __forceinline__ uint32_t heavy_cost(const KT* C, uint32_t i, bool has_pred, KT pred) {
+  return i ? vlen_t((KT)(C[i] - C[i - 1])) : (has_pred ? vlen_t((KT)(C[0] - pred)) : 8u);
 }
-__device__ __forceinline__ HeavyRun heavy_plan(const uint64_t* C, uint32_t m, bool has_pred, uint64_t pred,
-                                               uint32_t* wsum) {
+template <typename KT>
+__device__ __forceinline__ HeavyRun heavy_plan(const KT* C, uint32_t m, bool has_pred, KT pred, uint32_t* wsum) {
   HeavyRun r;
   const uint32_t per = (m + kHeavyThreads - 1) / kHeavyThreads;
   r.i0 = min(m, per * threadIdx.x);
@@ -66,54 +68,107 @@ __device__ __forceinline__ HeavyRun heavy_plan(const uint64_t* C, uint32_t m, bo
   r.off = heavy_scan(s, wsum, &r.total);
   return r;
 }
-template <typename P>
-__device__ __forceinline__ void heavy_encode(const uint64_t* C, const HeavyRun& r, bool has_pred, uint64_t pred,
+template <typename KT, typename P>
+__device__ __forceinline__ void heavy_encode(const KT* C, const HeavyRun& r, bool has_pred, KT pred, uint64_t base,
                                              P dst) {
   auto p = dst + r.off;
   for (uint32_t i = r.i0; i < r.i1; i++) {
     if (i == 0 && !has_pred) {
-      put_le64(p, C[0]);
+      put_le64(p, base + (uint64_t)C[0]);
       p += 8;
     } else {
-      p += vput(p, C[i] - (i ? C[i - 1] : pred));
+      KT d = C[i] - (i ? C[i - 1] : pred);
+      while (d >= 0x80) {
+        *p++ = (uint8_t)(d | 0x80);
+        d >>= 7;
+      }
+      *p++ = (uint8_t)d;
     }
   }
 }
 
 // LDS of k_merge_heavy for leaf size S and merged-key room cap beyond a full
 // leaf (byte offsets, each 16-byte aligned for even S): old keys A (a leaf
-// holds at most S - 7 keys: an 8-byte head and one byte per further key),
-// their presence flags F, the histogram N of the new batch keys' ranks, the
-// encode buffer and, with cap > 0, ccap = S - 7 + cap merged keys.
+// holds at most S - 7 keys: an 8-byte head and one byte per further key), the
+// counts P by rank, and, with cap > 0, room for ccap = S - 7 + cap merged keys of 8
+// bytes or twice as many offsets of 4.  The new codes take the place of A and P.
 struct HeavyLayout {
-  uint32_t f, n, buf, c, ccap, total;
+  uint32_t p, c, ccap, total;
   __host__ __device__ HeavyLayout(uint32_t S, uint32_t cap) {
     const uint32_t maxA = S - 7;
-    f = 8u * (maxA + 1);
-    n = f + 4u * ((maxA + 4) & ~3u);
-    buf = n + 4u * ((maxA + 4) & ~3u);
-    c = buf + ((S + 15u) & ~15u);
+    p = 8u * (maxA + 1);
+    c = (p + 4u * (maxA + 1) + 15u) & ~15u;
     ccap = cap ? maxA + cap : 0u;
     total = c + 8u * ccap;
   }
 };
 
+// Old keys of a leaf of at most 1024 bytes as offsets from base, four bytes a thread:
+// a code of at most five bytes carries its place in from the word before.
+__device__ __forceinline__ uint32_t heavy_decode_narrow(const uint8_t* __restrict__ lp, uint32_t used,
+                                                        uint32_t head_rel, uint32_t* A, uint32_t* wsum) {
+  const uint32_t pos = 4u * threadIdx.x;
+  uint32_t w = pos < used ? *reinterpret_cast<const uint32_t*>(lp + pos) : 0u;
+  const uint32_t before = pos > 8 && pos < used ? *reinterpret_cast<const uint32_t*>(lp + pos - 4) : 0u;
+  const uint32_t nvalid = pos < used ? min(4u, used - pos) : 0u;
+  uint32_t valid = nvalid == 4 ? 0x80808080u : (1u << (8 * nvalid)) - 1u;
+  uint32_t run = 0;
+  if (pos < 8) {  // the head: one key, counted at byte 7
+    w = 0x80808080u;
+    valid = 0;
+    if (pos == 0) run = head_rel;
+  }
+  const uint32_t stop = ~before & 0x80808080u;
+  uint32_t sh = stop ? 7u * ((uint32_t)__clz((int)stop) >> 3) : 28u, k[4];
+#pragma unroll
+  for (int j = 0; j < 4; j++) {
+    uint32_t c;
+    asm("v_bfe_i32 %0, %1, %2, 1" : "=v"(c) : "v"(w), "i"(8 * j + 7));
+    if (8 * j < 32 && (valid >> (8 * j)) & 0xffu) run += __builtin_amdgcn_ubfe(w, 8 * j, 7) << (sh & 31u);
+    k[j] = run;
+    sh = (sh + 7u) & c;
+  }
+  const uint32_t ends = (~w & valid & 0x80808080u) | (pos == 4 && used ? 0x80000000u : 0u);
+  const uint32_t n = (uint32_t)__popc(ends);
+  // both scans in one exchange
+  const uint32_t wid = threadIdx.x / kWave, is = wave_incl_scan(run), in = wave_incl_scan(n);
+  if (lane_id() == kWave - 1) {
+    wsum[2 * wid] = is;
+    wsum[2 * wid + 1] = in;
+  }
+  __syncthreads();
+  uint32_t at = in - n, base = is - run, all = 0;
+#pragma unroll
+  for (uint32_t v = 0; v < kHeavyThreads / kWave; v++) {
+    base += v < wid ? wsum[2 * v] : 0u;
+    at += v < wid ? wsum[2 * v + 1] : 0u;
+    all += wsum[2 * v + 1];
+  }
+#pragma unroll
+  for (int j = 0; j < 4; j++)
+    if (ends & (0x80u << (8 * j))) A[at++] = base + k[j];
+  return all;
+}
+
 // One block merges one long insert slice into its leaf.  Each batch key is ranked
 // among the old keys by binary search in LDS; an old key's output position is its
-// index plus the number of new batch keys ranked at or below it (an LDS histogram
-// of those ranks, scanned), so the slice is only streamed, twice.  The merged keys
-// are built in LDS when at most ccap of them result, else in the HBM staging
-// buffer, then encoded in place or into the arena.  Four waves share a slice's
-// LDS (33 KB at S = 1024): with one wave per slice and 41 KB three waves fitted a
-// CU, and 36 000 slices of 540 keys took 2.23 ms.
-__device__ __forceinline__ void heavy_slice(const MergeArgs& a, uint32_t s, uint8_t* smem, const HeavyLayout& lay,
-                                            uint32_t* wsum, uint64_t* shared, unsigned long long& delta,
-                                            unsigned long long& alg) {
+// index plus the number of new batch keys ranked at or below it (counted by rank in
+// LDS, scanned together with the batch keys already present, 16 bits each), so the
+// slice is only streamed.  The merged keys are built in LDS when they fit, else in
+// the HBM staging buffer, then encoded in LDS where A and P were and copied to the
+// leaf or the arena.  KT: 32-bit offsets from the segment's smallest possible key
+// for segments that span less than 2^32, else the keys.  Four waves share a slice's
+// LDS (29 KB at S = 1024).  36 000 slices of 540 keys: 2.23 ms with one wave per
+// slice, 0.70 with four waves, 64-bit keys, one wave decoding and two searches per
+// batch key, 0.50 now (half of that vector instructions; the rest waits at barriers).
+template <typename KT>
+__device__ __forceinline__ void heavy_slice(const MergeArgs& a, uint32_t s, uint64_t base, uint8_t* smem,
+                                            const HeavyLayout& lay, uint32_t* wsum, uint64_t* shared,
+                                            unsigned long long& delta, unsigned long long& alg) {
+  constexpr bool kNarrow = sizeof(KT) == 4;
   const uint32_t S = a.S, tid = threadIdx.x;
-  uint64_t* A = reinterpret_cast<uint64_t*>(smem);
-  uint32_t* F = reinterpret_cast<uint32_t*>(smem + lay.f);
-  uint32_t* N = reinterpret_cast<uint32_t*>(smem + lay.n);
-  uint8_t* buf = smem + lay.buf;
+  KT* A = reinterpret_cast<KT*>(smem);
+  uint32_t* P = reinterpret_cast<uint32_t*>(smem + lay.p);
   const uint64_t leaf = a.seg_leaf[s];
   const uint32_t b = a.seg_begin[s];
   const uint32_t nb = a.seg_begin[s + 1] - b;
@@ -121,79 +176,107 @@ __device__ __forceinline__ void heavy_slice(const MergeArgs& a, uint32_t s, uint
   const uint32_t used0 = a.used[leaf];
   const uint64_t* Bs = a.B + b;
   __syncthreads();  // the slice before is done with the LDS
-  if (tid < kWave) {
-    const uint32_t n = wave_decode_leaf(lp, used0, [&](uint32_t i, uint64_t x, uint64_t) { A[i] = x; });
-    if (tid == 0) shared[0] = n;
+  uint32_t nA;
+  for (uint32_t i = tid; i <= S - 7; i += kHeavyThreads) P[i] = 0;
+  if constexpr (kNarrow) {
+    nA = heavy_decode_narrow(lp, used0, (uint32_t)(a.head[leaf] - base), A, wsum);
+    __syncthreads();
+  } else {
+    if (tid < kWave) {
+      const uint32_t n = wave_decode_leaf(lp, used0, [&](uint32_t i, uint64_t x, uint64_t) { A[i] = x; });
+      if (tid == 0) shared[0] = n;
+    }
+    __syncthreads();
+    nA = (uint32_t)shared[0];
   }
-  for (uint32_t i = tid; i <= S - 7; i += kHeavyThreads) {
-    F[i] = 0;
-    N[i] = 0;
+  // the first batch keys of a thread keep their ranks in registers
+  constexpr uint32_t kKeep = 4;
+  KT kept[kKeep];
+  uint32_t rk[kKeep];  // rank, or ~0 when present or past the slice
+  auto rank = [&](KT x, uint32_t& r) {
+    r = lds_lower_bound<KT>(A, nA, x);
+    return r < nA && A[r] == x;
+  };
+#pragma unroll
+  for (uint32_t q = 0; q < kKeep; q++) {
+    const uint32_t j = tid + q * kHeavyThreads;
+    kept[q] = 0;
+    rk[q] = ~0u;
+    if (j < nb) {
+      kept[q] = (KT)(Bs[j] - base);
+      uint32_t r;
+      const bool present = rank(kept[q], r);
+      atomicAdd(&P[r], present ? 1u << 16 : 1u);
+      if (!present) rk[q] = r;
+    }
+  }
+  for (uint32_t j = tid + kKeep * kHeavyThreads; j < nb; j += kHeavyThreads) {
+    uint32_t r;
+    const bool present = rank((KT)(Bs[j] - base), r);
+    atomicAdd(&P[r], present ? 1u << 16 : 1u);
   }
   __syncthreads();
-  const uint32_t nA = (uint32_t)shared[0];
-  for (uint32_t j = tid; j < nb; j += kHeavyThreads) {
-    const uint64_t x = Bs[j];
-    const uint32_t r = lds_lower_bound(A, nA, x);
-    if (r < nA && A[r] == x)
-      F[r] = 1;
-    else
-      atomicAdd(&N[r], 1u);
-  }
-  __syncthreads();
-  // exclusive scans: F[i] = batch keys already present among A[0, i),
-  // N[i] = new batch keys whose rank among the old keys is below i
-  heavy_scan_inplace(F, nA + 1, wsum);
-  heavy_scan_inplace(N, nA + 1, wsum);
-  const uint32_t present = F[nA];
+  // P[i], scanned: new batch keys whose rank is below i, and (high half) batch keys
+  // present among A[0, i)
+  heavy_scan_inplace(P, nA + 1, wsum);
+  // all batch keys are ranked at most nA: the last entry lacks those ranked nA, which
+  // are new
+  const uint32_t present = P[nA] >> 16;
   const uint32_t m = nA + nb - present;
-  uint64_t* stage = nullptr;
-  if (m > lay.ccap) {
+  KT* stage = nullptr;
+  if (m > lay.ccap * (kNarrow ? 2u : 1u)) {
     if (tid == 0) shared[1] = atomicAdd(&a.ctr->stage_cursor, (unsigned long long)m);
     __syncthreads();
     if (shared[1] + m > a.stage_cap) {
       if (tid == 0) atomicOr(&a.ctr->error, 2u);
       return;
     }
-    stage = a.stage + shared[1];
+    stage = reinterpret_cast<KT*>(a.stage + shared[1]);
   }
   // C in LDS or in the staging buffer: two instances, so that each copy's
   // accesses have a known address space
   auto place_and_store = [&](auto C) {
-    for (uint32_t j = tid; j < nb; j += kHeavyThreads) {
-      const uint64_t x = Bs[j];
-      const uint32_t r = lds_lower_bound(A, nA, x);
-      if (!(r < nA && A[r] == x)) C[r + j - F[r]] = x;
+#pragma unroll
+    for (uint32_t q = 0; q < kKeep; q++)
+      if (rk[q] != ~0u) C[rk[q] + (tid + q * kHeavyThreads) - (P[rk[q]] >> 16)] = kept[q];
+    for (uint32_t j = tid + kKeep * kHeavyThreads; j < nb; j += kHeavyThreads) {
+      const KT x = (KT)(Bs[j] - base);
+      uint32_t r;
+      if (!rank(x, r)) C[r + j - (P[r] >> 16)] = x;
     }
     // new batch keys before A[i]: those ranked at most i
-    for (uint32_t i = tid; i < nA; i += kHeavyThreads) C[i + N[i + 1]] = A[i];
+    for (uint32_t i = tid; i < nA; i += kHeavyThreads) C[i + (P[i + 1] & 0xffffu)] = A[i];
     __threadfence_block();
-    __syncthreads();
-    const HeavyRun run = heavy_plan(C, m, false, 0, wsum);
+    __syncthreads();  // A and P have been read
+    const HeavyRun run = heavy_plan<KT>(C, m, false, (KT)0, wsum);
     const uint32_t T = run.total;
-    uint64_t written;
-    if (T <= S) {
-      const uint32_t len = (max(used0, T) + 15u) & ~15u;
-      for (uint32_t o = 16u * tid; o < len; o += 16u * kHeavyThreads)
-        *reinterpret_cast<uint4*>(buf + o) = make_uint4(0, 0, 0, 0);
-      __syncthreads();
-      heavy_encode(C, run, false, 0, buf);
-      __syncthreads();
-      for (uint32_t o = 16u * tid; o < len; o += 16u * kHeavyThreads)
-        *reinterpret_cast<uint4*>(lp + o) = *reinterpret_cast<const uint4*>(buf + o);
-      written = len;
-    } else {
+    uint64_t written = T;
+    uint8_t* dst = lp;
+    if (T > S) {
       const uint64_t off = arena_region(a, s);
       if (off + (((uint64_t)T + 15) & ~15ull) > a.arena_cap) {
         if (tid == 0) atomicOr(&a.ctr->error, 1u);
         return;
       }
-      heavy_encode(C, run, false, 0, a.arena + off);
+      dst = a.arena + off;
       if (tid == 0) a.ovf[leaf] = off;
-      written = T;
+    }
+    const uint32_t len = ((T > S ? T : max(used0, T)) + 15u) & ~15u;
+    if (T <= S) written = len;
+    if (len <= lay.c) {
+      for (uint32_t o = 16u * tid; o < len; o += 16u * kHeavyThreads)
+        *reinterpret_cast<uint4*>(smem + o) = make_uint4(0, 0, 0, 0);
+      __syncthreads();
+      heavy_encode<KT>(C, run, false, (KT)0, base, smem);
+      __syncthreads();
+      for (uint32_t o = 16u * tid; o < len; o += 16u * kHeavyThreads)
+        *reinterpret_cast<uint4*>(dst + o) = *reinterpret_cast<const uint4*>(smem + o);
+    } else {
+      heavy_encode<KT>(C, run, false, (KT)0, base, dst);
     }
     if (tid == 0) {
       a.used[leaf] = T;
-      a.head[leaf] = C[0];
+      a.head[leaf] = base + (uint64_t)C[0];
     }
     alg += used0 + written + 8ull * nb + 20;
     delta += nb - present;
@@ -201,7 +284,7 @@ __device__ __forceinline__ void heavy_slice(const MergeArgs& a, uint32_t s, uint
   if (stage)
     place_and_store(stage);
   else
-    place_and_store(reinterpret_cast<uint64_t*>(smem + lay.c));
+    place_and_store(reinterpret_cast<KT*>(smem + lay.c));
 }
 
 // Merges the slices of the heavy list (the lane merge's longest), or with
@@ -213,7 +296,7 @@ __device__ __forceinline__ void heavy_slice(const MergeArgs& a, uint32_t s, uint
 __global__ void __launch_bounds__(kHeavyThreads) k_merge_heavy(MergeArgs a, uint32_t cap, int from_spill,
                                                                uint32_t* __restrict__ giant_list) {
   extern __shared__ __align__(16) uint8_t smem[];
-  __shared__ uint32_t wsum[kHeavyThreads / kWave];
+  __shared__ uint32_t wsum[2 * kHeavyThreads / kWave];
   __shared__ uint64_t shared[2];
   const HeavyLayout lay(a.S, cap);
   const uint32_t n = from_spill ? a.ctr->nspill : a.ctr->heavy;
@@ -225,7 +308,13 @@ __global__ void __launch_bounds__(kHeavyThreads) k_merge_heavy(MergeArgs a, uint
       if (threadIdx.x == 0) giant_list[atomicAdd(&a.ctr->ngiant, 1u)] = s;
       continue;
     }
-    heavy_slice(a, s, smem, lay, wsum, shared, delta, alg);
+    const uint64_t leaf = a.seg_leaf[s], head = a.head[leaf], first = a.B[a.seg_begin[s]];
+    const uint64_t base = a.used[leaf] && head < first ? head : first;
+    const uint64_t above = leaf + 1 < a.L ? a.head[leaf + 1] : ~0ull;
+    if (a.S <= kWaveMaxS && above - base <= 1ull << 32)
+      heavy_slice<uint32_t>(a, s, base, smem, lay, wsum, shared, delta, alg);
+    else
+      heavy_slice<uint64_t>(a, s, 0, smem, lay, wsum, shared, delta, alg);
   }
   if (threadIdx.x == 0) {
     a.part[2 * blockIdx.x] = delta;
@@ -348,7 +437,7 @@ __global__ void __launch_bounds__(kHeavyThreads) k_giant_merge(MergeArgs a, Gian
     const bool has_pred = c0 > 0;
     uint64_t pred = has_pred ? Bs[c0 - 1] : 0;
     if (has_pred && r0 && A[r0 - 1] > pred) pred = A[r0 - 1];
-    const HeavyRun run = heavy_plan(M, m, has_pred, pred, wsum);
+    const HeavyRun run = heavy_plan<uint64_t>(M, m, has_pred, pred, wsum);
     if (!kWrite) {
       if (tid == 0) {
         g.bytes[p] = run.total;
@@ -360,7 +449,7 @@ __global__ void __launch_bounds__(kHeavyThreads) k_giant_merge(MergeArgs a, Gian
       const uint64_t U = g.scan[g.first[lo + 1]] - start, region = arena_region(a, s);
       const bool fits = region + ((U + 15) & ~15ull) <= a.arena_cap;
       if (fits)
-        heavy_encode(M, run, has_pred, pred, a.arena + region + off);
+        heavy_encode<uint64_t>(M, run, has_pred, pred, 0, a.arena + region + off);
       else if (tid == 0)
         atomicOr(&a.ctr->error, 1u);
       if (tid == 0) {

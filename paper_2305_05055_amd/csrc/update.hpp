@@ -217,6 +217,7 @@ struct MergeArgs {
   Counters* ctr;
   unsigned long long* part;  // per wave of the launch: {keys added / removed, algorithmic bytes}
   uint32_t S;
+  uint64_t L;
   int is_insert;
   // key-value leaves
   uint32_t kv;               // every key carries an 8-byte value
