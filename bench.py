@@ -258,7 +258,7 @@ def trace_summary(kind, csv_path, args):
     if kind == "steps":
         cmd = ("rocprofv3 --kernel-trace --stats --output-format csv -d " + PROF_DIR + "/tr_steps -o run -- "
                f"python3 /root/repo/bench.py --only-steps --no-cpu-baseline {shape}")
-        starts = [i for i, r in enumerate(rows) if r[1] in VALIDATION_KERNELS]
+        starts = [i for i, r in enumerate(rows) if r[1].split("<")[0] in VALIDATION_KERNELS]
         nb = MERGES_PER_STEP * args.steps
         first, last = starts[-(nb + TAIL_MERGES)], starts[-TAIL_MERGES]
         # each batch's validation follows the fills that clear its counters
