@@ -339,8 +339,12 @@ uint32_t sort_blocks(uint64_t k) {
   return (uint32_t)((k + tile - 1) / tile);
 }
 
-// s->cnt for the digit counts of k keys.
-void sort_hist_buffer(cpma* s, uint64_t k) { ensure(s->cnt, ((uint64_t)sort_blocks(k) * 256 + 1) * sizeof(uint32_t)); }
+// s->cnt for the digit counts of k keys, and the two words of s->koff that a spread
+// over a fresh layout takes after the merge, when an update must not allocate.
+void sort_hist_buffer(cpma* s, uint64_t k) {
+  ensure(s->cnt, ((uint64_t)sort_blocks(k) * 256 + 1) * sizeof(uint32_t));
+  ensure(s->koff, 2 * sizeof(uint64_t));
+}
 
 // LSD radix passes (8-bit digits, `passes` of them) over k keys from src,
 // alternating between kb0 and kb1; with kv every key carries a 32-bit value
