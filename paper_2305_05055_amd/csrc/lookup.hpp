@@ -8,7 +8,7 @@
 // leaf, the obvious split, asks the L1 for 64 separate lines with every 16-byte
 // load and walks its leaf in a chain of a dozen rounds, and a wave waits for the
 // longest of its 64 walks.  1e6 membership tests on 1e8 keys: 389 -> 200 us; the
-// partial end leaves of 1e6 ranges: 816 -> 460 us; get of 1e6 keys of a key-value
+// partial end leaves of 1e6 ranges: 816 -> 423 us; get of 1e6 keys of a key-value
 // set (byte loads before): 727 -> 151 us.  Bound: VALU issue of the byte walk
 // (about 135 instructions per round).
 #pragma once
@@ -127,9 +127,20 @@ struct Lookup {
 // continuation byte's all-ones mask).  The 16 bytes in which a row's offset
 // reaches X go to `reach`; the lanes before them only need their totals (kSum: and
 // the sum of their keys' offsets).  Returns the rows' lanes that reached X.
-template <typename KT, bool kSum>
+//
+// kPair: a row may look for a second key X2 >= X in the same walk (dual), with its
+// own slot, count, sum and lanes in `two`; X2 = X otherwise.
+template <typename KT>
+struct Second {
+  KT X;
+  bool dual;
+  Reach* reach;
+  uint32_t cnt;
+  uint64_t sum, found;
+};
+template <typename KT, bool kSum, bool kPair>
 __device__ __forceinline__ uint64_t row_walk(const uint8_t* __restrict__ leaf, uint4 w, uint32_t used, KT X,
-                                             Reach* reach, uint32_t& cnt, uint64_t& sum) {
+                                             Reach* reach, uint32_t& cnt, uint64_t& sum, Second<KT>& two) {
   const uint32_t l16 = (uint32_t)lane_id() & 15u;
   KT base = 0;        // offset reached before the round (the row's lanes alike)
   uint32_t tail = 0;  // this lane's trailing continuation bytes in the round before
@@ -160,17 +171,29 @@ __device__ __forceinline__ uint64_t row_walk(const uint8_t* __restrict__ leaf, u
     const KT at = base + (incl - run), end = base + incl;
     base += row_last(incl);
     if constexpr (kSum) {
-      if (end < X) {
+      if (end < (kPair ? two.X : X)) {
         const uint32_t c = 16u - (uint32_t)(__popc(w.x & 0x80808080u) + __popc(w.y & 0x80808080u) +
                                             __popc(w.z & 0x80808080u) + __popc(w.w & 0x80808080u));
-        cnt += c;
-        sum += s + (uint64_t)c * (uint64_t)at;
+        const uint64_t t = s + (uint64_t)c * (uint64_t)at;
+        if (!kPair || end < X) {
+          cnt += c;
+          sum += t;
+        }
+        if constexpr (kPair) {
+          two.cnt += c;
+          two.sum += t;
+        }
       }
     }
     const bool here = end >= X && (at < X || pos0 == 0);
     if (here) *reach = Reach{w, (uint64_t)at, sh, 0};
     found |= __ballot(here);
-    const bool more = pos + 256 < used && base < X;
+    if constexpr (kPair) {
+      const bool here2 = two.dual && end >= two.X && (at < two.X || pos0 == 0);
+      if (here2) *two.reach = Reach{w, (uint64_t)at, sh, 0};
+      two.found |= __ballot(here2);
+    }
+    const bool more = pos + 256 < used && base < (kPair ? two.X : X);
     if (!__ballot(more)) return found;
     // a finished row goes on over bytes without keys
     w = make_uint4(0x80808080u, 0x80808080u, 0x80808080u, 0x80808080u);
@@ -184,9 +207,14 @@ __device__ __forceinline__ uint64_t row_walk(const uint8_t* __restrict__ leaf, u
 // besides the count is wanted (kEq alone: not even the count, unless kCnt).
 // Every lane then finishes its own lookup in the 16 bytes where it reached x: the
 // per-key comparisons run once per 64 lookups instead of once per four.
-template <bool kCnt, bool kSum, bool kEq>
+//
+// kPair: lanes 2i and 2i + 1 look up a range's two ends (x of the odd lane not below
+// the even one's); pairs in one leaf share a walk, and `order` (64 entries of LDS per
+// wave) lists the walks.  Many short ranges have both ends in one leaf: the end
+// leaves of 1e6 Zipf(1.2) ranges take 423 us, 477 with a walk per end.
+template <bool kCnt, bool kSum, bool kEq, bool kPair = false>
 __device__ __forceinline__ Lookup wave_lookup(const QueryArgs& a, bool valid, uint64_t leaf, uint64_t x,
-                                              Reach* reach) {
+                                              Reach* reach, uint8_t* order = nullptr) {
   const uint32_t l = (uint32_t)lane_id(), l16 = l & 15u;
   const uint64_t head = valid ? a.head[leaf] : kNoKey;
   const uint64_t next = valid && leaf + 1 < a.L ? a.head[leaf + 1] : kNoKey;
@@ -196,7 +224,34 @@ __device__ __forceinline__ Lookup wave_lookup(const QueryArgs& a, bool valid, ui
   const uint32_t used = valid && x >= head && head != kNoKey && !(kEq && x == kNoKey) ? a.used[leaf] : 0u;
   const uint64_t X = used ? x - head : 0;
   const bool wide = used && next - head >= 0xffffffffull;
-  const uint32_t nit = ((uint32_t)__popcll(__ballot(valid)) + 3u) / 4u;
+  const uint32_t nvalid = (uint32_t)__popcll(__ballot(valid));
+  uint32_t nwalk = nvalid, slot = l;  // walks, and the one that answers this lane
+  bool same = false, answered = true;
+  if constexpr (kPair) {
+    constexpr int kXor1 = 1 | (0 << 2) | (3 << 4) | (2 << 6);
+    const uint32_t other_used = dpp32<kXor1>(used);  // every lane takes part in the exchange
+    const uint64_t other_leaf = dpp64<kXor1>(leaf);
+    same = !a.raw && used && other_used && other_leaf == leaf;
+    const bool own = used && !(same && (l & 1u));
+    const uint64_t walks = __ballot(own);
+    nwalk = (uint32_t)__popcll(walks);
+    slot = __builtin_amdgcn_mbcnt_hi((uint32_t)(walks >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)walks, 0u));
+    if (own) order[slot] = (uint8_t)l;
+    const uint32_t other = dpp32<kXor1>(slot);
+    if (same && (l & 1u)) slot = other;
+    answered = used != 0;
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+  }
+  const uint32_t nit = (nwalk + 3u) / 4u;
+  auto walk_lane = [&](uint32_t it) {
+    const uint32_t w = 4u * it + (opaque_lane() >> 4);
+    if constexpr (kPair)
+      return w < nwalk ? (uint32_t)order[w] : 64u;
+    else
+      return w;
+  };
   const bool any_wide = __ballot(wide) != 0;
   Lookup out{0, 0, false};
   bool reached = false;
@@ -204,21 +259,32 @@ __device__ __forceinline__ Lookup wave_lookup(const QueryArgs& a, bool valid, ui
   uint32_t n_used = 0, n_leaf = 0;
   uint4 n_w = make_uint4(0, 0, 0, 0);
   auto fetch = [&](uint32_t it) {
-    const uint32_t from = 4u * it + (opaque_lane() >> 4);
+    const uint32_t from = walk_lane(it);
     n_used = from_lane(used, from);
+    if (kPair && from == 64u) n_used = 0;
     n_leaf = from_lane((uint32_t)leaf, from);
     if (16u * l16 < n_used) n_w = load16(a.bytes + (uint64_t)n_leaf * a.S + 16u * l16);
   };
   if (!a.raw) fetch(0);
 #pragma unroll 1
   for (uint32_t it = 0; it < nit; it++) {
-    const uint32_t from = 4u * it + (opaque_lane() >> 4);
-    const uint64_t Xr = from_lane(X, from);
+    const uint32_t from = walk_lane(it);
+    const bool none = kPair && from == 64u;
+    const uint64_t Xf = from_lane(X, from), Xr = none ? 1 : Xf;  // no key: a row without bytes never reaches 1
+    bool dual = false;
+    uint64_t X2 = Xr, sum2 = 0, found2 = 0;
+    uint32_t cnt2 = 0;
+    if constexpr (kPair) {
+      const uint32_t d = from_lane(same ? 1u : 0u, from);
+      dual = d != 0 && !none;
+      const uint64_t o = from_lane(X, from | 1u);
+      if (dual) X2 = o;
+    }
     uint64_t sum = 0, found = 0;
     uint32_t cnt = 0;
     bool eq = false;
     if (a.raw) {
-      const uint32_t m = from_lane(used, from) / 8;
+      const uint32_t uf = from_lane(used, from), m = none ? 0u : uf / 8;
       const uint64_t hd = from_lane(head, from);
       const uint64_t* k = reinterpret_cast<const uint64_t*>(a.bytes + (uint64_t)from_lane((uint32_t)leaf, from) * a.S);
       for (uint32_t i = l16; i < m; i += 16) {
@@ -232,23 +298,39 @@ __device__ __forceinline__ Lookup wave_lookup(const QueryArgs& a, bool valid, ui
       const uint8_t* lp = a.bytes + (uint64_t)n_leaf * a.S;
       const uint4 w = n_w;
       if (it + 1 < nit) fetch(it + 1);
+      auto walk = [&](auto zero) {
+        using KT = decltype(zero);
+        Second<KT> two{(KT)X2, dual, reach + (from | 1u), 0, 0, 0};
+        found = row_walk<KT, kCnt || kSum, kPair>(lp, w, ur, (KT)Xr, reach + from, cnt, sum, two);
+        cnt2 = two.cnt;
+        sum2 = two.sum;
+        found2 = two.found;
+      };
       if (any_wide)
-        found = row_walk<uint64_t, kCnt || kSum>(lp, w, ur, Xr, reach + from, cnt, sum);
+        walk((uint64_t)0);
       else
-        found = row_walk<uint32_t, kCnt || kSum>(lp, w, ur, (uint32_t)Xr, reach + from, cnt, sum);
+        walk((uint32_t)0);
     }
     // to the lanes whose lookups these were
-    const uint32_t ol = opaque_lane(), src = 16u * (ol & 3u);
-    const bool mine = (ol >> 2) == it;
+    const uint32_t ol = kPair ? slot : opaque_lane(), src = 16u * (ol & 3u);
+    const bool mine = answered && (ol >> 2) == it, second = kPair && same && (l & 1u);
     if constexpr (kCnt || kSum) {
-      const uint32_t c = from_lane(row_last(row_incl_scan(cnt)), src);
+      uint32_t c = from_lane(row_last(row_incl_scan(cnt)), src);
+      if constexpr (kPair) {
+        const uint32_t c2 = from_lane(row_last(row_incl_scan(cnt2)), src);
+        if (second) c = c2;
+      }
       if (mine) out.cnt = c;
     }
     if constexpr (kSum) {
-      const uint64_t t = from_lane(row_last(row_incl_scan(sum)), src);
+      uint64_t t = from_lane(row_last(row_incl_scan(sum)), src);
+      if constexpr (kPair) {
+        const uint64_t t2 = from_lane(row_last(row_incl_scan(sum2)), src);
+        if (second) t = t2;
+      }
       if (mine) out.sum = t;
     }
-    if (mine) reached = ((found >> src) & 0xffffu) != 0;
+    if (mine) reached = (((second ? found2 : found) >> src) & 0xffffu) != 0;
     if constexpr (kEq) {
       const uint64_t em = __ballot(eq);
       if (mine) out.eq = ((em >> src) & 0xffffu) != 0;
@@ -290,7 +372,7 @@ __device__ __forceinline__ Lookup wave_lookup(const QueryArgs& a, bool valid, ui
       // the values of the keys below x: the first of the leaf's m values
       const uint32_t m = used ? (a.fill[leaf] - used) / 8 : 0u;
 #pragma unroll 1
-      for (uint32_t it = 0; it < nit; it++) {
+      for (uint32_t it = 0; it < (nvalid + 3u) / 4u; it++) {
         const uint32_t from = 4u * it + (opaque_lane() >> 4);
         const uint32_t c = from_lane((uint32_t)out.cnt, from);
         const uint64_t* v = reinterpret_cast<const uint64_t*>(

@@ -30,6 +30,7 @@ __global__ void __launch_bounds__(256) k_rm_ends(QueryArgs a, uint64_t* __restri
                                                  unsigned long long* __restrict__ alg, unsigned int* ticket,
                                                  uint32_t per) {
   __shared__ Reach reach[256 / kWave][kWave];
+  __shared__ uint8_t order[256 / kWave][kWave];
   Reach* const mine = reach[threadIdx.x / kWave];
   if (ticket && blockIdx.x == 0 && threadIdx.x == 0) *ticket = 0;  // for k_rm_interior's prefix pass
   const uint32_t wave = blockIdx.x * (256 / kWave) + threadIdx.x / kWave, nwaves = gridDim.x * (256 / kWave);
@@ -42,7 +43,8 @@ __global__ void __launch_bounds__(256) k_rm_ends(QueryArgs a, uint64_t* __restri
     const bool some = lo < hi;
     // the even lane looks lo up, the odd one hi in the leaf of hi - 1
     const uint64_t leaf = wave_locate(a, valid, lane & 1 ? (some ? hi - 1 : 0) : lo);
-    const Lookup r = wave_lookup<true, true, false>(a, valid, leaf, lane & 1 ? hi : lo, mine);
+    const Lookup r = wave_lookup<true, true, false, true>(a, valid, leaf, lane & 1 ? hi : lo, mine,
+                                                          order[threadIdx.x / kWave]);
     constexpr int kXor1 = 1 | (0 << 2) | (3 << 4) | (2 << 6);
     const uint64_t leaf_l = dpp64<kXor1>(leaf), sum_l = dpp64<kXor1>(r.sum), cnt_l = dpp64<kXor1>(r.cnt);
     if (valid && !(lane & 1)) {
