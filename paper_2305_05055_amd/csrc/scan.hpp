@@ -1,4 +1,8 @@
-// Device-wide exclusive prefix sums (reduce -> scan of block totals -> apply).
+// Device-wide exclusive prefix sums (reduce -> scan of block totals -> apply).  Up to
+// kScanSumBlocks blocks the apply blocks add the earlier totals up themselves (at most
+// four coalesced loads a thread, about a microsecond) instead of a launch that scans
+// them (1.5 to 4.5 us and a gap of 2 to 5; insert and delete of 1e5 keys 479 -> 470
+// us, of 1e7 1461 -> 1445).
 // Inputs come from a functor so producers (flags, costs, counts) fuse into the scan.
 #pragma once
 #include "common.hpp"
@@ -8,6 +12,7 @@ namespace cpma_dev {
 constexpr int kScanThreads = 256;
 constexpr int kScanItems = 8;
 constexpr uint64_t kScanTile = (uint64_t)kScanThreads * kScanItems;
+constexpr uint64_t kScanSumBlocks = 1024;
 
 template <typename T>
 __device__ __forceinline__ T block_excl_scan(T v, T* wtot /*LDS [4]*/, T* total) {
@@ -40,9 +45,10 @@ __global__ void __launch_bounds__(kScanThreads) k_scan_reduce(F in, uint64_t n, 
   if (threadIdx.x == 0) partial[blockIdx.x] = tot;
 }
 
+// partial: the blocks' totals (totals), their exclusive scan, or null (one block).
 template <typename T, typename F>
-__global__ void __launch_bounds__(kScanThreads) k_scan_apply(F in, uint64_t n, T* out,
-                                                             const T* partial_scan) {
+__global__ void __launch_bounds__(kScanThreads) k_scan_apply(F in, uint64_t n, T* out, const T* partial,
+                                                             bool totals) {
   __shared__ T wtot[kScanThreads / kWave];
   const uint64_t base = (uint64_t)blockIdx.x * kScanTile + (uint64_t)threadIdx.x * kScanItems;
   T v[kScanItems];
@@ -52,8 +58,16 @@ __global__ void __launch_bounds__(kScanThreads) k_scan_apply(F in, uint64_t n, T
     v[j] = (base + j < n) ? in(base + j) : (T)0;
     s += v[j];
   }
+  T before = 0;
+  if (totals) {
+    T e = 0;
+    for (uint32_t b = threadIdx.x; b < blockIdx.x; b += kScanThreads) e += partial[b];
+    block_excl_scan<T>(e, wtot, &before);
+  } else if (partial) {
+    before = partial[blockIdx.x];
+  }
   T tot;
-  T ofs = block_excl_scan<T>(s, wtot, &tot) + (partial_scan ? partial_scan[blockIdx.x] : (T)0);
+  T ofs = block_excl_scan<T>(s, wtot, &tot) + before;
 #pragma unroll
   for (int j = 0; j < kScanItems; j++) {
     if (base + j < n) out[base + j] = ofs;
@@ -61,8 +75,7 @@ __global__ void __launch_bounds__(kScanThreads) k_scan_apply(F in, uint64_t n, T
   }
   // The last block also writes the grand total at position n.
   if (blockIdx.x == gridDim.x - 1 && threadIdx.x == kScanThreads - 1) {
-    T grand = (partial_scan ? partial_scan[blockIdx.x] : (T)0) + tot;
-    out[n] = grand;
+    out[n] = before + tot;
   }
 }
 
@@ -93,18 +106,20 @@ hipError_t scan_exclusive(F in, uint64_t n, T* out, T* tmp, hipStream_t s) {
   const uint64_t nb = (n + kScanTile - 1) / kScanTile;
   if (nb == 1) {
     hipLaunchKernelGGL((k_scan_apply<T, F>), dim3(1), dim3(kScanThreads), 0, s, in, n, out,
-                       (const T*)nullptr);
+                       (const T*)nullptr, false);
     return hipGetLastError();
   }
   T* partial = tmp;
   T* partial_scan = tmp + nb + 1;
   hipLaunchKernelGGL((k_scan_reduce<T, F>), dim3((uint32_t)nb), dim3(kScanThreads), 0, s, in, n,
                      partial);
-  hipError_t e = scan_exclusive<T>(LoadFn<T>{partial}, nb, partial_scan,
-                                   partial_scan + nb + 1, s);
-  if (e != hipSuccess) return e;
+  const bool totals = nb <= kScanSumBlocks;
+  if (!totals) {
+    hipError_t e = scan_exclusive<T>(LoadFn<T>{partial}, nb, partial_scan, partial_scan + nb + 1, s);
+    if (e != hipSuccess) return e;
+  }
   hipLaunchKernelGGL((k_scan_apply<T, F>), dim3((uint32_t)nb), dim3(kScanThreads), 0, s, in, n, out,
-                     (const T*)partial_scan);
+                     (const T*)(totals ? partial : partial_scan), totals);
   return hipGetLastError();
 }
 
