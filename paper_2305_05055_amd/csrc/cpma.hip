@@ -125,6 +125,8 @@ struct cpma {
   int device = 0;
   int num_cus = 256;
   uint32_t rm_blocks[2] = {2048, 2048};  // resident blocks of k_rm_interior<false>, <true>
+  int mid_bits = 0;  // bit length of the last unsorted batch of 4097 to 2^18 keys (0: none yet)
+  int mid_skip = 0;  // such batches to sort with radix passes at once, after a skewed one
   int msd_bits = 0;  // bit length of the last unsorted batch of the MSD split's size (0: none yet)
   // a small batch's merge totals, left for the single-block path check to fold
   const unsigned long long* fin_parts = nullptr;
@@ -402,6 +404,7 @@ struct MsdPlan {
   int r = 0;          // low bits sorted inside a bucket
   uint32_t nd = 0;    // buckets
   uint32_t nt = 0;    // split tiles
+  bool mid = false;   // a batch of 4097 to 2^18 keys
   uint64_t nc() const { return (uint64_t)nd * nt; }
 };
 
@@ -416,8 +419,18 @@ bool msd_plan(uint64_t k, int bits, MsdPlan* p) {
   return true;
 }
 
+bool mid_plan(uint64_t k, int bits, MsdPlan* p) {
+  const int b = std::min(kMidBits, bits);
+  if (bits - b > 32) return false;
+  p->r = bits - b;
+  p->nd = 1u << b;
+  p->nt = (uint32_t)((k + kMidTile - 1) / kMidTile);
+  p->mid = true;
+  return true;
+}
+
 void msd_buffers(cpma* s, uint64_t k, const MsdPlan& p) {
-  ensure(s->cnt, (p.nc() + 1) * sizeof(uint32_t));
+  ensure(s->cnt, std::max<uint64_t>(p.nc() + 1, 2 * (p.nd + 1)) * sizeof(uint32_t));
   ensure(s->koff, (p.nc() + 1) * sizeof(uint32_t));
   ensure(s->kb0, k * sizeof(uint64_t));
   ensure(s->kb1, k * sizeof(uint64_t));
@@ -454,14 +467,15 @@ void wait_published(cpma* s, hipStream_t st) {
 // bucket exceeds kBktCap.
 void msd_finish(cpma* s, const uint64_t* src, uint64_t k, const MsdPlan& p, hipStream_t st) {
   const uint32_t* koff = s->koff.as<uint32_t>();
-  hipLaunchKernelGGL(k_msd_scatter, dim3(p.nt), dim3(kMsdThreads), 0, st, src, s->kb0.as<uint32_t>(), (uint32_t)k,
-                     p.r, p.nd, koff);
+  hipLaunchKernelGGL(p.mid ? k_msd_scatter<kMidItems> : k_msd_scatter<kMsdItems>, dim3(p.nt), dim3(kMsdThreads), 0,
+                     st, src, s->kb0.as<uint32_t>(), (uint32_t)k, p.r, p.nd, koff);
   HIPCHK(hipGetLastError());
   // the per-tile counts are consumed: their buffer takes the buckets' first
-  // occurrence counts and those counts' scan (nc >= 32 nd)
+  // occurrence counts and those counts' scan (see msd_buffers)
   uint32_t* ucnt = s->cnt.as<uint32_t>();
   uint32_t* uoff = ucnt + p.nd + 1;
-  hipLaunchKernelGGL(k_bucket_sort, dim3(p.nd), dim3(kBktThreads), 0, st, (const uint32_t*)s->kb0.as<uint32_t>(),
+  hipLaunchKernelGGL(p.mid ? k_bucket_sort<kMidBktThreads> : k_bucket_sort<kBktThreads>, dim3(p.nd),
+                     dim3(p.mid ? kMidBktThreads : kBktThreads), 0, st, (const uint32_t*)s->kb0.as<uint32_t>(),
                      s->kb1.as<uint64_t>(), koff, p.nt, p.r, ucnt, &s->dctr->error);
   HIPCHK(hipGetLastError());
   scan<uint32_t>(s, uoff, p.nd, st, LoadFn<uint32_t>{ucnt});
@@ -521,15 +535,21 @@ const uint64_t* prepare_batch(cpma* s, const uint64_t* keys, uint64_t k, cpma_me
   // are scanned before the one read-back
   const bool msd_size = k >= kMsdMinKeys && k <= kMsdMaxKeys;
   MsdPlan guess;
-  const bool fused = msd_size && s->msd_bits > 0 && msd_plan(k, s->msd_bits, &guess);
+  // batches of 4097 to 2^18 keys: likewise with the bit length of the last of them;
+  // without it, or when the counts do not hold, the radix passes.  After a skewed
+  // batch the next 16 do not try (a try that fails costs its count, about 15 us)
+  const bool mid_size = k >= kMidMinKeys && k <= kMidMaxKeys;
+  const bool fused = (msd_size && s->msd_bits > 0 && msd_plan(k, s->msd_bits, &guess)) ||
+                     (mid_size && s->mid_skip == 0 && s->mid_bits > 0 && mid_plan(k, s->mid_bits, &guess));
   // the validation counts the first LSD digit when the split is out of reach
   // (batch size, or the last large batch's bit length); hist0 says whether
   // those counts are still in s->cnt
-  bool hist0 = !msd_size || (s->msd_bits > 0 && !fused);
+  bool hist0 = !fused && (!msd_size || s->msd_bits > 0);
   if (fused) {
     msd_buffers(s, k, guess);
-    hipLaunchKernelGGL(k_validate_msd, dim3(guess.nt), dim3(kMsdThreads), 0, st, src, (uint32_t)k, guess.r, guess.nd,
-                       s->dinfo, s->cnt.as<uint32_t>());
+    hipLaunchKernelGGL(guess.mid ? k_validate_msd<kMidItems> : k_validate_msd<kMsdItems>, dim3(guess.nt),
+                       dim3(kMsdThreads), 0, st, src, (uint32_t)k, guess.r, guess.nd, s->dinfo,
+                       s->cnt.as<uint32_t>());
     HIPCHK(hipGetLastError());
     msd_offsets(s, guess, st, true);
   } else if (!hist0) {
@@ -557,6 +577,20 @@ const uint64_t* prepare_batch(cpma* s, const uint64_t* keys, uint64_t k, cpma_me
     int passes = (bits + 7) / 8;
     ensure(s->kb0, k * sizeof(uint64_t));
     ensure(s->kb1, k * sizeof(uint64_t));
+    if (mid_size) {
+      const bool fits = fused && bits <= s->mid_bits;
+      const bool counted = fits && s->hinfo->max_bucket <= kMidBktCap;
+      if (fits && !counted)
+        s->mid_skip = 16;
+      else if (s->mid_skip)
+        s->mid_skip--;
+      s->mid_bits = bits;
+      if (counted) {
+        msd_finish(s, src, k, guess, st);
+        phase_end(s, pm, st, 40ull * k);  // as for the large split below
+        return s->kdedup.as<uint64_t>();
+      }
+    }
     if (msd_size) {
       // the validation's counts hold if this batch has no more bits than the
       // one they were counted for (fewer only leaves high buckets empty)

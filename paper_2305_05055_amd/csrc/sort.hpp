@@ -406,6 +406,16 @@ constexpr uint64_t kBktTarget = kBktCap * 4 / 5;          // average bucket the 
 constexpr int kMsdMinBits = 8;
 constexpr uint64_t kMsdMinKeys = 1ull << 19;              // smaller batches take the LSD passes
 constexpr uint64_t kMsdMaxKeys = kBktTarget << kMsdMaxBits;
+// Batches of 4097 to 2^18 keys split too, into 256 buckets of at most 1024 keys on
+// average, in tiles of 4096 keys and sorted by blocks of 256 threads: 1e5 keys 34 us
+// in eight launches and no wait for a copy, the radix passes and the removal of
+// repeats 58 in twelve.  Above 2^18 (up to the large split's size) the passes stay.
+constexpr int kMidItems = 4;
+constexpr uint32_t kMidTile = kMsdThreads * kMidItems;
+constexpr uint64_t kMidMinKeys = 4097, kMidMaxKeys = 1ull << 18;
+constexpr int kMidBits = 8;
+constexpr int kMidBktThreads = 256;
+constexpr uint32_t kMidBktCap = kMidBktThreads * kBktRounds;  // 3072
 
 __device__ __forceinline__ uint32_t msd_bucket(uint64_t x, int r, uint32_t nd) {
   // clamped so that a key outside the announced bit length cannot index past
@@ -439,23 +449,24 @@ __global__ void __launch_bounds__(kMsdThreads) k_msd_hist(const uint64_t* __rest
 // wave (or of wave 0 in the next round), so lane 63 parks its keys in LDS and
 // compares them after the barrier, when the keys' registers are free; only
 // the tile's last item reads the next tile's first key.
+template <int kItems>
 __global__ void __launch_bounds__(kMsdThreads) __attribute__((amdgpu_waves_per_eu(8, 8)))
 k_validate_msd(const uint64_t* __restrict__ keys, uint32_t n, int r, uint32_t nd, BatchInfo* __restrict__ info,
                uint32_t* __restrict__ counts) {
   constexpr int kW = kMsdThreads / kWave;
   __shared__ uint32_t h[kMsdMaxBuckets];
-  __shared__ uint64_t first[kMsdItems][kW];
-  __shared__ uint64_t last[kMsdItems][kW];
+  __shared__ uint64_t first[kItems][kW];
+  __shared__ uint64_t last[kItems][kW];
   __shared__ uint64_t red[kW];
   __shared__ uint32_t fl[kW];
   const int tid = threadIdx.x, lane = lane_id(), wid = tid / kWave;
   for (uint32_t d = tid; d < kMsdMaxBuckets; d += kMsdThreads) h[d] = 0;
-  const uint32_t base = blockIdx.x * kMsdTile;
+  const uint32_t base = blockIdx.x * (uint32_t)(kItems * kMsdThreads);
   __syncthreads();  // counters cleared
   uint64_t orv = 0;
   uint32_t res = 0, uns = 0;
-  // two halves of kMsdItems / 2 loads in flight, so two blocks fit a CU
-  constexpr int kHalf = kMsdItems / 2;
+  // two halves of kItems / 2 loads in flight, so two blocks fit a CU
+  constexpr int kHalf = kItems / 2;
 #pragma unroll
   for (int hf = 0; hf < 2; hf++) {
     uint64_t x[kHalf];
@@ -481,11 +492,11 @@ k_validate_msd(const uint64_t* __restrict__ keys, uint32_t n, int r, uint32_t nd
   }
   __syncthreads();
   if (lane == kWave - 1) {
-    const uint64_t after = base + kMsdTile < n ? keys[base + kMsdTile] : 0;  // the next tile's first key
+    const uint64_t after = base + (uint32_t)(kItems * kMsdThreads) < n ? keys[base + (uint32_t)(kItems * kMsdThreads)] : 0;  // the next tile's first key
 #pragma unroll
-    for (int j = 0; j < kMsdItems; j++) {
+    for (int j = 0; j < kItems; j++) {
       const uint32_t i = base + j * kMsdThreads + tid;
-      const uint64_t nx = wid + 1 < kW ? first[j][wid + 1] : (j + 1 < kMsdItems ? first[j + 1][0] : after);
+      const uint64_t nx = wid + 1 < kW ? first[j][wid + 1] : (j + 1 < kItems ? first[j + 1][0] : after);
       if (i + 1 < n && nx < last[j][wid]) uns = 1;
     }
   }
@@ -546,10 +557,11 @@ __global__ void __launch_bounds__(kMsdThreads) k_msd_max(const uint32_t* __restr
 
 // The bucket's low parts only go out: a key is its bucket number above its
 // low r bits, and the bucket sort restores it.
+template <int kItems>
 __global__ void __launch_bounds__(kMsdThreads) k_msd_scatter(const uint64_t* __restrict__ in,
                                                              uint32_t* __restrict__ out, uint32_t n, int r,
                                                              uint32_t nd, const uint32_t* __restrict__ koff) {
-  __shared__ uint64_t tile[kMsdTile];
+  __shared__ uint64_t tile[(uint32_t)(kItems * kMsdThreads)];
   __shared__ uint32_t h[kMsdMaxBuckets];   // counts, then the tile's bucket offsets
   __shared__ uint32_t gb[kMsdMaxBuckets];  // the tile's output position per bucket
   __shared__ uint32_t wsum[kMsdThreads / kWave];
@@ -557,16 +569,16 @@ __global__ void __launch_bounds__(kMsdThreads) k_msd_scatter(const uint64_t* __r
   for (uint32_t d = tid; d < kMsdMaxBuckets; d += kMsdThreads) h[d] = 0;
   for (uint32_t d = tid; d < nd; d += kMsdThreads) gb[d] = koff[(uint64_t)d * gridDim.x + blockIdx.x];
   __syncthreads();
-  const uint32_t base = blockIdx.x * kMsdTile;
-  uint64_t x[kMsdItems];
-  uint32_t rk[kMsdItems];
+  const uint32_t base = blockIdx.x * (uint32_t)(kItems * kMsdThreads);
+  uint64_t x[kItems];
+  uint32_t rk[kItems];
 #pragma unroll
-  for (int j = 0; j < kMsdItems; j++) {
+  for (int j = 0; j < kItems; j++) {
     const uint32_t i = base + j * kMsdThreads + tid;
     x[j] = i < n ? in[i] : 0;
   }
 #pragma unroll
-  for (int j = 0; j < kMsdItems; j++)
+  for (int j = 0; j < kItems; j++)
     if (base + j * kMsdThreads + tid < n) rk[j] = atomicAdd(&h[msd_bucket(x[j], r, nd)], 1u);
   __syncthreads();
   // exclusive scan of the 2048 counters, kPer consecutive ones per thread
@@ -592,10 +604,10 @@ __global__ void __launch_bounds__(kMsdThreads) k_msd_scatter(const uint64_t* __r
   }
   __syncthreads();
 #pragma unroll
-  for (int j = 0; j < kMsdItems; j++)
+  for (int j = 0; j < kItems; j++)
     if (base + j * kMsdThreads + tid < n) tile[h[msd_bucket(x[j], r, nd)] + rk[j]] = x[j];
   __syncthreads();
-  const uint32_t m = min(kMsdTile, n - base);
+  const uint32_t m = min((uint32_t)(kItems * kMsdThreads), n - base);
   const uint32_t lowmask = r >= 32 ? 0xffffffffu : ((1u << r) - 1u);
   for (uint32_t i = tid; i < m; i += kMsdThreads) {
     const uint64_t y = tile[i];
@@ -628,20 +640,23 @@ __device__ __forceinline__ void match_bit(uint32_t y, uint32_t& p0, uint32_t& p1
 // rounds).  The host launches this only when every bucket holds at most
 // kBktCap keys; a larger one is left unsorted and raises *err (the update's
 // device-error counter, which the host checks before it reports success).
-__global__ void __launch_bounds__(kBktThreads) __attribute__((amdgpu_waves_per_eu(8, 8)))
+template <int kThreads>
+__global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(8, 8)))
 k_bucket_sort(const uint32_t* __restrict__ in,
                                                              uint64_t* __restrict__ out,
                                                              const uint32_t* __restrict__ koff, uint32_t ntiles,
                                                              int r, uint32_t* __restrict__ ucnt,
                                                              unsigned int* __restrict__ err) {
-  __shared__ uint32_t buf[kBktCap];
-  __shared__ uint32_t cnt[kBktWaves][256];  // the first pass uses row 0 for the whole block
+  constexpr int kW = kThreads / kWave;
+  constexpr uint32_t kCap = kThreads * kBktRounds;
+  __shared__ uint32_t buf[kCap];
+  __shared__ uint32_t cnt[kW][256];  // the first pass uses row 0 for the whole block
   __shared__ uint32_t wsum[256 / kWave];
-  __shared__ uint32_t wtot[kBktWaves];
+  __shared__ uint32_t wtot[kW];
   const uint32_t bkt = blockIdx.x;
   const uint32_t beg = koff[(uint64_t)bkt * ntiles];
   const uint32_t n = koff[(uint64_t)(bkt + 1) * ntiles] - beg;
-  if (n > kBktCap) {
+  if (n > kCap) {
     if (threadIdx.x == 0) {
       ucnt[bkt] = 0u;
       atomicOr(err, 1u);
@@ -649,28 +664,32 @@ k_bucket_sort(const uint32_t* __restrict__ in,
     return;
   }
   const int tid = threadIdx.x, lane = lane_id(), wid = tid / kWave;
-  const uint32_t wb = (uint32_t)wid * (kBktRounds * kWave);
+  // the small block's buckets fill a third of it: its waves share the rounds evenly
+  const uint32_t rounds = kThreads == kBktThreads ? (uint32_t)kBktRounds : (n + kThreads - 1) / kThreads;
+  const uint32_t wb = (uint32_t)wid * (rounds * kWave);
+  auto mine = [&](int j) { return (uint32_t)j < rounds && wb + (uint32_t)j * kWave + lane < n; };
   uint32_t x[kBktRounds];
 #pragma unroll
   for (int j = 0; j < kBktRounds; j++) {
     const uint32_t i = wb + (uint32_t)j * kWave + lane;
-    x[j] = i < n ? in[beg + i] : 0u;
+    x[j] = mine(j) ? in[beg + i] : 0u;
   }
   for (int sh = 0; sh < r; sh += 8) {
     const bool first = sh == 0;
 #pragma unroll
-    for (int q = 0; q < kBktWaves * 256 / kBktThreads; q++) (&cnt[0][0])[q * kBktThreads + tid] = 0;
+    for (int q = 0; q < kW * 256 / kThreads; q++) (&cnt[0][0])[q * kThreads + tid] = 0;
     __syncthreads();
     uint32_t rk[kBktRounds];
     if (wb < n) {  // waves past the bucket's end rank nothing
       if (first) {
 #pragma unroll
         for (int j = 0; j < kBktRounds; j++)
-          if (wb + (uint32_t)j * kWave + lane < n) rk[j] = atomicAdd(&cnt[0][x[j] & 255u], 1u);
+          if (mine(j)) rk[j] = atomicAdd(&cnt[0][x[j] & 255u], 1u);
       } else {
 #pragma unroll
         for (int j = 0; j < kBktRounds; j++) {
-          const bool valid = wb + (uint32_t)j * kWave + lane < n;
+          if (kThreads != kBktThreads && (uint32_t)j >= rounds) break;
+          const bool valid = mine(j);
           const uint32_t y = x[j] >> sh;
           const uint64_t vm = __ballot(valid);
           uint32_t p0 = (uint32_t)vm, p1 = (uint32_t)(vm >> 32);
@@ -697,7 +716,7 @@ k_bucket_sort(const uint32_t* __restrict__ in,
         tot = cnt[0][tid];
       } else {
 #pragma unroll
-        for (int w = 0; w < kBktWaves; w++) tot += cnt[w][tid];
+        for (int w = 0; w < kW; w++) tot += cnt[w][tid];
       }
       incl = wave_incl_scan(tot);
       if (lane == kWave - 1) wsum[wid] = incl;
@@ -712,7 +731,7 @@ k_bucket_sort(const uint32_t* __restrict__ in,
         cnt[0][tid] = run;
       } else {
 #pragma unroll
-        for (int w = 0; w < kBktWaves; w++) {
+        for (int w = 0; w < kW; w++) {
           const uint32_t c = cnt[w][tid];
           cnt[w][tid] = run;  // wave w's first slot for digit tid
           run += c;
@@ -724,13 +743,13 @@ k_bucket_sort(const uint32_t* __restrict__ in,
       const int row = first ? 0 : wid;
 #pragma unroll
       for (int j = 0; j < kBktRounds; j++)
-        if (wb + (uint32_t)j * kWave + lane < n) buf[cnt[row][(x[j] >> sh) & 255u] + rk[j]] = x[j];
+        if (mine(j)) buf[cnt[row][(x[j] >> sh) & 255u] + rk[j]] = x[j];
     }
     __syncthreads();
 #pragma unroll
     for (int j = 0; j < kBktRounds; j++) {
       const uint32_t i = wb + (uint32_t)j * kWave + lane;
-      if (i < n) x[j] = buf[i];
+      if (mine(j)) x[j] = buf[i];
     }
     __syncthreads();  // the next pass clears the counters the scatter read
   }
@@ -748,7 +767,7 @@ k_bucket_sort(const uint32_t* __restrict__ in,
   }
   auto first_occ = [&](int j) {
     const uint32_t i = wb + (uint32_t)j * kWave + lane;
-    return i < n && (i == 0 || buf[i - 1] != x[j]);
+    return mine(j) && (i == 0 || buf[i - 1] != x[j]);
   };
   uint32_t tw = 0;
 #pragma unroll
@@ -757,7 +776,7 @@ k_bucket_sort(const uint32_t* __restrict__ in,
   __syncthreads();
   uint32_t woff = 0, total = 0;
 #pragma unroll
-  for (int w = 0; w < kBktWaves; w++) {
+  for (int w = 0; w < kW; w++) {
     const uint32_t t = wtot[w];
     if (w < wid) woff += t;
     total += t;
