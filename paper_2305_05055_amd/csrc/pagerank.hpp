@@ -17,6 +17,7 @@
 // 16 bytes of HBM per edge and iteration, all in order.
 #pragma once
 #include "fgraph.hpp"
+#include "pg_segments.hpp"
 #include "update.hpp"
 
 namespace cpma_dev {
@@ -161,7 +162,7 @@ __global__ void __launch_bounds__(kPgThreads) k_pg_scatter(FgArgs g, PgArgs a) {
 // Gather segments of every part, and each segment's part.
 __global__ void k_pg_segments(PgArgs a) {
   for (uint32_t p = blockIdx.x * blockDim.x + threadIdx.x; p < a.P; p += gridDim.x * blockDim.x)
-    a.nseg[p] = (a.pos[(uint64_t)(p + 1) * a.B] - a.pos[(uint64_t)p * a.B] + a.seg - 1) / a.seg;
+    a.nseg[p] = pg_segment_count(a.pos[(uint64_t)p * a.B], a.pos[(uint64_t)(p + 1) * a.B], a.seg);
 }
 __global__ void k_pg_segparts(PgArgs a) {
   for (uint32_t p = blockIdx.x * blockDim.x + threadIdx.x; p < a.P; p += gridDim.x * blockDim.x)
@@ -176,7 +177,8 @@ __global__ void __launch_bounds__(kPgThreads) k_pg_gather(PgArgs a) {
   for (uint32_t s = blockIdx.x; s < nseg; s += gridDim.x) {
     const uint32_t p = a.segpart[s];
     const uint32_t b0 = a.pos[(uint64_t)p * a.B], b1 = a.pos[(uint64_t)(p + 1) * a.B];
-    const uint32_t e0 = b0 + (s - a.segoff[p]) * a.seg, e1 = min(b1, e0 + a.seg);
+    const PgSegment sg = pg_segment(b0, b1, a.seg, s - a.segoff[p]);
+    const uint32_t e0 = sg.e0, e1 = sg.e1;
     const uint32_t v0 = p << a.pbits;
     __syncthreads();
     for (uint32_t i = threadIdx.x; i < part && v0 + i < a.nv; i += kPgThreads) c[i] = a.contrib[v0 + i];
