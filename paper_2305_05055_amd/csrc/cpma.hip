@@ -1543,9 +1543,11 @@ void reserve_batch(cpma* s, uint64_t kbound, bool insert) {
   const uint64_t arena_cap =
       insert ? std::min<uint64_t>(L, kbound) * (uint64_t)(s->S + 16) + (s->kv() ? 32 : 16) * kbound + 256 : 256;
   ensure(s->arena, arena_cap, 1.0);
-  // heavy-merge staging: only slices of more than kHeavyLds keys stage, each at
-  // most its own keys plus one leaf's keys
-  uint64_t stage_cap = insert ? kbound + (kbound / kHeavyLds + 1) * (uint64_t)s->S + 64 : 64;
+  // heavy-merge staging: a slice stages its own keys and its leaf's (at most S - 7).
+  // Up to kWaveMaxS only slices of more than kHeavyLds keys do (shorter ones merge
+  // in LDS), above it every heavy slice (the launch has no LDS for merged keys)
+  const uint64_t longest_unstaged = s->S <= kWaveMaxS ? kHeavyLds : kLaneHeavy;
+  uint64_t stage_cap = insert ? kbound + (kbound / (longest_unstaged + 1) + 1) * (uint64_t)(s->S - 7) + 64 : 64;
   if (s->kv()) {
     // key-value merges stage a merged leaf of more than KvLayout::cap keys:
     // its new keys (more than its old ones) and its old ones
