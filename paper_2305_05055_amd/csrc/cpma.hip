@@ -135,6 +135,7 @@ struct cpma {
   MergeArgs giant_args{};
   uint64_t giant_k = 0;
   uint32_t giant_n = 0;  // giant leaves of the current update, in the arena until a redistribution
+  std::mutex query_m;  // the scratch of queries (see guarded_query)
   cpma_config cfg{};
   uint32_t S = 1024;
   uint64_t L = 0, n = 0;
@@ -1835,6 +1836,17 @@ cpma_status guarded(cpma* s, F&& f) {
   }
 }
 
+// A query call that uses the handle's scratch or pinned memory.  Queries may come
+// from several host threads on one stream: each holds the scratch from its first
+// write to its last enqueue, which protects device buffers by stream order, and to
+// the copy out where results return through pinned memory, which the GPU reads and
+// writes when the work runs.
+template <typename F>
+cpma_status guarded_query(cpma* s, F&& f) {
+  std::lock_guard<std::mutex> lk(s->query_m);
+  return guarded(s, f);
+}
+
 }  // namespace
 
 // =============================================================================
@@ -2333,7 +2345,7 @@ static cpma_status range_map_impl(const cpma* cs, const uint64_t* lo, const uint
   if (q == 0) return CPMA_OK;
   if (!lo || !hi || !sum || !count) return CPMA_ERR_INVALID;
   hipStream_t st = (hipStream_t)stream;
-  return guarded(s, [&] {
+  return guarded_query(s, [&] {
     HIPCHK(hipSetDevice(s->device));
     QueryArgs a = query_args(s);
     a.q = q;
@@ -2427,6 +2439,8 @@ cpma_status cpma_get(const cpma* cs, const uint64_t* keys, uint64_t q, cpma_mem 
   if (q == 0) return CPMA_OK;
   if (!keys || !values || !found) return CPMA_ERR_INVALID;
   hipStream_t st = (hipStream_t)stream;
+  std::unique_lock<std::mutex> lk(s->query_m, std::defer_lock);
+  if (mem == CPMA_MEM_HOST || s->stats_on) lk.lock();  // else no scratch
   return guarded(s, [&] {
     HIPCHK(hipSetDevice(s->device));
     QueryArgs a = query_args(s);
@@ -2531,6 +2545,8 @@ cpma_status cpma_contains(const cpma* cs, const uint64_t* keys, uint64_t q, cpma
   if (q == 0) return CPMA_OK;
   if (!keys || !out) return CPMA_ERR_INVALID;
   hipStream_t st = (hipStream_t)stream;
+  std::unique_lock<std::mutex> lk(s->query_m, std::defer_lock);
+  if (mem == CPMA_MEM_HOST || s->stats_on) lk.lock();  // else no scratch
   return guarded(s, [&] {
     HIPCHK(hipSetDevice(s->device));
     QueryArgs a = query_args(s);
@@ -2654,7 +2670,7 @@ cpma_status cpma_fgraph_bfs(const cpma* cs, uint32_t nv, uint32_t source, int sy
   if (s->S > kWaveMaxS || s->cfg.uncompressed) return CPMA_ERR_INVALID;
   if (s->broken) return CPMA_ERR_DEVICE;
   hipStream_t st = (hipStream_t)stream;
-  return guarded(s, [&] {
+  return guarded_query(s, [&] {
     HIPCHK(hipSetDevice(s->device));
     uint32_t* lv = level;
     if (mem == CPMA_MEM_HOST) {
@@ -2675,7 +2691,7 @@ cpma_status cpma_fgraph_offsets(const cpma* cs, uint32_t nv, cpma_mem mem, uint6
   if (s->S > kWaveMaxS || s->cfg.uncompressed) return CPMA_ERR_INVALID;
   if (s->broken) return CPMA_ERR_DEVICE;
   hipStream_t st = (hipStream_t)stream;
-  return guarded(s, [&] {
+  return guarded_query(s, [&] {
     HIPCHK(hipSetDevice(s->device));
     uint64_t* dof = off;
     if (mem == CPMA_MEM_HOST) {
@@ -2701,7 +2717,7 @@ cpma_status cpma_fgraph_cc(const cpma* cs, uint32_t nv, cpma_mem mem, uint32_t* 
   if (s->S > kWaveMaxS || s->cfg.uncompressed) return CPMA_ERR_INVALID;
   if (s->broken) return CPMA_ERR_DEVICE;
   hipStream_t st = (hipStream_t)stream;
-  return guarded(s, [&] {
+  return guarded_query(s, [&] {
     HIPCHK(hipSetDevice(s->device));
     uint32_t* lab = label;
     if (mem == CPMA_MEM_HOST) {
@@ -2735,7 +2751,7 @@ cpma_status cpma_fgraph_bc(const cpma* cs, uint32_t nv, uint32_t source, cpma_me
   if (s->S > kWaveMaxS || s->cfg.uncompressed) return CPMA_ERR_INVALID;
   if (s->broken) return CPMA_ERR_DEVICE;
   hipStream_t st = (hipStream_t)stream;
-  return guarded(s, [&] {
+  return guarded_query(s, [&] {
     HIPCHK(hipSetDevice(s->device));
     ensure(s->fg_level, (uint64_t)nv * 4);
     uint32_t* lv = s->fg_level.as<uint32_t>();
@@ -2872,7 +2888,7 @@ cpma_status cpma_fgraph_pagerank(const cpma* cs, uint32_t nv, int iters, double 
   if (s->S > kWaveMaxS || s->cfg.uncompressed) return CPMA_ERR_INVALID;
   if (s->broken) return CPMA_ERR_DEVICE;
   hipStream_t st = (hipStream_t)stream;
-  return guarded(s, [&] {
+  return guarded_query(s, [&] {
     HIPCHK(hipSetDevice(s->device));
     float* pv = p;
     if (mem == CPMA_MEM_HOST) {
