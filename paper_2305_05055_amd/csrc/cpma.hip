@@ -16,6 +16,7 @@
 #include <vector>
 
 #include "cpma.h"
+#include "launch_rules.hpp"
 #include "query.hpp"
 #include "sort.hpp"
 #include "update.hpp"
@@ -127,6 +128,8 @@ struct cpma {
   uint32_t rm_blocks[2] = {2048, 2048};  // resident blocks of k_rm_interior<false>, <true>
   int mid_bits = 0;  // bit length of the last unsorted batch of 4097 to 2^18 keys (0: none yet)
   int mid_skip = 0;  // such batches to sort with radix passes at once, after a skewed one
+  double wide_share = 1.0;  // wide segments among the last classified batch's
+  bool classified = false;  // the current update's segments were classified
   int msd_bits = 0;  // bit length of the last unsorted batch of the MSD split's size (0: none yet)
   // a small batch's merge totals, left for the single-block path check to fold
   const unsigned long long* fin_parts = nullptr;
@@ -1306,6 +1309,8 @@ uint64_t resize(cpma* s, uint64_t total, uint32_t viol, hipStream_t st) {
 // or removed, and its algorithmic bytes for the statistics.
 uint64_t take_merge(cpma* s, const Counters& c, int merged) {
   if (c.reserved) throw Fail{CPMA_ERR_RESERVED_KEY};  // small batch: nothing was merged
+  if (s->classified && c.T) s->wide_share = (double)c.nwide / (double)c.T;
+  s->classified = false;
   if (s->stats_on) {
     if ((s->stats_mask >> CPMA_PHASE_MERGE) & 1u) s->stats[CPMA_PHASE_MERGE].alg_bytes += c.alg_bytes;
     if ((s->stats_mask >> CPMA_PHASE_HEAVY) & 1u) s->stats[CPMA_PHASE_HEAVY].alg_bytes += c.alg_bytes_h;
@@ -1510,9 +1515,7 @@ MergeGrids merge_grids(const cpma* s, uint64_t kbound) {
   // dispatcher hands out the rest as waves finish, which evens out segments of
   // unequal work (4-5 % faster at 1e7 into 1e8 than 40 waves per CU)
   m.wgrid = std::max(1u, (uint32_t)std::min<uint64_t>(segs, (uint64_t)s->num_cus * 320));
-  // the wide list is empty for most batches, and 320 idle waves per CU cost 20 us to
-  // dispatch (32: 8 us, the last leaf's slice included); a full list still has two waves for every resident one
-  m.wide_grid = std::min(m.wgrid, (uint32_t)s->num_cus * 32);
+  m.wide_grid = wide_waves(segs, s->wide_share, (uint32_t)s->num_cus, m.wgrid);
   m.lwaves = std::max(1u, m.lgrid) * (256 / kWave);
   // heavy merge of spilled slices: at most kbound / (kWaveSlice + 1) of them,
   // more than the five blocks that fit a CU, which evens out slices of unequal
@@ -1611,6 +1614,7 @@ bool finish_in_path_check(const cpma* s, uint64_t k) {
 uint64_t apply_batch(cpma* s, const uint64_t* B, uint64_t kbound, bool insert, hipStream_t st, bool small = false,
                      bool rebuild_all = false) {
   const bool segments_ready = small;
+  s->classified = false;
   s->fin_parts = nullptr;
   reserve_batch(s, kbound, insert);
   PhaseMark pl = phase_begin(s, CPMA_PHASE_LOCATE, st);
@@ -1652,6 +1656,7 @@ uint64_t apply_batch(cpma* s, const uint64_t* B, uint64_t kbound, bool insert, h
                        s->seg_desc.as<uint4>(), (const uint32_t*)s->seg_begin.as<uint32_t>(), kWaveSlice,
                        insert ? 1 : 0, s->wide.as<uint32_t>(), s->spill.as<uint32_t>(), s->dctr, nseg);
     HIPCHK(hipGetLastError());
+    s->classified = true;
   }
   phase_end(s, pl, st, 24ull * kbound);
   MergeArgs a = merge_args(s, B, insert);
