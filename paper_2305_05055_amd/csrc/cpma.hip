@@ -126,8 +126,7 @@ struct cpma {
   int device = 0;
   int num_cus = 256;
   uint32_t rm_blocks[2] = {2048, 2048};  // resident blocks of k_rm_interior<false>, <true>
-  int mid_bits = 0;  // bit length of the last unsorted batch of 4097 to 2^18 keys (0: none yet)
-  int mid_skip = 0;  // such batches to sort with radix passes at once, after a skewed one
+  SplitGuess mid;    // for unsorted batches of 4097 to 2^18 keys
   double wide_share = 1.0;  // wide segments among the last classified batch's
   bool classified = false;  // the current update's segments were classified
   int msd_bits = 0;  // bit length of the last unsorted batch of the MSD split's size (0: none yet)
@@ -540,11 +539,10 @@ const uint64_t* prepare_batch(cpma* s, const uint64_t* keys, uint64_t k, cpma_me
   const bool msd_size = k >= kMsdMinKeys && k <= kMsdMaxKeys;
   MsdPlan guess;
   // batches of 4097 to 2^18 keys: likewise with the bit length of the last of them;
-  // without it, or when the counts do not hold, the radix passes.  After a skewed
-  // batch the next 16 do not try (a try that fails costs its count, about 15 us)
+  // without it, or when the counts do not hold, the radix passes
   const bool mid_size = k >= kMidMinKeys && k <= kMidMaxKeys;
   const bool fused = (msd_size && s->msd_bits > 0 && msd_plan(k, s->msd_bits, &guess)) ||
-                     (mid_size && s->mid_skip == 0 && s->mid_bits > 0 && mid_plan(k, s->mid_bits, &guess));
+                     (mid_size && s->mid.tries() && mid_plan(k, s->mid.bits, &guess));
   // the validation counts the first LSD digit when the split is out of reach
   // (batch size, or the last large batch's bit length); hist0 says whether
   // those counts are still in s->cnt
@@ -582,13 +580,8 @@ const uint64_t* prepare_batch(cpma* s, const uint64_t* keys, uint64_t k, cpma_me
     ensure(s->kb0, k * sizeof(uint64_t));
     ensure(s->kb1, k * sizeof(uint64_t));
     if (mid_size) {
-      const bool fits = fused && bits <= s->mid_bits;
-      const bool counted = fits && s->hinfo->max_bucket <= kMidBktCap;
-      if (fits && !counted)
-        s->mid_skip = 16;
-      else if (s->mid_skip)
-        s->mid_skip--;
-      s->mid_bits = bits;
+      const bool counted = fused && bits <= s->mid.bits && s->hinfo->max_bucket <= kMidBktCap;
+      s->mid.took(bits, fused, counted);
       if (counted) {
         msd_finish(s, src, k, guess, st);
         phase_end(s, pm, st, 40ull * k);  // as for the large split below

@@ -28,7 +28,46 @@ static void wide_merge() {
   EXPECT(wide_waves(100, 0.0, cus, 100) == 100);
 }
 
+// Batches of the given bit lengths, repeated: how many of the last 68 tried the split
+// and how many were split.  Buckets counted for more bits than a batch has overflow.
+static void run(const int* bits, int n, bool skewed, int* tried, int* split) {
+  SplitGuess g;
+  *tried = *split = 0;
+  for (int i = 0; i < 200; i++) {
+    const int b = bits[i % n];
+    const bool t = g.tries(), ok = t && !skewed && b == g.bits;
+    g.took(b, t, ok);
+    if (i >= 132) {
+      *tried += t;
+      *split += ok;
+    }
+  }
+}
+
+static void small_split() {
+  int t, s;
+  const int same[] = {40}, alternating[] = {40, 34};
+  run(same, 1, false, &t, &s);
+  EXPECT(t == 68 && s == 68);
+  run(same, 1, true, &t, &s);
+  EXPECT(t == 4);  // a skewed stream: one try in 17
+  run(alternating, 2, false, &t, &s);
+  EXPECT(t <= 4);  // every count would be lost
+  // a single change of length, shorter or longer, costs one count and no pause
+  for (int b : {38, 42}) {
+    SplitGuess g;
+    g.took(40, false, false);
+    EXPECT(g.tries());
+    g.took(40, true, true);
+    g.took(b, true, false);
+    EXPECT(g.tries() && g.bits == b);
+    g.took(b, true, true);
+    EXPECT(g.tries());
+  }
+}
+
 int main() {
   wide_merge();
+  small_split();
   return failures != 0;
 }
