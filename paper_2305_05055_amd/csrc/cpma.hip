@@ -125,7 +125,7 @@ int tree_height(uint64_t L) {
 struct cpma {
   int device = 0;
   int num_cus = 256;
-  uint32_t rm_blocks[2] = {2048, 2048};  // resident blocks of k_rm_interior<false>, <true>
+  uint32_t rm_blocks[3] = {2048, 2048, 2048};  // resident blocks of k_rm_interior<true>, <false> and k_rm_words
   SplitGuess mid;    // for unsorted batches of 4097 to 2^18 keys
   double wide_share = 1.0;  // wide segments among the last classified batch's
   bool classified = false;  // the current update's segments were classified
@@ -1924,11 +1924,11 @@ static cpma_status build_impl(const uint64_t* keys, const uint64_t* vals, uint64
     s->num_cus = prop.multiProcessorCount;
     // the interior range scan runs one generation of blocks: every block
     // resident at once, so no block starts after the others have finished
-    for (int plain = 0; plain < 2; plain++) {
+    decltype(&k_rm_words) scans[3] = {k_rm_interior<true>, k_rm_interior<false>, k_rm_words};
+    for (int i = 0; i < 3; i++) {
       int per = 0;
-      HIPCHK(plain ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, k_rm_interior<true>, 256, 0)
-                   : hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, k_rm_interior<false>, 256, 0));
-      s->rm_blocks[plain] = (uint32_t)std::max(1, per) * (uint32_t)s->num_cus;
+      HIPCHK(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, scans[i], 256, 0));
+      s->rm_blocks[i] = (uint32_t)std::max(1, per) * (uint32_t)s->num_cus;
     }
     ensure(s->ctr_buf, sizeof(Counters), 0.0);
     s->dctr = s->ctr_buf.as<Counters>();
@@ -2257,20 +2257,16 @@ cpma_status cpma_apply_updates(cpma* s, uint32_t nreq, const int32_t* kind, cons
   });
 }
 
-// The interior scan of range_map: the plain-CPMA instance for compressed sets
-// without values, the general one otherwise.
-static uint32_t interior_blocks(const cpma* s, const QueryArgs& a) {
-  return s->rm_blocks[a.zero_fill && !a.raw && !a.vals ? 1 : 0];
-}
+// The interior scan of range_map: compressed sets without values, keys of key-value
+// sets, 8-byte words.
+static int interior_kind(const QueryArgs& a) { return a.raw || a.vals ? 2 : (a.zero_fill ? 0 : 1); }
+static uint32_t interior_blocks(const cpma* s, const QueryArgs& a) { return s->rm_blocks[interior_kind(a)]; }
 static void launch_interior(const QueryArgs& a, uint32_t blocks, hipStream_t st, const uint64_t* voff,
                             const uint64_t* first, uint32_t chunk, unsigned long long* dsum, unsigned long long* dcount,
                             unsigned long long* alg, const LeafPrefix& lp) {
-  if (a.zero_fill && !a.raw && !a.vals)
-    hipLaunchKernelGGL(k_rm_interior<true>, dim3(blocks), dim3(256), 0, st, a, voff, first, chunk, dsum, dcount, alg,
-                       lp);
-  else
-    hipLaunchKernelGGL(k_rm_interior<false>, dim3(blocks), dim3(256), 0, st, a, voff, first, chunk, dsum, dcount, alg,
-                       lp);
+  const int kind = interior_kind(a);
+  hipLaunchKernelGGL(kind == 0 ? k_rm_interior<true> : (kind == 1 ? k_rm_interior<false> : k_rm_words), dim3(blocks),
+                     dim3(256), 0, st, a, voff, first, chunk, dsum, dcount, alg, lp);
   if (lp.ps && a.q > kPrefixInline)
     hipLaunchKernelGGL(k_rm_prefix_apply, dim3(grid_for(a.q, 256, 1024)), dim3(256), 0, st, a, voff, first, lp, blocks,
                        dsum, dcount);

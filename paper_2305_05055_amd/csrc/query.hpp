@@ -72,8 +72,8 @@ __global__ void __launch_bounds__(256) k_rm_ends(QueryArgs a, uint64_t* __restri
 // shifted by 7 times its place in its code, so a lane sums its own terminators'
 // offsets from zero, and the second lane adds the first one's total to each of
 // its keys.  The shift a code carries into the second half is 7 times the run
-// of continuation bytes just before it (at most 4: within a span of 2^32 a code
-// has at most 5 bytes).  Two lanes halve the chain of dependent rounds, which
+// of continuation bytes just before it (at most 4 within a span of 2^32, where a
+// code has at most 5 bytes, and 9 otherwise).  Two lanes halve the chain of dependent rounds, which
 // bounds a scan of few leaves, and give a set of 4e5 leaves twice as many waves.
 //
 // A round is loaded for the whole wave, four lanes to one lane's 64 bytes, and
@@ -87,7 +87,7 @@ __global__ void __launch_bounds__(256) k_rm_ends(QueryArgs a, uint64_t* __restri
 constexpr uint32_t kStageBytes = 64u * kWave;
 constexpr uint32_t kStepLeaves = kWave / 2;
 
-template <bool kZero, bool kWide>
+template <bool kZero, bool kSum64, typename KT>
 __device__ __forceinline__ LeafSum wave_code_sums(const QueryArgs& a, uint32_t leaf, uint64_t head, uint32_t used,
                                                   uint8_t* stage) {
   const uint32_t lane = (uint32_t)lane_id(), r = lane & 1u;
@@ -107,18 +107,25 @@ __device__ __forceinline__ LeafSum wave_code_sums(const QueryArgs& a, uint32_t l
     cnt[j] = w >> 16;
     src[j] = a.bytes + (uint64_t)lf * a.S + (w & 0xffffu) + 16u * ((ol & 3u) ^ ((o >> 2) & 3u));
   }
-  uint32_t before = 0;
-  if (r && own) before = *reinterpret_cast<const uint32_t*>(a.bytes + leaf * (uint64_t)a.S + start - 4);
+  // the run of continuation bytes just before this lane's part
+  uint32_t tail = 0;
+  if (r && own) {
+    const uint8_t* part = a.bytes + leaf * (uint64_t)a.S + start;
+    if constexpr (sizeof(KT) == 8) {
+      tail = tail_run<KT>(load16(part - 16));
+    } else {
+      const uint32_t ends = ~*reinterpret_cast<const uint32_t*>(part - 4) & 0x80808080u;
+      tail = ends ? (uint32_t)__clz((int)ends) >> 3 : 4u;
+    }
+  }
   uint4 nx[4];
 #pragma unroll
   for (uint32_t j = 0; j < 4; j++) {
     nx[j] = make_uint4(0, 0, 0, 0);
     if (cnt[j]) nx[j] = load16(src[j]);
   }
-  // leading ones of the four bytes' high bits, from the last byte backwards
-  const uint32_t ends = ~before & 0x80808080u;
-  uint32_t D = 0, cont = 0;
-  uint32_t sh = r ? 7u * (ends ? (uint32_t)__clz((int)ends) >> 3 : 4u) : 0u;
+  KT D = 0;
+  uint32_t cont = 0, sh = 7u * tail;
   uint64_t Sc = 0;
   uint4* const put = reinterpret_cast<uint4*>(stage) + lane;
   const uint4* const get = reinterpret_cast<const uint4*>(stage) + 4u * lane;
@@ -161,7 +168,7 @@ __device__ __forceinline__ LeafSum wave_code_sums(const QueryArgs& a, uint32_t l
             w = make_uint4(x[0], x[1], x[2], x[3]);
           }
         }
-        zf_chunk<kWide>(w, D, sh, Sc, cont);
+        zf_chunk<kSum64, KT>(w, D, sh, Sc, cont);
         w = ahead;
       }
     }
@@ -176,8 +183,12 @@ __device__ __forceinline__ LeafSum wave_code_sums(const QueryArgs& a, uint32_t l
     Sc -= (uint64_t)zeros * D;
   }
   constexpr int kXor1 = 1 | (0 << 2) | (3 << 4) | (2 << 6);  // DPP quad permutation: the pair's other lane
-  const uint32_t D0 = dpp32<kXor1>(D);
-  uint64_t s = Sc + (uint64_t)keys * (head + (r ? D0 : 0u));
+  KT D0;
+  if constexpr (sizeof(KT) == 8)
+    D0 = dpp64<kXor1>(D);
+  else
+    D0 = dpp32<kXor1>(D);
+  uint64_t s = Sc + (uint64_t)keys * (head + (r ? D0 : (KT)0));
   s += dpp64<kXor1>(s);
   keys += dpp32<kXor1>(keys);
   return r ? LeafSum{0, 0} : LeafSum{s, keys};
@@ -208,29 +219,40 @@ __device__ __forceinline__ LeafSum wave_word_sums(const QueryArgs& a, uint32_t l
   return out;
 }
 
-template <bool kPlain>
+// What an interior visit sums: the keys of leaves that are zero past `used` (every
+// compressed set without values), the keys of key-value leaves, or 8-byte words (an
+// uncompressed leaf's keys, a key-value leaf's values).  One kernel instance each:
+// together the decoders need more registers than four waves per SIMD leave.
+enum class Visit { kPlain, kCodes, kWords };
+
+template <Visit kVisit>
 __device__ __forceinline__ LeafSum wave_leaf_sums(const QueryArgs& a, uint32_t leaf, bool valid, uint8_t* stage,
                                                   uint32_t& visited) {
   const uint32_t r = (uint32_t)lane_id() & 1u;
   const uint32_t u = valid ? a.used[leaf] : 0u;
   if (!r) visited += u;
-  if constexpr (!kPlain) {
-    if (a.vals || a.raw) {
-      // 8-byte words: the values at the leaf's end, or the keys from its start
-      const uint32_t m = !valid ? 0u : (a.vals ? (a.fill[leaf] - u) / 8 : u / 8);
-      return wave_word_sums(a, leaf, a.vals ? a.S - 8u * m : 0u, m);
-    }
+  if constexpr (kVisit == Visit::kWords) {
+    // the values at the leaf's end, or the keys from its start
+    const uint32_t m = !valid ? 0u : (a.vals ? (a.fill[leaf] - u) / 8 : u / 8);
+    return wave_word_sums(a, leaf, a.vals ? a.S - 8u * m : 0u, m);
   }
+  constexpr bool kPlain = kVisit == Visit::kPlain;
   const uint64_t h = u ? a.head[leaf] : 0;
   const uint64_t span = u ? a.head[leaf + 1] - h : 0;
-  // three classes of leaves, each decoded at once: 32-bit sums of a chunk's
-  // offsets, 64-bit sums, and keys walked in 64 bits by one lane
-  LeafSum x = wave_code_sums<kPlain, false>(a, leaf, h, span < (1ull << 28) ? u : 0u, stage);
-  if (__ballot(span >= (1ull << 28))) {
-    const bool wide = span >= (1ull << 28) && span < (1ull << 32);
-    const LeafSum y = wave_code_sums<kPlain, true>(a, leaf, h, wide ? u : 0u, stage);
-    if (wide) x = y;
-    if (span >= (1ull << 32) && !r) x = leaf_sum_range(a.bytes + leaf * (uint64_t)a.S, u, 0, kNoKey);
+  // three classes of leaves, each decoded at once: offsets and a chunk's sum in 32
+  // bits, 32-bit offsets summed in 64, and 64-bit offsets (one lane walking such a
+  // leaf alone took 80 us at 1 KiB and 300 at 4; thirty scans of a whole set of 63-bit
+  // keys 665 us, 191 now)
+  LeafSum x{0, 0};
+  const bool small = span < (1ull << 28), mid = !small && span < (1ull << 32);
+  if (__ballot(small && u)) x = wave_code_sums<kPlain, false, uint32_t>(a, leaf, h, small ? u : 0u, stage);
+  if (__ballot(mid)) {
+    const LeafSum y = wave_code_sums<kPlain, true, uint32_t>(a, leaf, h, mid ? u : 0u, stage);
+    if (mid) x = y;
+  }
+  if (__ballot(span >= (1ull << 32))) {
+    const LeafSum y = wave_code_sums<kPlain, true, uint64_t>(a, leaf, h, span >= (1ull << 32) ? u : 0u, stage);
+    if (span >= (1ull << 32)) x = y;
   }
   return x;
 }
@@ -373,18 +395,13 @@ __device__ __forceinline__ void leaf_prefix_finish(const QueryArgs& a, const Lea
 //    (visits ascend with the lane, so equal queries sit in runs of lanes), one
 //    pair of atomics per run -- a query spanning millions of leaves would
 //    otherwise serialise on one address.
-//
-// kPlain: compressed leaves without values (zero past `used`); this instance
-// also keeps the register count of the other formats' decoders out of the hot
-// kernel.
-template <bool kPlain>
-__global__ void __launch_bounds__(256, 4) k_rm_interior(QueryArgs a, const uint64_t* __restrict__ ioff,
-                                                     const uint64_t* __restrict__ first_int, uint32_t chunk,
-                                                     unsigned long long* __restrict__ sum,
-                                                     unsigned long long* __restrict__ count,
-                                                     unsigned long long* __restrict__ alg, LeafPrefix lp) {
-  __shared__ __align__(16) uint8_t stages[256 / kWave][kStageBytes];
-  uint8_t* const stage = stages[threadIdx.x / kWave];
+template <Visit kVisit>
+__device__ __forceinline__ void interior_visits(const QueryArgs& a, const uint64_t* __restrict__ ioff,
+                                                const uint64_t* __restrict__ first_int, uint32_t chunk,
+                                                unsigned long long* __restrict__ sum,
+                                                unsigned long long* __restrict__ count,
+                                                unsigned long long* __restrict__ alg, const LeafPrefix& lp,
+                                                uint8_t* stage) {
   const int lane = lane_id();
   const uint64_t V = uniform64(ioff[a.q]);
   const bool by_prefix = lp.ps && V > a.L;
@@ -441,7 +458,7 @@ __global__ void __launch_bounds__(256, 4) k_rm_interior(QueryArgs a, const uint6
         leaf = (uint32_t)(first_int[qi] + (v - ioff[qi]));
       }
       // nothing lies after the last leaf: no prefix needs its sum
-      const LeafSum x = wave_leaf_sums<kPlain>(a, leaf, v < Wend && leaf + 1ull < a.L, stage, visited);
+      const LeafSum x = wave_leaf_sums<kVisit>(a, leaf, v < Wend && leaf + 1ull < a.L, stage, visited);
       uint64_t s = x.sum;
       uint32_t n = (uint32_t)x.count;
       if (by_prefix) {
@@ -499,6 +516,25 @@ __global__ void __launch_bounds__(256, 4) k_rm_interior(QueryArgs a, const uint6
     const uint64_t t = wave_sum((uint64_t)visited);
     if (lane_id() == 0) alg[((uint64_t)blockIdx.x * blockDim.x + threadIdx.x) / kWave] = t;
   }
+}
+
+// Compressed leaves (kPlain: zero past `used`), and 8-byte words.
+template <bool kPlain>
+__global__ void __launch_bounds__(256, 4) k_rm_interior(QueryArgs a, const uint64_t* __restrict__ ioff,
+                                                     const uint64_t* __restrict__ first_int, uint32_t chunk,
+                                                     unsigned long long* __restrict__ sum,
+                                                     unsigned long long* __restrict__ count,
+                                                     unsigned long long* __restrict__ alg, LeafPrefix lp) {
+  __shared__ __align__(16) uint8_t stages[256 / kWave][kStageBytes];
+  interior_visits<kPlain ? Visit::kPlain : Visit::kCodes>(a, ioff, first_int, chunk, sum, count, alg, lp,
+                                                          stages[threadIdx.x / kWave]);
+}
+__global__ void __launch_bounds__(256, 4) k_rm_words(QueryArgs a, const uint64_t* __restrict__ ioff,
+                                                  const uint64_t* __restrict__ first_int, uint32_t chunk,
+                                                  unsigned long long* __restrict__ sum,
+                                                  unsigned long long* __restrict__ count,
+                                                  unsigned long long* __restrict__ alg, LeafPrefix lp) {
+  interior_visits<Visit::kWords>(a, ioff, first_int, chunk, sum, count, alg, lp, nullptr);
 }
 
 // After a prefix pass of more than kPrefixInline queries (the same test as in

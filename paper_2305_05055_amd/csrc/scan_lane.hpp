@@ -113,30 +113,40 @@ __device__ __forceinline__ uint32_t zf_byte(uint32_t x, uint32_t& D, uint32_t& s
   return D & ~cm;
 }
 
+// The same with 64-bit offsets.
+template <int J>
+__device__ __forceinline__ uint64_t zf_byte(uint32_t x, uint64_t& D, uint32_t& sh) {
+  uint32_t cm;
+  asm("v_bfe_i32 %0, %1, %2, 1" : "=v"(cm) : "v"(x), "i"(8 * J + 7));
+  D += (uint64_t)__builtin_amdgcn_ubfe(x, 8 * J, 7) << (sh & 63u);
+  sh = (sh + 7u) & cm;
+  return D & ~(uint64_t)(int64_t)(int32_t)cm;
+}
+
 // One 16-byte chunk of wave_leaf_sums.  `cont` counts continuation bytes.
-// kWide: offsets may reach 2^32, so every terminator's is added in 64 bits;
-// otherwise they stay below 2^28, the chunk's 16 sum below 2^32 and are folded
-// into the 64-bit total once.
-template <bool kWide>
-__device__ __forceinline__ void zf_chunk(const uint4 q, uint32_t& D, uint32_t& sh, uint64_t& Sc, uint32_t& cont) {
+// kSum64: every terminator's offset is added in 64 bits; otherwise offsets stay
+// below 2^28, the chunk's 16 sum below 2^32 and are folded into the 64-bit total
+// once.  KT: 32-bit offsets (up to 2^32) or 64-bit ones.
+template <bool kSum64, typename KT>
+__device__ __forceinline__ void zf_chunk(const uint4 q, KT& D, uint32_t& sh, uint64_t& Sc, uint32_t& cont) {
   const uint32_t w[4] = {q.x, q.y, q.z, q.w};
   uint32_t s = 0;
 #pragma unroll
-  for (int k = 0; k < 4; k++) {
-    const uint32_t x = w[k];
-    const uint32_t t0 = zf_byte<0>(x, D, sh);
-    const uint32_t t1 = zf_byte<1>(x, D, sh);
-    const uint32_t t2 = zf_byte<2>(x, D, sh);
-    const uint32_t t3 = zf_byte<3>(x, D, sh);
-    if constexpr (kWide) {
+  for (int j = 0; j < 4; j++) {
+    const uint32_t x = w[j];
+    const KT t0 = zf_byte<0>(x, D, sh);
+    const KT t1 = zf_byte<1>(x, D, sh);
+    const KT t2 = zf_byte<2>(x, D, sh);
+    const KT t3 = zf_byte<3>(x, D, sh);
+    if constexpr (kSum64) {
       Sc += ((uint64_t)t0 + t1) + ((uint64_t)t2 + t3);
-      __builtin_amdgcn_sched_barrier(0);  // few registers: this instance is rarely the one that runs
+      __builtin_amdgcn_sched_barrier(0);  // few registers: occupancy hides the loads
     } else {
-      s += (t0 + t1) + (t2 + t3);
+      s += (uint32_t)((t0 + t1) + (t2 + t3));
     }
     cont += (uint32_t)__popc(x & 0x80808080u);
   }
-  if constexpr (!kWide) Sc += s;
+  if constexpr (!kSum64) Sc += s;
 }
 
 // General path: 64-bit decode; counts and sums keys in [lo, hi).  Stops early
