@@ -157,9 +157,15 @@ __device__ __forceinline__ uint64_t row_walk(const uint8_t* __restrict__ leaf, u
     uint64_t s = 0;
     uint32_t s32 = 0;
     const KT run = walk_bytes<KT>(w, sh, [&](KT off, uint32_t cm) {
-      if constexpr (kSum) s32 += (uint32_t)off & ~cm;
+      if constexpr (kSum && sizeof(KT) == 8) {
+        s += off & ~(KT)(int64_t)(int32_t)cm;
+        // added as it comes: a tree over all sixteen offsets takes 60 registers, and the
+        // narrow walk, in the same kernel, a wave of occupancy
+        asm volatile("" : "+v"(s));
+      }
+      if constexpr (kSum && sizeof(KT) == 4) s32 += (uint32_t)off & ~cm;
     });
-    if constexpr (kSum) {
+    if constexpr (kSum && sizeof(KT) == 4) {
       // 16 offsets below 2^28 sum below 2^32; larger ones are added again in 64 bits
       s = s32;
       if (run >= (KT)(1u << 28)) {
@@ -257,11 +263,13 @@ __device__ __forceinline__ Lookup wave_lookup(const QueryArgs& a, bool valid, ui
   bool reached = false;
   // the next lookups' first round is loaded before the current ones are decoded
   uint32_t n_used = 0, n_leaf = 0;
+  bool n_wide = false;
   uint4 n_w = make_uint4(0, 0, 0, 0);
   auto fetch = [&](uint32_t it) {
     const uint32_t from = walk_lane(it);
-    n_used = from_lane(used, from);
-    if (kPair && from == 64u) n_used = 0;
+    const uint32_t u = from_lane(used | (wide ? 1u << 31 : 0u), from);
+    n_used = kPair && from == 64u ? 0u : u & ~(1u << 31);
+    n_wide = (u >> 31) != 0;
     n_leaf = from_lane((uint32_t)leaf, from);
     if (16u * l16 < n_used) n_w = load16(a.bytes + (uint64_t)n_leaf * a.S + 16u * l16);
   };
@@ -297,6 +305,7 @@ __device__ __forceinline__ Lookup wave_lookup(const QueryArgs& a, bool valid, ui
       const uint32_t ur = n_used;
       const uint8_t* lp = a.bytes + (uint64_t)n_leaf * a.S;
       const uint4 w = n_w;
+      const bool walk_wide = __ballot(n_wide) != 0;  // one of these four
       if (it + 1 < nit) fetch(it + 1);
       auto walk = [&](auto zero) {
         using KT = decltype(zero);
@@ -306,7 +315,7 @@ __device__ __forceinline__ Lookup wave_lookup(const QueryArgs& a, bool valid, ui
         sum2 = two.sum;
         found2 = two.found;
       };
-      if (any_wide)
+      if (walk_wide)
         walk((uint64_t)0);
       else
         walk((uint32_t)0);

@@ -69,3 +69,27 @@ def test_ten_byte_codes(cp, orc):
             es, en = orc.range_map(k, lo, hi)
             assert np.array_equal(n, en) and np.array_equal(s, es), S
             c.close()
+
+
+@pytest.mark.parametrize("S", [64, 1024, 4096])
+@pytest.mark.parametrize("values", [False, True])
+def test_lookups_over_mixed_leaves(cp, orc, S, values):
+    """Lookups of one wave in leaves of small and of wide spans, beside and at their keys."""
+    keys = mixed_keys(40000, 7970, 52)
+    c = cp.CPMA(keys, leaf_bytes=S, values=keys if values else None)
+    r = np.random.default_rng(7971)
+    at = keys[r.integers(0, len(keys), 6000)]
+    x = at + r.integers(0, 3, 6000).astype(np.uint64) - np.uint64(1)
+    width = np.uint64(1) << r.integers(0, 60, 6000).astype(np.uint64)
+    hi = np.minimum(x, np.uint64((1 << 64) - 2) - width) + width
+    for sel in (slice(None), slice(0, 7)):
+        s, n = c.range_map(x[sel], hi[sel])
+        es, en = orc.range_map(keys, x[sel], hi[sel])
+        assert np.array_equal(n, en) and np.array_equal(s, es)
+        assert np.array_equal(c.contains(x[sel]), orc.contains(keys, x[sel]))
+        if values:
+            v, found = c.get(x[sel])
+            member = orc.contains(keys, x[sel]).astype(bool)
+            assert np.array_equal(found.astype(bool), member)
+            assert np.array_equal(v, np.where(member, x[sel], np.uint64(0)))
+    c.close()
