@@ -2386,8 +2386,8 @@ static cpma_status range_map_impl(const cpma* cs, const uint64_t* lo, const uint
       ensure(s->qparts, 8 * nslots);
       qalg = s->qparts.as<unsigned long long>();
     }
-    hipLaunchKernelGGL(k_rm_ends, dim3(egrid), dim3(256), 0, st, a, s->qfirst.as<uint64_t>(),
-                       s->qnvis.as<uint64_t>(), dsum, dcount, qalg, lp.ticket, per);
+    hipLaunchKernelGGL(ends_to_leaf_end(q, a.raw != 0) ? k_rm_ends<true> : k_rm_ends<false>, dim3(egrid), dim3(256), 0,
+                       st, a, s->qfirst.as<uint64_t>(), s->qnvis.as<uint64_t>(), dsum, dcount, qalg, lp.ticket, per);
     HIPCHK(hipGetLastError());
     scan<uint64_t>(s, s->qvoff.as<uint64_t>(), q, st, LoadFn<uint64_t>{s->qnvis.as<uint64_t>()});
     PhaseMark ps = phase_begin(s, CPMA_PHASE_RANGE_SCAN, st);
@@ -2521,7 +2521,8 @@ cpma_status cpma_range_map_noalloc(const cpma* cs, const uint64_t* lo, const uin
     unsigned long long* dcount = (unsigned long long*)count;
     // the same kernels as cpma_range_map, without statistics
     const uint32_t per = lookups_per_wave(s, 2 * q);
-    hipLaunchKernelGGL(k_rm_ends, dim3(lookup_grid(s, 2 * q, per)), dim3(256), 0, st, a, first, nvis, dsum, dcount,
+    hipLaunchKernelGGL(ends_to_leaf_end(q, a.raw != 0) ? k_rm_ends<true> : k_rm_ends<false>,
+                       dim3(lookup_grid(s, 2 * q, per)), dim3(256), 0, st, a, first, nvis, dsum, dcount,
                        (unsigned long long*)nullptr, (unsigned int*)nullptr, per);
     HIPCHK(hipGetLastError());
     HIPCHK(scan_exclusive<uint64_t>(LoadFn<uint64_t>{nvis}, q, voff, tmp, st));

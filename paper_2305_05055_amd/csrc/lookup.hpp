@@ -120,6 +120,7 @@ struct Lookup {
   uint64_t cnt;  // keys of the leaf below x
   uint64_t sum;  // their sum, or the sum of their values
   bool eq;       // x is a key of the leaf
+  uint64_t cnt_from, sum_from;  // to the leaf's end: its other keys (then, with values, sum is not set)
 };
 
 // Four leaves' walks, one per row.  KT: the type of key offsets from the head, 32
@@ -129,7 +130,8 @@ struct Lookup {
 // the sum of their keys' offsets).  Returns the rows' lanes that reached X.
 //
 // kPair: a row may look for a second key X2 >= X in the same walk (dual), with its
-// own slot, count, sum and lanes in `two`; X2 = X otherwise.
+// own slot, count, sum and lanes in `two`; or, with X2 above every offset, go on to
+// the leaf's end, whose totals are then in `two`; X2 = X otherwise.
 template <typename KT>
 struct Second {
   KT X;
@@ -217,18 +219,20 @@ __device__ __forceinline__ uint64_t row_walk(const uint8_t* __restrict__ leaf, u
 // kPair: lanes 2i and 2i + 1 look up a range's two ends (x of the odd lane not below
 // the even one's); pairs in one leaf share a walk, and `order` (64 entries of LDS per
 // wave) lists the walks.  Many short ranges have both ends in one leaf: the end
-// leaves of 1e6 Zipf(1.2) ranges take 423 us, 477 with a walk per end.
+// leaves of 1e6 Zipf(1.2) ranges take 423 us, 477 with a walk per end.  An even lane
+// may also want what lies from x to the end of its leaf (to_end).
 template <bool kCnt, bool kSum, bool kEq, bool kPair = false>
 __device__ __forceinline__ Lookup wave_lookup(const QueryArgs& a, bool valid, uint64_t leaf, uint64_t x,
-                                              Reach* reach, uint8_t* order = nullptr) {
+                                              Reach* reach, uint8_t* order = nullptr, bool to_end = false) {
   const uint32_t l = (uint32_t)lane_id(), l16 = l & 15u;
   const uint64_t head = valid ? a.head[leaf] : kNoKey;
   const uint64_t next = valid && leaf + 1 < a.L ? a.head[leaf + 1] : kNoKey;
-  // x below the head (only below every key) and an empty leaf: nothing to read;
-  // nor for the reserved key, which no leaf holds (its offset can look like a
+  // x below the head (only below every key) and an empty leaf: nothing to read, but
+  // to the leaf's end; nor for the reserved key, which no leaf holds (its offset can look like a
   // continuation byte's)
-  const uint32_t used = valid && x >= head && head != kNoKey && !(kEq && x == kNoKey) ? a.used[leaf] : 0u;
-  const uint64_t X = used ? x - head : 0;
+  const uint32_t used =
+      valid && (x >= head || to_end) && head != kNoKey && !(kEq && x == kNoKey) ? a.used[leaf] : 0u;
+  const uint64_t X = used && x >= head ? x - head : 0;
   const bool wide = used && next - head >= 0xffffffffull;
   const uint32_t nvalid = (uint32_t)__popcll(__ballot(valid));
   uint32_t nwalk = nvalid, slot = l;  // walks, and the one that answers this lane
@@ -237,7 +241,7 @@ __device__ __forceinline__ Lookup wave_lookup(const QueryArgs& a, bool valid, ui
     constexpr int kXor1 = 1 | (0 << 2) | (3 << 4) | (2 << 6);
     const uint32_t other_used = dpp32<kXor1>(used);  // every lane takes part in the exchange
     const uint64_t other_leaf = dpp64<kXor1>(leaf);
-    same = !a.raw && used && other_used && other_leaf == leaf;
+    same = used && other_used && other_leaf == leaf;
     const bool own = used && !(same && (l & 1u));
     const uint64_t walks = __ballot(own);
     nwalk = (uint32_t)__popcll(walks);
@@ -259,7 +263,7 @@ __device__ __forceinline__ Lookup wave_lookup(const QueryArgs& a, bool valid, ui
       return w;
   };
   const bool any_wide = __ballot(wide) != 0;
-  Lookup out{0, 0, false};
+  Lookup out{0, 0, false, 0, 0};
   bool reached = false;
   // the next lookups' first round is loaded before the current ones are decoded
   uint32_t n_used = 0, n_leaf = 0;
@@ -283,10 +287,11 @@ __device__ __forceinline__ Lookup wave_lookup(const QueryArgs& a, bool valid, ui
     uint64_t X2 = Xr, sum2 = 0, found2 = 0;
     uint32_t cnt2 = 0;
     if constexpr (kPair) {
-      const uint32_t d = from_lane(same ? 1u : 0u, from);
-      dual = d != 0 && !none;
+      const uint32_t want = from_lane(same ? 1u : (to_end ? 2u : 0u), from);  // every lane takes part
+      const uint32_t d = none ? 0u : want;
+      dual = d == 1u;
       const uint64_t o = from_lane(X, from | 1u);
-      if (dual) X2 = o;
+      if (d) X2 = dual ? o : ~0ull;
     }
     uint64_t sum = 0, found = 0;
     uint32_t cnt = 0;
@@ -295,11 +300,16 @@ __device__ __forceinline__ Lookup wave_lookup(const QueryArgs& a, bool valid, ui
       const uint32_t uf = from_lane(used, from), m = none ? 0u : uf / 8;
       const uint64_t hd = from_lane(head, from);
       const uint64_t* k = reinterpret_cast<const uint64_t*>(a.bytes + (uint64_t)from_lane((uint32_t)leaf, from) * a.S);
+#pragma unroll 4
       for (uint32_t i = l16; i < m; i += 16) {
         const uint64_t d = k[i] - hd;
         cnt += d < Xr ? 1u : 0u;
         if constexpr (kSum) sum += d < Xr ? d : 0ull;
         if constexpr (kEq) eq |= d == Xr;
+        if constexpr (kPair) {
+          cnt2 += d < X2 ? 1u : 0u;
+          sum2 += d < X2 ? d : 0ull;
+        }
       }
     } else {
       const uint32_t ur = n_used;
@@ -328,6 +338,7 @@ __device__ __forceinline__ Lookup wave_lookup(const QueryArgs& a, bool valid, ui
       if constexpr (kPair) {
         const uint32_t c2 = from_lane(row_last(row_incl_scan(cnt2)), src);
         if (second) c = c2;
+        if (mine && to_end) out.cnt_from = c2;
       }
       if (mine) out.cnt = c;
     }
@@ -336,6 +347,7 @@ __device__ __forceinline__ Lookup wave_lookup(const QueryArgs& a, bool valid, ui
       if constexpr (kPair) {
         const uint64_t t2 = from_lane(row_last(row_incl_scan(sum2)), src);
         if (second) t = t2;
+        if (mine && to_end) out.sum_from = t2;
       }
       if (mine) out.sum = t;
     }
@@ -374,23 +386,31 @@ __device__ __forceinline__ Lookup wave_lookup(const QueryArgs& a, bool valid, ui
     }
     __builtin_amdgcn_wave_barrier();  // the slots may be written again
   }
+  if constexpr (kPair) {  // from the leaf's totals
+    if (to_end) {
+      out.cnt_from -= out.cnt;
+      out.sum_from = out.sum_from - out.sum + out.cnt_from * head;
+    }
+  }
   if constexpr (kSum) {
     if (!a.vals) {
       out.sum += out.cnt * head;
     } else {
-      // the values of the keys below x: the first of the leaf's m values
+      // the values of the keys below x: the first of the leaf's m values; to the
+      // leaf's end: the others
       const uint32_t m = used ? (a.fill[leaf] - used) / 8 : 0u;
 #pragma unroll 1
       for (uint32_t it = 0; it < (nvalid + 3u) / 4u; it++) {
         const uint32_t from = 4u * it + (opaque_lane() >> 4);
-        const uint32_t c = from_lane((uint32_t)out.cnt, from);
+        const uint32_t v0 = from_lane(to_end ? (uint32_t)out.cnt : 0u, from);
+        const uint32_t v1 = from_lane(to_end ? m : (uint32_t)out.cnt, from);
         const uint64_t* v = reinterpret_cast<const uint64_t*>(
             a.bytes + (uint64_t)from_lane((uint32_t)leaf, from) * a.S + a.S - 8u * from_lane(m, from));
         uint64_t s = 0;
-        for (uint32_t i = l16; i < c; i += 16) s += v[i];
+        for (uint32_t i = v0 + l16; i < v1; i += 16) s += v[i];
         const uint32_t ol = opaque_lane();
         const uint64_t t = from_lane(row_last(row_incl_scan(s)), 16u * (ol & 3u));
-        if ((ol >> 2) == it) out.sum = t;
+        if ((ol >> 2) == it) (to_end ? out.sum_from : out.sum) = t;
       }
     }
   }

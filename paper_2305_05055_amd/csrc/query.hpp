@@ -20,9 +20,12 @@ namespace cpma_dev {
 // keys of [lo, hi) are those of leaves f .. l - 1 and the ones of leaf l below hi,
 // without the ones of leaf f below lo; the result initialises sum / count with
 // the two partial leaves (in wrapping 64-bit arithmetic), and leaves f .. l - 1
-// are the query's interior visits.  Two lookups per query, each stopping where
-// it reaches its key.  A wave takes `per` lookups (4 .. 64) at a time: as many as
+// are the query's interior visits.  With kToEnd, lo's lookup goes on to the end of
+// its leaf instead when l lies behind it, and the interior visits are f + 1 .. l - 1:
+// a short range that runs into the next leaf then waits for no scan.  Two lookups
+// per query, each stopping where it reaches its key.  A wave takes `per` lookups (4 .. 64) at a time: as many as
 // it has lanes for when there are plenty, four when that leaves waves idle.
+template <bool kToEnd>
 __global__ void __launch_bounds__(256) k_rm_ends(QueryArgs a, uint64_t* __restrict__ first_int,
                                                  uint64_t* __restrict__ nint,
                                                  unsigned long long* __restrict__ sum,
@@ -43,16 +46,18 @@ __global__ void __launch_bounds__(256) k_rm_ends(QueryArgs a, uint64_t* __restri
     const bool some = lo < hi;
     // the even lane looks lo up, the odd one hi in the leaf of hi - 1
     const uint64_t leaf = wave_locate(a, valid, lane & 1 ? (some ? hi - 1 : 0) : lo);
-    const Lookup r = wave_lookup<true, true, false, true>(a, valid, leaf, lane & 1 ? hi : lo, mine,
-                                                          order[threadIdx.x / kWave]);
     constexpr int kXor1 = 1 | (0 << 2) | (3 << 4) | (2 << 6);
-    const uint64_t leaf_l = dpp64<kXor1>(leaf), sum_l = dpp64<kXor1>(r.sum), cnt_l = dpp64<kXor1>(r.cnt);
+    const uint64_t leaf_l = dpp64<kXor1>(leaf);
+    const bool whole = kToEnd && some && !(lane & 1) && leaf_l > leaf;
+    const Lookup r = wave_lookup<true, true, false, true>(a, valid, leaf, lane & 1 ? hi : lo, mine,
+                                                          order[threadIdx.x / kWave], whole);
+    const uint64_t sum_l = dpp64<kXor1>(r.sum), cnt_l = dpp64<kXor1>(r.cnt);
     if (valid && !(lane & 1)) {
-      first_int[i] = leaf;
-      nint[i] = some ? leaf_l - leaf : 0;
-      sum[i] = some ? sum_l - r.sum : 0;
-      count[i] = some ? cnt_l - r.cnt : 0;
-      if (alg && some) visited += a.used[leaf_l];
+      first_int[i] = whole ? leaf + 1 : leaf;
+      nint[i] = some ? leaf_l - leaf - (whole ? 1 : 0) : 0;
+      sum[i] = some ? sum_l + (whole ? r.sum_from : 0 - r.sum) : 0;
+      count[i] = some ? cnt_l + (whole ? r.cnt_from : 0 - r.cnt) : 0;
+      if (alg && some) visited += a.used[leaf_l] + (whole ? a.used[leaf] : 0u);
     }
   }
   if (alg) {  // statistics: one slot per wave (no shared counter), summed by k_fold_sum
