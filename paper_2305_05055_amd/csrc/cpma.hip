@@ -2272,12 +2272,10 @@ static void launch_interior(const QueryArgs& a, uint32_t blocks, hipStream_t st,
                        dsum, dcount);
 }
 
-// Memory of the leaf prefixes for a batch of q queries, kept across calls
-// (about 13 bytes per leaf): none for a single query, which never visits a leaf
-// twice, nor when it cannot be had (the scan then visits leaf by leaf).  A
-// handful of queries rarely visits more leaves than the set has: it uses the
-// memory when it is there but does not take it (45 us in a first call).
-constexpr uint64_t kPrefixMinQueries = 32;
+// Memory of the leaf prefixes for a batch of q queries, kept across calls (12 bytes
+// per leaf, and a little per 32 leaves): none for a single query, which never visits
+// a leaf twice, nor when it cannot be had (the scan then visits leaf by leaf).  A
+// batch uses the memory when it is there; takes_prefix says when it takes it.
 static LeafPrefix leaf_prefix(cpma* s, uint64_t q, uint32_t blocks, hipStream_t st) {
   LeafPrefix lp{};
   if (q < 2 || blocks > kPrefixRuns) return lp;
@@ -2286,7 +2284,7 @@ static LeafPrefix leaf_prefix(cpma* s, uint64_t q, uint32_t blocks, hipStream_t 
   const size_t need = s->L * 12 + steps * 16 + blocks * 16 + 64;
   if (s->qprefix.cap < need) {
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-    if (q < kPrefixMinQueries) return lp;
+    if (!takes_prefix(q, s->L)) return lp;
     if (hipStreamIsCapturing(st, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) {
       hipGetLastError();
       return lp;

@@ -66,8 +66,16 @@ static void small_split() {
   }
 }
 
+static void prefix_memory() {
+  EXPECT(!takes_prefix(1, 1ull << 40));
+  EXPECT(takes_prefix(32, 1) && !takes_prefix(31, 1000));
+  EXPECT(takes_prefix(25, 1'000'000));  // few scans of a large set
+  EXPECT(!takes_prefix(10, 400'000) && takes_prefix(2, 1ull << 22) && !takes_prefix(2, (1ull << 22) - 1));
+}
+
 int main() {
   wide_merge();
+  prefix_memory();
   small_split();
   return failures != 0;
 }
