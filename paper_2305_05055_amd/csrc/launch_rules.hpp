@@ -49,15 +49,14 @@ struct SplitGuess {
 };
 
 // Whether the lookup of a range's lower end goes on to the end of its leaf when the
-// range does, so that the leaf needs no visit of its own.  A batch of few queries
-// waits for its longest chain, and a visit of one leaf is a chain of its own; many
-// queries are bound by the lookups' instructions, and the visits of different
-// queries share the chip better than longer walks.  Ranges of 3 keys in 5e6: 1000
-// queries 18.8 us to the end and 22.4 with the visits, 30 000 28.9 and 43.9, 1e6 317
-// and 329; of 300 keys: 1000 24.9 and 24.7, 30 000 56 and 52, 1e6 629 and 556.
-// Uncompressed leaves are read whole by the lookup anyway (1e6 ranges of 3 keys: 186
-// and 206).
-inline bool ends_to_leaf_end(uint64_t q, bool raw) { return raw || q <= 32768; }
+// range ends in the next one, so that the leaf needs no visit of its own.  A batch of
+// few queries waits for its longest chain, and a visit of one leaf is a chain of its
+// own; many queries are bound by the lookups' instructions, and the visits of
+// different queries share the chip better than longer walks.  Ranges of 3 keys in 5e6:
+// 1000 queries 20 us to the end and 23 with the visits, 8000 21 and 34; of 300 keys:
+// 30 000 56 and 52, 1e6 629 and 556.  Uncompressed leaves are read whole by the lookup
+// anyway (1e6 ranges of 3 keys: 186 and 206).
+inline bool ends_to_leaf_end(uint64_t q, bool raw) { return raw || q <= 8192; }
 
 // Whether a batch of q ranges on a set of L leaves takes the memory of the leaf prefix
 // sums (12 bytes a leaf) when the handle does not have it yet.  It needs them if it

@@ -21,8 +21,8 @@ namespace cpma_dev {
 // without the ones of leaf f below lo; the result initialises sum / count with
 // the two partial leaves (in wrapping 64-bit arithmetic), and leaves f .. l - 1
 // are the query's interior visits.  With kToEnd, lo's lookup goes on to the end of
-// its leaf instead when l lies behind it, and the interior visits are f + 1 .. l - 1:
-// a short range that runs into the next leaf then waits for no scan.  Two lookups
+// its leaf when l is the next one, and the query has no visits: a short range that
+// runs into the next leaf then waits for no scan.  Two lookups
 // per query, each stopping where it reaches its key.  A wave takes `per` lookups (4 .. 64) at a time: as many as
 // it has lanes for when there are plenty, four when that leaves waves idle.
 template <bool kToEnd>
@@ -48,7 +48,7 @@ __global__ void __launch_bounds__(256) k_rm_ends(QueryArgs a, uint64_t* __restri
     const uint64_t leaf = wave_locate(a, valid, lane & 1 ? (some ? hi - 1 : 0) : lo);
     constexpr int kXor1 = 1 | (0 << 2) | (3 << 4) | (2 << 6);
     const uint64_t leaf_l = dpp64<kXor1>(leaf);
-    const bool whole = kToEnd && some && !(lane & 1) && leaf_l > leaf;
+    const bool whole = kToEnd && some && !(lane & 1) && leaf_l == leaf + 1;
     const Lookup r = wave_lookup<true, true, false, true>(a, valid, leaf, lane & 1 ? hi : lo, mine,
                                                           order[threadIdx.x / kWave], whole);
     const uint64_t sum_l = dpp64<kXor1>(r.sum), cnt_l = dpp64<kXor1>(r.cnt);

@@ -32,7 +32,7 @@ def ranges(keys, q, seed):
     return lo, hi
 
 
-@pytest.mark.parametrize("q", [1, 2, 5, 32768, 32769, 40001])
+@pytest.mark.parametrize("q", [1, 2, 5, 8192, 8193, 40001])
 @pytest.mark.parametrize("bits,S,form", [(22, 1024, "plain"), (40, 128, "plain"), (63, 1024, "plain"), (40, 1024, "raw"),
                                          (63, 512, "values"), (22, 2048, "values")])
 def test_forms(cp, orc, bits, S, form, q):
