@@ -122,10 +122,13 @@ int tree_height(uint64_t L) {
 
 }  // namespace
 
+// The instances of range_map's interior scan, by interior_kind.
+static decltype(&k_rm_words) const kInteriorScans[3] = {k_rm_interior<true>, k_rm_interior<false>, k_rm_words};
+
 struct cpma {
   int device = 0;
   int num_cus = 256;
-  uint32_t rm_blocks[3] = {2048, 2048, 2048};  // resident blocks of k_rm_interior<true>, <false> and k_rm_words
+  uint32_t rm_blocks[3] = {1024, 1024, 1024};  // resident blocks of the interior scans (see interior_kind)
   SplitGuess mid;    // for unsorted batches of 4097 to 2^18 keys
   double wide_share = 1.0;  // wide segments among the last classified batch's
   bool classified = false;  // the current update's segments were classified
@@ -1924,11 +1927,11 @@ static cpma_status build_impl(const uint64_t* keys, const uint64_t* vals, uint64
     s->num_cus = prop.multiProcessorCount;
     // the interior range scan runs one generation of blocks: every block
     // resident at once, so no block starts after the others have finished
-    decltype(&k_rm_words) scans[3] = {k_rm_interior<true>, k_rm_interior<false>, k_rm_words};
     for (int i = 0; i < 3; i++) {
       int per = 0;
-      HIPCHK(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, scans[i], 256, 0));
-      s->rm_blocks[i] = (uint32_t)std::max(1, per) * (uint32_t)s->num_cus;
+      HIPCHK(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, kInteriorScans[i], 256, 0));
+      // four at most: the end of the prefix pass costs every block
+      s->rm_blocks[i] = (uint32_t)std::min(4, std::max(1, per)) * (uint32_t)s->num_cus;
     }
     ensure(s->ctr_buf, sizeof(Counters), 0.0);
     s->dctr = s->ctr_buf.as<Counters>();
@@ -2264,9 +2267,8 @@ static uint32_t interior_blocks(const cpma* s, const QueryArgs& a) { return s->r
 static void launch_interior(const QueryArgs& a, uint32_t blocks, hipStream_t st, const uint64_t* voff,
                             const uint64_t* first, uint32_t chunk, unsigned long long* dsum, unsigned long long* dcount,
                             unsigned long long* alg, const LeafPrefix& lp) {
-  const int kind = interior_kind(a);
-  hipLaunchKernelGGL(kind == 0 ? k_rm_interior<true> : (kind == 1 ? k_rm_interior<false> : k_rm_words), dim3(blocks),
-                     dim3(256), 0, st, a, voff, first, chunk, dsum, dcount, alg, lp);
+  hipLaunchKernelGGL(kInteriorScans[interior_kind(a)], dim3(blocks), dim3(256), 0, st, a, voff, first, chunk, dsum,
+                     dcount, alg, lp);
   if (lp.ps && a.q > kPrefixInline)
     hipLaunchKernelGGL(k_rm_prefix_apply, dim3(grid_for(a.q, 256, 1024)), dim3(256), 0, st, a, voff, first, lp, blocks,
                        dsum, dcount);
@@ -2276,11 +2278,14 @@ static void launch_interior(const QueryArgs& a, uint32_t blocks, hipStream_t st,
 // per leaf, and a little per 32 leaves): none for a single query, which never visits
 // a leaf twice, nor when it cannot be had (the scan then visits leaf by leaf).  A
 // batch uses the memory when it is there; takes_prefix says when it takes it.
-static LeafPrefix leaf_prefix(cpma* s, uint64_t q, uint32_t blocks, hipStream_t st) {
+static LeafPrefix leaf_prefix(cpma* s, const QueryArgs& a, uint32_t blocks, hipStream_t st) {
+  const uint64_t q = a.q;
   LeafPrefix lp{};
   if (q < 2 || blocks > kPrefixRuns) return lp;
   const uint64_t steps = (s->L + kStepLeaves - 1) / kStepLeaves;
-  lp.range = (uint32_t)((steps + blocks - 1) / blocks) * kStepLeaves;
+  // whole steps of the scan: 64 leaves with a lane each, else 32
+  const uint32_t unit = interior_kind(a) < 2 && s->L >= lane_visits(a) ? 2 * kStepLeaves : kStepLeaves;
+  lp.range = (uint32_t)(((s->L + unit - 1) / unit + blocks - 1) / blocks) * unit;
   const size_t need = s->L * 12 + steps * 16 + blocks * 16 + 64;
   if (s->qprefix.cap < need) {
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
@@ -2378,7 +2383,7 @@ static cpma_status range_map_impl(const cpma* cs, const uint64_t* lo, const uint
     const uint64_t ewaves = 4ull * egrid;
     const uint32_t blocks = interior_blocks(s, a);
     const uint64_t nslots = ewaves + 4ull * blocks;
-    const LeafPrefix lp = leaf_prefix(s, q, blocks, st);
+    const LeafPrefix lp = leaf_prefix(s, a, blocks, st);
     unsigned long long* qalg = nullptr;
     if (s->stats_on && ((s->stats_mask >> CPMA_PHASE_RANGE_SCAN) & 1u)) {
       ensure(s->qparts, 8 * nslots);

@@ -66,13 +66,13 @@ __global__ void __launch_bounds__(256) k_rm_ends(QueryArgs a, uint64_t* __restri
   }
 }
 
-// ---- whole leaves, 32 per wave ------------------------------------------------------
-// Sums and counts of whole leaves, two lanes per leaf (the wave's 32 leaves need
-// not be neighbours; lanes 2i and 2i + 1 pass the same leaf and `valid`).  A
-// leaf must have a successor, whose head bounds its key span.  The result is in
+// ---- whole leaves, 32 or 64 per wave ------------------------------------------------
+// Sums and counts of whole leaves, kPer lanes per leaf: one, or two (the wave's 32
+// leaves need not be neighbours; lanes 2i and 2i + 1 pass the same leaf and `valid`).
+// A leaf must have a successor, whose head bounds its key span.  The result is in
 // the even lane; the odd lane returns zeros.
 //
-// The leaf's 64-byte rounds are split between its two lanes.  A key's offset
+// With two lanes (lane_visits says when), the leaf's 64-byte rounds are split between its two lanes.  A key's offset
 // from the head is the sum of the payloads of every code byte before it, each
 // shifted by 7 times its place in its code, so a lane sums its own terminators'
 // offsets from zero, and the second lane adds the first one's total to each of
@@ -92,11 +92,11 @@ __global__ void __launch_bounds__(256) k_rm_ends(QueryArgs a, uint64_t* __restri
 constexpr uint32_t kStageBytes = 64u * kWave;
 constexpr uint32_t kStepLeaves = kWave / 2;
 
-template <bool kZero, bool kSum64, typename KT>
+template <uint32_t kPer, bool kZero, bool kSum64, typename KT>
 __device__ __forceinline__ LeafSum wave_code_sums(const QueryArgs& a, uint32_t leaf, uint64_t head, uint32_t used,
                                                   uint8_t* stage) {
-  const uint32_t lane = (uint32_t)lane_id(), r = lane & 1u;
-  const uint32_t half = (used + 127u) >> 7;              // rounds of the first lane
+  const uint32_t lane = (uint32_t)lane_id(), r = lane & (kPer - 1u);
+  const uint32_t half = (used + 64u * kPer - 1u) / (64u * kPer);  // rounds of the first lane
   const uint32_t own = r ? ((used + 63u) >> 6) - half : half;
   const uint32_t start = r ? 64u * half : 0u;
   const uint32_t R = lane63_u32(dpp_incl_max(half));
@@ -187,6 +187,7 @@ __device__ __forceinline__ LeafSum wave_code_sums(const QueryArgs& a, uint32_t l
     keys -= zeros;
     Sc -= (uint64_t)zeros * D;
   }
+  if constexpr (kPer == 1) return LeafSum{Sc + (uint64_t)keys * head, keys};
   constexpr int kXor1 = 1 | (0 << 2) | (3 << 4) | (2 << 6);  // DPP quad permutation: the pair's other lane
   KT D0;
   if constexpr (sizeof(KT) == 8)
@@ -199,6 +200,10 @@ __device__ __forceinline__ LeafSum wave_code_sums(const QueryArgs& a, uint32_t l
   return r ? LeafSum{0, 0} : LeafSum{s, keys};
 }
 
+struct __attribute__((packed, aligned(8))) WordPair {  // values begin at any multiple of 8
+  uint64_t a, b;
+};
+
 // Sums of 8-byte words of 32 leaves (lane 2i, and 2i + 1 alike: m words at byte
 // `at` of `leaf`), eight lanes per leaf and eight leaves at a time.
 __device__ __forceinline__ LeafSum wave_word_sums(const QueryArgs& a, uint32_t leaf, uint32_t at, uint32_t m) {
@@ -209,11 +214,21 @@ __device__ __forceinline__ LeafSum wave_word_sums(const QueryArgs& a, uint32_t l
     const uint32_t from = 16u * it + 2u * (l >> 3);
     const uint64_t lf = from_lane(leaf, from);
     const uint32_t n = from_lane(m, from);
-    const uint64_t* w = reinterpret_cast<const uint64_t*>(a.bytes + lf * a.S + from_lane(at, from));
+    const WordPair* w = reinterpret_cast<const WordPair*>(a.bytes + lf * a.S + from_lane(at, from));
     uint64_t s = 0;
-    uint32_t i = l & 7u;
-    for (; i + 24 < n; i += 32) s += (w[i] + w[i + 8]) + (w[i + 16] + w[i + 24]);
-    for (; i < n; i += 8) s += w[i];
+    // 512 bytes of every leaf in flight; the last pair's second word may be past the end
+    for (uint32_t i = l & 7u; 2 * i < n; i += 32) {
+      WordPair p[4];
+#pragma unroll
+      for (uint32_t k = 0; k < 4; k++) {
+        p[k] = WordPair{0, 0};
+        if (2 * (i + 8 * k) + 1 < n)
+          p[k] = w[i + 8 * k];
+        else if (2 * (i + 8 * k) < n)
+          p[k].a = w[i + 8 * k].a;
+      }
+      s += ((p[0].a + p[0].b) + (p[1].a + p[1].b)) + ((p[2].a + p[2].b) + (p[3].a + p[3].b));
+    }
     constexpr int kXor1 = 1 | (0 << 2) | (3 << 4) | (2 << 6), kXor2 = 2 | (3 << 2) | (0 << 4) | (1 << 6);
     s += dpp64<kXor1>(s);
     s += dpp64<kXor2>(s);
@@ -230,10 +245,10 @@ __device__ __forceinline__ LeafSum wave_word_sums(const QueryArgs& a, uint32_t l
 // together the decoders need more registers than four waves per SIMD leave.
 enum class Visit { kPlain, kCodes, kWords };
 
-template <Visit kVisit>
+template <Visit kVisit, uint32_t kPer>
 __device__ __forceinline__ LeafSum wave_leaf_sums(const QueryArgs& a, uint32_t leaf, bool valid, uint8_t* stage,
                                                   uint32_t& visited) {
-  const uint32_t r = (uint32_t)lane_id() & 1u;
+  const uint32_t r = (uint32_t)lane_id() & (kPer - 1u);
   const uint32_t u = valid ? a.used[leaf] : 0u;
   if (!r) visited += u;
   if constexpr (kVisit == Visit::kWords) {
@@ -248,16 +263,17 @@ __device__ __forceinline__ LeafSum wave_leaf_sums(const QueryArgs& a, uint32_t l
   // bits, 32-bit offsets summed in 64, and 64-bit offsets (one lane walking such a
   // leaf alone took 80 us at 1 KiB and 300 at 4; thirty scans of a whole set of 63-bit
   // keys 665 us, 191 now)
-  LeafSum x{0, 0};
-  const bool small = span < (1ull << 28), mid = !small && span < (1ull << 32);
-  if (__ballot(small && u)) x = wave_code_sums<kPlain, false, uint32_t>(a, leaf, h, small ? u : 0u, stage);
-  if (__ballot(mid)) {
-    const LeafSum y = wave_code_sums<kPlain, true, uint32_t>(a, leaf, h, mid ? u : 0u, stage);
-    if (mid) x = y;
-  }
-  if (__ballot(span >= (1ull << 32))) {
-    const LeafSum y = wave_code_sums<kPlain, true, uint64_t>(a, leaf, h, span >= (1ull << 32) ? u : 0u, stage);
-    if (span >= (1ull << 32)) x = y;
+  const bool mid = span >= (1ull << 28) && span < (1ull << 32), wide = span >= (1ull << 32);
+  LeafSum x = wave_code_sums<kPer, kPlain, false, uint32_t>(a, leaf, h, mid || wide ? 0u : u, stage);
+  if (__ballot(mid || wide)) {
+    if (__ballot(mid)) {
+      const LeafSum y = wave_code_sums<kPer, kPlain, true, uint32_t>(a, leaf, h, mid ? u : 0u, stage);
+      if (mid) x = y;
+    }
+    if (__ballot(wide)) {
+      const LeafSum y = wave_code_sums<kPer, kPlain, true, uint64_t>(a, leaf, h, wide ? u : 0u, stage);
+      if (wide) x = y;
+    }
   }
   return x;
 }
@@ -266,7 +282,7 @@ __device__ __forceinline__ LeafSum wave_leaf_sums(const QueryArgs& a, uint32_t l
 // than the set has: every leaf is then summed once and a query's interior is
 // the difference of two prefixes, exact in wrapping 64-bit arithmetic.  A block
 // takes one run of `range` leaves, its waves 32 leaves at a time.
-//   ps / pc: exclusive prefix of the leaf sums / counts inside the 32 leaves;
+//   ps / pc: exclusive prefix of the leaf sums / counts inside groups of 32 leaves;
 //   ss / sc: the 32 leaves' totals, then their exclusive prefix in the run;
 //   ts / tc: the runs' totals, then their exclusive prefix.
 // ps NULL: no memory for it, visit leaf by leaf.  10^6 Zipf(1.2) queries on
@@ -400,13 +416,14 @@ __device__ __forceinline__ void leaf_prefix_finish(const QueryArgs& a, const Lea
 //    (visits ascend with the lane, so equal queries sit in runs of lanes), one
 //    pair of atomics per run -- a query spanning millions of leaves would
 //    otherwise serialise on one address.
-template <Visit kVisit>
+template <Visit kVisit, uint32_t kPer>
 __device__ __forceinline__ void interior_visits(const QueryArgs& a, const uint64_t* __restrict__ ioff,
                                                 const uint64_t* __restrict__ first_int, uint32_t chunk,
                                                 unsigned long long* __restrict__ sum,
                                                 unsigned long long* __restrict__ count,
                                                 unsigned long long* __restrict__ alg, const LeafPrefix& lp,
                                                 uint8_t* stage) {
+  constexpr uint32_t kStep = kWave / kPer;  // leaves at a time
   const int lane = lane_id();
   const uint64_t V = uniform64(ioff[a.q]);
   const bool by_prefix = lp.ps && V > a.L;
@@ -417,15 +434,15 @@ __device__ __forceinline__ void interior_visits(const QueryArgs& a, const uint64
   if (by_prefix) {
     f0 = min(a.L, (uint64_t)blockIdx.x * lp.range);
     f1 = min(a.L, f0 + lp.range);
-    G = kStepLeaves;
-    g = f0 / kStepLeaves + (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
+    G = kStep;
+    g = f0 / kStep + (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
     step = 256 / kWave;
     end = f0 < f1 ? f1 : 0;
   } else {
     step = (uint64_t)gridDim.x * (256 / kWave);
     g = (uint64_t)blockIdx.x * (256 / kWave) + (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
     const uint64_t share = (V + step - 1) / step;
-    G = max<uint64_t>(1, min<uint64_t>((uint64_t)kWave * chunk, (share + kStepLeaves - 1) / kStepLeaves * kStepLeaves));
+    G = max<uint64_t>(1, min<uint64_t>((uint64_t)kWave * chunk, (share + kStep - 1) / kStep * kStep));
     end = V;
   }
   uint64_t cq = ~0ull, cs = 0;  // carried query (wave-uniform) and this lane's share of its sum
@@ -446,8 +463,8 @@ __device__ __forceinline__ void interior_visits(const QueryArgs& a, const uint64
     const uint64_t Wend = min((g + 1) * G, end);
     // the query of the group's first visit; then of the part before
     uint64_t q0 = by_prefix ? 0 : uniform64(upper_bound_u64(ioff, a.q + 1, g * G) - 1);
-    for (uint64_t base = g * G; base < Wend; base += kStepLeaves) {
-      const uint64_t v = base + (lane >> 1);
+    for (uint64_t base = g * G; base < Wend; base += kStep) {
+      const uint64_t v = base + (uint32_t)lane / kPer;
       uint64_t vq = ~0ull;
       uint32_t leaf = (uint32_t)v;
       if (!by_prefix && v < Wend) {
@@ -463,19 +480,29 @@ __device__ __forceinline__ void interior_visits(const QueryArgs& a, const uint64
         leaf = (uint32_t)(first_int[qi] + (v - ioff[qi]));
       }
       // nothing lies after the last leaf: no prefix needs its sum
-      const LeafSum x = wave_leaf_sums<kVisit>(a, leaf, v < Wend && leaf + 1ull < a.L, stage, visited);
+      const LeafSum x = wave_leaf_sums<kVisit, kPer>(a, leaf, v < Wend && leaf + 1ull < a.L, stage, visited);
       uint64_t s = x.sum;
       uint32_t n = (uint32_t)x.count;
       if (by_prefix) {
-        const uint64_t is = wave_incl_scan(s);
-        const uint32_t ic = wave_incl_scan(n);
-        if (!(lane & 1) && v < Wend) {
+        uint64_t is = wave_incl_scan(s);
+        uint32_t ic = wave_incl_scan(n);
+        if (kPer == 1) {  // two groups of kStepLeaves
+          const uint64_t s31 = from_lane(is, kStepLeaves - 1);
+          const uint32_t c31 = from_lane(ic, kStepLeaves - 1);
+          if (lane >= (int)kStepLeaves) {
+            is -= s31;
+            ic -= c31;
+          }
+        }
+        if (!(lane & (kPer - 1u)) && v < Wend) {
           lp.ps[v] = is - s;
           lp.pc[v] = ic - n;
         }
-        if (lane == kWave - 1) {
-          lp.ss[base / kStepLeaves] = is;
-          lp.sc[base / kStepLeaves] = ic;
+        const uint64_t group = base / kStepLeaves + (kPer == 1 ? (uint32_t)lane / kStepLeaves : 0u);
+        if ((kPer == 1 ? (lane & (kStepLeaves - 1u)) == kStepLeaves - 1u : lane == kWave - 1) &&
+            group * kStepLeaves < Wend) {
+          lp.ss[group] = is;
+          lp.sc[group] = ic;
         }
         continue;
       }
@@ -523,23 +550,44 @@ __device__ __forceinline__ void interior_visits(const QueryArgs& a, const uint64
   }
 }
 
-// Compressed leaves (kPlain: zero past `used`), and 8-byte words.
+// Leaves a scan sums from which on each gets one lane, not two.  Two lanes halve a
+// leaf's chain of 64-byte rounds, which bounds a scan of few leaves; one lane wastes
+// no half round and takes 64 leaves per wait for memory.  The fewer rounds a leaf has,
+// the sooner that counts; about a third of a key-value leaf is codes.  Scans of a whole set of 40-bit keys,
+// one lane and two: 5e6 at 64, 256 and 512 bytes a leaf 52 and 68 us, 34 and 51, 27 and
+// 35; 1e9 at 1024 bytes 477 and 518, at 2048 457 and 502, at 4096 478 and 485; but 3e5 at 512 bytes (2200
+// leaves) 34 and 27, 1000 ranges of 1000 keys there 25 and 21, and 5e6 at 1024 (18 500)
+// 28 and 27, 1000 ranges of 1e5 keys at 4096 (72 000 visits) 96 and 77.
+__host__ __device__ inline uint64_t lane_visits(const QueryArgs& a) {
+  const uint32_t codes = a.zero_fill ? a.S : a.S / 2;
+  return codes <= 512 ? 16384 : (codes <= 2048 ? 65536 : 262144);
+}
+
+// Compressed leaves (kPlain: zero past `used`; the other instance takes three waves
+// per SIMD, at four it spills 46 registers: a scan of 5e7 key-value keys 117 and 87 us).
 template <bool kPlain>
-__global__ void __launch_bounds__(256, 4) k_rm_interior(QueryArgs a, const uint64_t* __restrict__ ioff,
+__global__ void __launch_bounds__(256, kPlain ? 4 : 3) k_rm_interior(QueryArgs a, const uint64_t* __restrict__ ioff,
                                                      const uint64_t* __restrict__ first_int, uint32_t chunk,
                                                      unsigned long long* __restrict__ sum,
                                                      unsigned long long* __restrict__ count,
                                                      unsigned long long* __restrict__ alg, LeafPrefix lp) {
   __shared__ __align__(16) uint8_t stages[256 / kWave][kStageBytes];
-  interior_visits<kPlain ? Visit::kPlain : Visit::kCodes>(a, ioff, first_int, chunk, sum, count, alg, lp,
-                                                          stages[threadIdx.x / kWave]);
+  constexpr Visit kVisit = kPlain ? Visit::kPlain : Visit::kCodes;
+  uint8_t* const stage = stages[threadIdx.x / kWave];
+  const uint64_t V = uniform64(ioff[a.q]);
+  if ((lp.ps && V > a.L ? a.L : V) >= lane_visits(a))
+    interior_visits<kVisit, 1>(a, ioff, first_int, chunk, sum, count, alg, lp, stage);
+  else
+    interior_visits<kVisit, 2>(a, ioff, first_int, chunk, sum, count, alg, lp, stage);
 }
+
+// 8-byte words.
 __global__ void __launch_bounds__(256, 4) k_rm_words(QueryArgs a, const uint64_t* __restrict__ ioff,
                                                   const uint64_t* __restrict__ first_int, uint32_t chunk,
                                                   unsigned long long* __restrict__ sum,
                                                   unsigned long long* __restrict__ count,
                                                   unsigned long long* __restrict__ alg, LeafPrefix lp) {
-  interior_visits<Visit::kWords>(a, ioff, first_int, chunk, sum, count, alg, lp, nullptr);
+  interior_visits<Visit::kWords, 2>(a, ioff, first_int, chunk, sum, count, alg, lp, nullptr);
 }
 
 // After a prefix pass of more than kPrefixInline queries (the same test as in
