@@ -540,10 +540,33 @@ __device__ __forceinline__ void interior_visits(const QueryArgs& a, const uint64
       }
     }
   }
-  if (by_prefix)
+  if (by_prefix) {
     leaf_prefix_finish(a, lp, ioff, first_int, sum, count, f0, f1);
-  else
-    flush_carry();
+  } else {
+    // what the block's waves carry at the end: one pair of atomics per query, since a
+    // scan of one query ends with all of them on one address, about 7 ns each
+    __shared__ uint64_t end_q[256 / kWave], end_s[256 / kWave], end_n[256 / kWave];
+    const uint64_t ts = wave_sum<uint64_t>(cs), tn = wave_sum<uint64_t>((uint64_t)cn);
+    if (lane == 0) {
+      end_q[threadIdx.x / kWave] = cq;
+      end_s[threadIdx.x / kWave] = ts;
+      end_n[threadIdx.x / kWave] = tn;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      uint64_t s = 0, n = 0;
+      for (uint32_t w = 0; w < 256 / kWave; w++) {
+        s += end_s[w];
+        n += end_n[w];
+        if (w + 1 < 256 / kWave && end_q[w + 1] == end_q[w]) continue;
+        if (end_q[w] != ~0ull && n) {
+          atomicAdd(&sum[end_q[w]], (unsigned long long)s);
+          atomicAdd(&count[end_q[w]], (unsigned long long)n);
+        }
+        s = n = 0;
+      }
+    }
+  }
   if (alg) {
     const uint64_t t = wave_sum((uint64_t)visited);
     if (lane_id() == 0) alg[((uint64_t)blockIdx.x * blockDim.x + threadIdx.x) / kWave] = t;
@@ -553,14 +576,15 @@ __device__ __forceinline__ void interior_visits(const QueryArgs& a, const uint64
 // Leaves a scan sums from which on each gets one lane, not two.  Two lanes halve a
 // leaf's chain of 64-byte rounds, which bounds a scan of few leaves; one lane wastes
 // no half round and takes 64 leaves per wait for memory.  The fewer rounds a leaf has,
-// the sooner that counts; about a third of a key-value leaf is codes.  Scans of a whole set of 40-bit keys,
-// one lane and two: 5e6 at 64, 256 and 512 bytes a leaf 52 and 68 us, 34 and 51, 27 and
-// 35; 1e9 at 1024 bytes 477 and 518, at 2048 457 and 502, at 4096 478 and 485; but 3e5 at 512 bytes (2200
-// leaves) 34 and 27, 1000 ranges of 1000 keys there 25 and 21, and 5e6 at 1024 (18 500)
-// 28 and 27, 1000 ranges of 1e5 keys at 4096 (72 000 visits) 96 and 77.
+// the sooner that counts; about a third of a key-value leaf is codes.  One lane and
+// two: whole scans of 5e6 40-bit keys at 256 bytes a leaf (80 000 leaves) 20 and 23 us, of
+// 5e7 and 2e8 at 1 KiB 53 and 56, 128 and 134, of 2e8 at 2 KiB 125 and 136; but four
+// scans of 3e5 key-value keys at 1 KiB (22 000 visits) 26 and 18, ranges of 3000 keys
+// among 5e6 at 1 and 2 KiB 32 and 27, 43 and 33, 1000 ranges of 1e5 keys at 4 KiB (72 000
+// visits) 96 and 77.
 __host__ __device__ inline uint64_t lane_visits(const QueryArgs& a) {
   const uint32_t codes = a.zero_fill ? a.S : a.S / 2;
-  return codes <= 512 ? 16384 : (codes <= 2048 ? 65536 : 262144);
+  return codes <= 512 ? 32768 : (codes <= 2048 ? 65536 : 262144);
 }
 
 // Compressed leaves (kPlain: zero past `used`; the other instance takes three waves
