@@ -2215,7 +2215,10 @@ cpma_status cpma_apply_updates(cpma* s, uint32_t nreq, const int32_t* kind, cons
                          (const uint32_t*)s->leafid.as<uint32_t>(), s->fz_member.as<uint8_t>());
     } else {
       const uint32_t per = lookups_per_wave(s, m);
-      hipLaunchKernelGGL(k_contains, dim3(lookup_grid(s, m, per)), dim3(256), 0, st, qa,
+      const bool lanes = lane_lookups(s->S, m, false);
+      hipLaunchKernelGGL(lanes ? k_contains_lane : k_contains,
+                         dim3(lanes ? grid_for(m, 256, (uint32_t)s->num_cus * 16) : lookup_grid(s, m, per)), dim3(256),
+                         0, st, qa,
                          (const uint64_t*)s->kdedup.as<uint64_t>(), s->fz_member.as<uint8_t>(), per,
                          (const unsigned long long*)fctr);
     }
@@ -2325,6 +2328,15 @@ static QueryArgs query_args(const cpma* s) {
   return a;
 }
 
+static decltype(&k_rm_ends_lane) ends_kernel(const QueryArgs& a) {
+  if (!a.raw && !a.vals && lane_lookups(a.S, a.q, true)) return k_rm_ends_lane;
+  return ends_to_leaf_end(a.q, a.raw != 0) ? k_rm_ends<true> : k_rm_ends<false>;
+}
+static uint32_t ends_grid(const cpma* s, const QueryArgs& a, uint32_t per) {
+  if (ends_kernel(a) == k_rm_ends_lane) return grid_for(a.q, 256, (uint32_t)s->num_cus * 16);
+  return lookup_grid(s, 2 * a.q, per);
+}
+
 // values: sum the values of key-value leaves instead of the keys.
 // Host queries up to this many skip the copies of pageable memory: the end kernel
 // reads the bounds from pinned memory (once, a cache line per 8 queries) and one
@@ -2379,7 +2391,7 @@ static cpma_status range_map_impl(const cpma* cs, const uint64_t* lo, const uint
     ensure(s->qvoff, (q + 1) * 8);
     PhaseMark pq = phase_begin(s, CPMA_PHASE_QUERY, st);
     // statistics: one byte-count slot per wave of the end and interior kernels
-    const uint32_t per = lookups_per_wave(s, 2 * q), egrid = lookup_grid(s, 2 * q, per);
+    const uint32_t per = lookups_per_wave(s, 2 * q), egrid = ends_grid(s, a, per);
     const uint64_t ewaves = 4ull * egrid;
     const uint32_t blocks = interior_blocks(s, a);
     const uint64_t nslots = ewaves + 4ull * blocks;
@@ -2389,8 +2401,7 @@ static cpma_status range_map_impl(const cpma* cs, const uint64_t* lo, const uint
       ensure(s->qparts, 8 * nslots);
       qalg = s->qparts.as<unsigned long long>();
     }
-    hipLaunchKernelGGL(ends_to_leaf_end(q, a.raw != 0) ? k_rm_ends<true> : k_rm_ends<false>, dim3(egrid), dim3(256), 0,
-                       st, a, s->qfirst.as<uint64_t>(), s->qnvis.as<uint64_t>(), dsum, dcount, qalg, lp.ticket, per);
+    hipLaunchKernelGGL(ends_kernel(a), dim3(egrid), dim3(256), 0, st, a, s->qfirst.as<uint64_t>(), s->qnvis.as<uint64_t>(), dsum, dcount, qalg, lp.ticket, per);
     HIPCHK(hipGetLastError());
     scan<uint64_t>(s, s->qvoff.as<uint64_t>(), q, st, LoadFn<uint64_t>{s->qnvis.as<uint64_t>()});
     PhaseMark ps = phase_begin(s, CPMA_PHASE_RANGE_SCAN, st);
@@ -2524,8 +2535,7 @@ cpma_status cpma_range_map_noalloc(const cpma* cs, const uint64_t* lo, const uin
     unsigned long long* dcount = (unsigned long long*)count;
     // the same kernels as cpma_range_map, without statistics
     const uint32_t per = lookups_per_wave(s, 2 * q);
-    hipLaunchKernelGGL(ends_to_leaf_end(q, a.raw != 0) ? k_rm_ends<true> : k_rm_ends<false>,
-                       dim3(lookup_grid(s, 2 * q, per)), dim3(256), 0, st, a, first, nvis, dsum, dcount,
+    hipLaunchKernelGGL(ends_kernel(a), dim3(ends_grid(s, a, per)), dim3(256), 0, st, a, first, nvis, dsum, dcount,
                        (unsigned long long*)nullptr, (unsigned int*)nullptr, per);
     HIPCHK(hipGetLastError());
     HIPCHK(scan_exclusive<uint64_t>(LoadFn<uint64_t>{nvis}, q, voff, tmp, st));
@@ -2560,7 +2570,10 @@ cpma_status cpma_contains(const cpma* cs, const uint64_t* keys, uint64_t q, cpma
     }
     PhaseMark pq = phase_begin(s, CPMA_PHASE_QUERY, st);
     const uint32_t per = lookups_per_wave(s, q);
-    hipLaunchKernelGGL(k_contains, dim3(lookup_grid(s, q, per)), dim3(256), 0, st, a, dk, dout, per,
+    const bool lanes = !a.raw && lane_lookups(s->S, q, false);
+    hipLaunchKernelGGL(lanes ? k_contains_lane : k_contains,
+                       dim3(lanes ? grid_for(q, 256, (uint32_t)s->num_cus * 16) : lookup_grid(s, q, per)), dim3(256),
+                       0, st, a, dk, dout, per,
                        (const unsigned long long*)nullptr);
     HIPCHK(hipGetLastError());
     phase_end(s, pq, st);

@@ -66,6 +66,47 @@ __global__ void __launch_bounds__(256) k_rm_ends(QueryArgs a, uint64_t* __restri
   }
 }
 
+// The same for small leaves and many queries (lane_lookups): a lane per query scans its
+// one or two end leaves with comparisons, and the interior visits are f + 1 .. l - 1.
+// A row of 16 lanes has bytes for as many only in leaves of 256.
+__global__ void __launch_bounds__(256) k_rm_ends_lane(QueryArgs a, uint64_t* __restrict__ first_int,
+                                                      uint64_t* __restrict__ nint,
+                                                      unsigned long long* __restrict__ sum,
+                                                      unsigned long long* __restrict__ count,
+                                                      unsigned long long* __restrict__ alg, unsigned int* ticket,
+                                                      uint32_t) {
+  if (ticket && blockIdx.x == 0 && threadIdx.x == 0) *ticket = 0;  // for k_rm_interior's prefix pass
+  uint64_t visited = 0;
+  for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < a.q;
+       i += (uint64_t)gridDim.x * blockDim.x) {
+    const uint64_t lo = a.lo[i], hi = a.hi[i];
+    uint64_t f = 0, l = 0;
+    LeafSum r{0, 0};
+    if (lo < hi) {
+      f = locate_leaf(a.head, a.L, lo);
+      l = locate_leaf(a.head, a.L, hi - 1);
+      const uint32_t uf = a.used[f];
+      r = leaf_sum_range(a.bytes + f * a.S, uf, lo, hi);
+      visited += uf;
+      if (l != f) {
+        const uint32_t ul = a.used[l];
+        const LeafSum r2 = leaf_sum_range(a.bytes + l * a.S, ul, lo, hi);
+        r.sum += r2.sum;
+        r.count += r2.count;
+        visited += ul;
+      }
+    }
+    first_int[i] = f + 1;
+    nint[i] = l > f ? l - f - 1 : 0;
+    sum[i] = r.sum;
+    count[i] = r.count;
+  }
+  if (alg) {
+    const uint64_t t = wave_sum(visited);
+    if (lane_id() == 0) alg[((uint64_t)blockIdx.x * blockDim.x + threadIdx.x) / kWave] = t;
+  }
+}
+
 // ---- whole leaves, 32 or 64 per wave ------------------------------------------------
 // Sums and counts of whole leaves, kPer lanes per leaf: one, or two (the wave's 32
 // leaves need not be neighbours; lanes 2i and 2i + 1 pass the same leaf and `valid`).
@@ -692,6 +733,17 @@ __global__ void __launch_bounds__(256) k_contains(QueryArgs a, const uint64_t* _
     const uint64_t x = valid ? keys[i] : 0;
     const Lookup r = wave_lookup<false, false, true>(a, valid, wave_locate(a, valid, x), x, mine);
     if (valid) out[i] = r.eq ? 1 : 0;
+  }
+}
+
+// The same for small leaves and many keys (lane_lookups): a lane per key.
+__global__ void __launch_bounds__(256) k_contains_lane(QueryArgs a, const uint64_t* __restrict__ keys,
+                                                       uint8_t* __restrict__ out, uint32_t,
+                                                       const unsigned long long* __restrict__ n) {
+  const uint64_t q = n ? (uint64_t)*n : a.q;
+  for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < q; i += (uint64_t)gridDim.x * blockDim.x) {
+    const uint64_t x = keys[i], leaf = locate_leaf(a.head, a.L, x);
+    out[i] = leaf_sum_range(a.bytes + leaf * a.S, a.used[leaf], x, x + 1).count ? 1 : 0;
   }
 }
 

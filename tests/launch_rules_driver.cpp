@@ -73,8 +73,16 @@ static void prefix_memory() {
   EXPECT(!takes_prefix(10, 400'000) && takes_prefix(2, 1ull << 22) && !takes_prefix(2, (1ull << 22) - 1));
 }
 
+static void lookups() {
+  EXPECT(lane_lookups(64, 32768, true) && !lane_lookups(64, 32767, true) && !lane_lookups(512, 1 << 30, true));
+  EXPECT(lane_lookups(256, 131072, true) && !lane_lookups(256, 1 << 30, false));
+  EXPECT(lane_lookups(128, 131072, false) && !lane_lookups(128, 131071, false));
+  EXPECT(ends_to_leaf_end(8192, false) && !ends_to_leaf_end(8193, false) && ends_to_leaf_end(1 << 20, true));
+}
+
 int main() {
   wide_merge();
+  lookups();
   prefix_memory();
   small_split();
   return failures != 0;
