@@ -2814,29 +2814,19 @@ cpma_status cpma_fgraph_bc(const cpma* cs, uint32_t nv, uint32_t source, cpma_me
 
 namespace {
 
-// PageRank over edges binned once for the call (pagerank.hpp).  False, with
-// nothing launched, where that does not apply: too few edges for its (part, bin)
-// table (with fewer than about 8 per run an iteration is bound by the runs: at 2^24
-// vertices and 1.6e7 edges it takes 0.25 ms and the pull over the leaves 0.35, at
-// 2e6 edges 0.2 and 0.13), edge positions beyond 32 bits, or no memory (8 bytes per
-// edge).
+// PageRank over edges binned once for the call (pagerank.hpp), for a set and nv that
+// pg_fits.  False, with nothing launched, without memory (8 bytes per edge).
 bool pagerank_binned(cpma* s, const FgArgs& g, int iters, double damping, float* pv, hipStream_t st) {
   PgArgs a{};
   a.nv = g.nv;
-  if (s->n >= (1ull << 32) - 1024 || g.nv > (1u << 25)) return false;
-  bool fits = false;
   // parts of 128 KB (a block per CU in the gather: parts of half the size gather 13 %
   // faster, add 9 % slower and are binned 18 % slower), bins of at most 64 KB (two
   // blocks per CU); about 2048 bins of equal edges, half as many for few edges
-  a.pbits = 15;
-  a.bbits = 13;
-  a.P = (uint32_t)(((uint64_t)g.nv + (1u << a.pbits) - 1) >> a.pbits);
-  for (uint32_t few = 0; few < 2 && !fits; few++) {
-    a.cuts = few ? 1024 : 2048;
-    a.B = a.cuts + (uint32_t)(((uint64_t)g.nv + (1u << a.bbits) - 1) >> a.bbits);
-    fits = s->n >= (few ? 8ull : 16ull) * a.P * a.B;
-  }
-  if (!fits) return false;
+  a.pbits = kPgPartBits;
+  a.bbits = kPgBinBits;
+  a.P = pg_parts(g.nv);
+  a.cuts = pg_cuts(s->n, g.nv);
+  a.B = pg_bins(g.nv, a.cuts);
   const uint64_t cells = (uint64_t)a.P * a.B;
   a.seg = (uint32_t)std::min<uint64_t>(1u << 17, std::max<uint64_t>(1u << 13, s->n / 2048 & ~3ull));
   const uint64_t segs = a.P + s->n / a.seg + 1;
@@ -2888,6 +2878,29 @@ bool pagerank_binned(cpma* s, const FgArgs& g, int iters, double damping, float*
   return true;
 }
 
+// PageRank by pulls over the leaves, sums of type T.
+template <typename T>
+void pagerank_pull(cpma* s, const FgArgs& g, int iters, double damping, float* pv, hipStream_t st) {
+  const uint32_t nv = g.nv, vg = grid_for(nv, 256, 8192);
+  const float rank0 = 1.0f / (float)nv, base = (float)((1.0 - damping) / (double)nv);
+  if (iters == 0) {
+    hipLaunchKernelGGL((k_fill<float>), dim3(vg), dim3(256), 0, st, pv, (uint64_t)nv, rank0);
+    return;
+  }
+  ensure(s->fg_acc, (uint64_t)nv * sizeof(T));
+  uint32_t* deg = s->fg_deg.as<uint32_t>();
+  float* contrib = s->fg_c.as<float>();
+  T* acc = s->fg_acc.as<T>();
+  hipLaunchKernelGGL((k_fill<uint32_t>), dim3(vg), dim3(256), 0, st, deg, (uint64_t)nv, 0u);
+  hipLaunchKernelGGL(k_fg_degree, dim3(fg_grid(s)), dim3(256), 0, st, g, deg);
+  hipLaunchKernelGGL(k_pr_first<T>, dim3(vg), dim3(256), 0, st, (const uint32_t*)deg, nv, rank0, contrib, acc);
+  for (int it = 0; it < iters; it++) {
+    hipLaunchKernelGGL(k_fg_pull<T>, dim3(fg_grid(s)), dim3(256), 0, st, g, (const float*)contrib, acc);
+    hipLaunchKernelGGL(k_pr_update<T>, dim3(vg), dim3(256), 0, st, (const uint32_t*)deg, nv, base, (float)damping, pv,
+                       contrib, acc, it + 1 < iters ? 1 : 0);
+  }
+}
+
 }  // namespace
 
 extern "C" {
@@ -2908,23 +2921,14 @@ cpma_status cpma_fgraph_pagerank(const cpma* cs, uint32_t nv, int iters, double 
     }
     ensure(s->fg_deg, (uint64_t)nv * 4);
     ensure(s->fg_c, (uint64_t)nv * 4);
-    ensure(s->fg_acc, (uint64_t)nv * 4);
-    const uint32_t vg = grid_for(nv, 256, 8192);
     const FgArgs g = fg_args(s, nv);
     PhaseMark pq = phase_begin(s, CPMA_PHASE_QUERY, st);
-    if (iters == 0 || !pagerank_binned(s, g, iters, damping, pv, st)) {
-      hipLaunchKernelGGL((k_fill<uint32_t>), dim3(vg), dim3(256), 0, st, s->fg_deg.as<uint32_t>(), (uint64_t)nv, 0u);
-      hipLaunchKernelGGL((k_fill<float>), dim3(vg), dim3(256), 0, st, pv, (uint64_t)nv, 1.0f / (float)nv);
-      hipLaunchKernelGGL(k_fg_degree, dim3(fg_grid(s)), dim3(256), 0, st, g, s->fg_deg.as<uint32_t>());
-      const float base = (float)((1.0 - damping) / (double)nv);
-      for (int it = 0; it < iters; it++) {
-        hipLaunchKernelGGL(k_pr_contrib, dim3(vg), dim3(256), 0, st, (const float*)pv,
-                           (const uint32_t*)s->fg_deg.as<uint32_t>(), nv, s->fg_c.as<float>(), s->fg_acc.as<float>());
-        hipLaunchKernelGGL(k_fg_pull, dim3(fg_grid(s)), dim3(256), 0, st, g, (const float*)s->fg_c.as<float>(),
-                           s->fg_acc.as<float>());
-        hipLaunchKernelGGL(k_pr_update, dim3(vg), dim3(256), 0, st, (const float*)s->fg_acc.as<float>(), nv, base,
-                           (float)damping, pv);
-      }
+    const bool dense = pg_fits(s->n, nv);
+    if (!(dense && bins_pay(s->n, nv, (uint32_t)iters) && pagerank_binned(s, g, iters, damping, pv, st))) {
+      if (dense)
+        pagerank_pull<double>(s, g, iters, damping, pv, st);
+      else
+        pagerank_pull<float>(s, g, iters, damping, pv, st);
     }
     HIPCHK(hipGetLastError());
     phase_end(s, pq, st);

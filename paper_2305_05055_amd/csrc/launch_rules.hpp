@@ -78,4 +78,30 @@ inline bool lane_lookups(uint32_t S, uint64_t q, bool ranges) {
   return ranges ? S <= 256 && q >= 512ull * S : S <= 128 && q >= 1024ull * S;
 }
 
+// PageRank's binned form (pagerank.hpp): parts of 2^kPgPartBits destinations, bins of at
+// most 2^kPgBinBits sources, `cuts` of them at the leaves' limits.
+constexpr uint32_t kPgPartBits = 15, kPgBinBits = 13;
+inline uint32_t pg_parts(uint32_t nv) { return (uint32_t)(((uint64_t)nv + (1u << kPgPartBits) - 1) >> kPgPartBits); }
+inline uint32_t pg_bins(uint32_t nv, uint32_t cuts) {
+  return cuts + (uint32_t)(((uint64_t)nv + (1u << kPgBinBits) - 1) >> kPgBinBits);
+}
+// 2048 cuts with at least 16 edges to a (part, bin) run, 1024 with at least 8, else none.
+inline uint32_t pg_cuts(uint64_t n, uint32_t nv) {
+  if (n >= 16ull * pg_parts(nv) * pg_bins(nv, 2048)) return 2048;
+  return n >= 8ull * pg_parts(nv) * pg_bins(nv, 1024) ? 1024 : 0;
+}
+// Whether the binned form applies: runs long enough, vertices and edge positions
+// within what its tables hold.
+inline bool pg_fits(uint64_t n, uint32_t nv) {
+  return n < (1ull << 32) - 1024 && nv <= (1u << 25) && pg_cuts(n, nv) != 0;
+}
+// Whether it pays: binning costs about 50 us more than the pull's setup, and up to 1e6
+// vertices, whose contributions the L2s hold, an iteration gains little.  Pull and
+// bins, one iteration and ten: 2^16 vertices and 2e6 edges 60 and 134 us, 284 and 400;
+// 2^18 and 8e6 155 and 222, 863 and 887; 2^20 and 2e6 100 and 143, 578 and 538; 2^20 and
+// 3.3e7 603 and 529; 2^22 and 2e6 170 and 156.
+inline bool bins_pay(uint64_t n, uint32_t nv, uint32_t iters) {
+  return iters && (unsigned __int128)iters * (n + nv / 2) * nv >= (1ull << 43);
+}
+
 }  // namespace cpma_dev

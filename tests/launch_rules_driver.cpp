@@ -80,8 +80,19 @@ static void lookups() {
   EXPECT(ends_to_leaf_end(8192, false) && !ends_to_leaf_end(8193, false) && ends_to_leaf_end(1 << 20, true));
 }
 
+static void pagerank() {
+  const uint64_t M = 1'000'000;
+  EXPECT(!bins_pay(2 * M, 1u << 16, 10) && !bins_pay(8 * M, 1u << 18, 1) && bins_pay(8 * M, 1u << 18, 10));
+  EXPECT(!bins_pay(2 * M, 1u << 20, 1) && bins_pay(2 * M, 1u << 20, 10) && bins_pay(33 * M, 1u << 20, 1));
+  EXPECT(bins_pay(2 * M, 1u << 22, 1) && !bins_pay(1000 * M, 1u << 24, 0));
+  EXPECT(pg_fits(2 * M, 1u << 20) && !pg_fits(2 * M, 1u << 24) && pg_fits(266 * M, 1u << 24));
+  EXPECT(pg_fits((1ull << 32) - 1025, 1u << 25) && !pg_fits((1ull << 32) - 1024, 1u << 25));
+  EXPECT(!pg_fits(1ull << 31, (1u << 25) + 1) && !pg_fits(10, 1));
+}
+
 int main() {
   wide_merge();
+  pagerank();
   lookups();
   prefix_memory();
   small_split();
