@@ -163,7 +163,7 @@ __device__ __forceinline__ uint64_t row_walk(const uint8_t* __restrict__ leaf, u
         s += off & ~(KT)(int64_t)(int32_t)cm;
         // added as it comes: a tree over all sixteen offsets takes 60 registers, and the
         // narrow walk, in the same kernel, a wave of occupancy
-        asm volatile("" : "+v"(s));
+        asm("" : "+v"(s));
       }
       if constexpr (kSum && sizeof(KT) == 4) s32 += (uint32_t)off & ~cm;
     });
