@@ -72,10 +72,11 @@ inline bool takes_prefix(uint64_t q, uint64_t L) { return q >= 32 || (q > 1 && L
 // enough lookups to hide it.  Row and lane: ranges of 3 keys, 1e6 of them in 5e6 keys,
 // at 64 bytes a leaf 271 and 155 us, at 256 231 and 173; 60 000 ranges of 100 keys in 1e6 at 64, 128
 // and 256 bytes 51 and 44, 48 and 52, 48 and 72; 1e6 of them at 512 385 and 438.
-// Membership of 1e6 keys among 5e6 at 64 bytes 118 and 78, of 60 000 and 250 000 in 1e6
-// at 128 bytes 13 and 16, 37 and 30, of 1e6 at 256 101 and 107.
+// Membership of 1e6 keys among 5e6 at 64 bytes 118 and 78, of 16 000 and 30 000 in 1e6
+// 10 and 10, 12 and 11, of 60 000 and 250 000 at 128 bytes 13 and 16, 37 and 30, of 1e6
+// at 256 101 and 107.
 inline bool lane_lookups(uint32_t S, uint64_t q, bool ranges) {
-  return ranges ? S <= 256 && q >= 512ull * S : S <= 128 && q >= 1024ull * S;
+  return ranges ? S <= 256 && q >= 384ull * S : S <= 128 && q >= 6ull * S * S;
 }
 
 // PageRank's binned form (pagerank.hpp): parts of 2^kPgPartBits destinations, bins of at

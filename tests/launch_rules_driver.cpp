@@ -74,9 +74,9 @@ static void prefix_memory() {
 }
 
 static void lookups() {
-  EXPECT(lane_lookups(64, 32768, true) && !lane_lookups(64, 32767, true) && !lane_lookups(512, 1 << 30, true));
-  EXPECT(lane_lookups(256, 131072, true) && !lane_lookups(256, 1 << 30, false));
-  EXPECT(lane_lookups(128, 131072, false) && !lane_lookups(128, 131071, false));
+  EXPECT(lane_lookups(64, 24576, true) && !lane_lookups(64, 24575, true) && !lane_lookups(512, 1 << 30, true));
+  EXPECT(lane_lookups(256, 98304, true) && !lane_lookups(256, 1 << 30, false));
+  EXPECT(lane_lookups(128, 98304, false) && !lane_lookups(128, 98303, false) && lane_lookups(64, 24576, false));
   EXPECT(ends_to_leaf_end(8192, false) && !ends_to_leaf_end(8193, false) && ends_to_leaf_end(1 << 20, true));
 }
 

@@ -24,7 +24,7 @@ def test_lookups(cp, orc, S, bits, values):
     keys = np.unique(synth.uniform_keys(50_000, 8200, bits=bits) + np.uint64(3))
     c = cp.CPMA(keys, leaf_bytes=S, values=keys if values else None)
     r = np.random.default_rng(8201)
-    for q in (512 * S - 1, 512 * S, 1024 * S):
+    for q in (384 * S - 1, 384 * S, 6 * S * S - 1, 6 * S * S):
         i = r.integers(0, len(keys), q)
         lo = keys[i] + r.choice(np.array([0, 1, 2**64 - 1], np.uint64), q)
         hi = keys[np.minimum(i + r.choice([0, 1, 2, 10, 90, 600], q), len(keys) - 1)] + np.uint64(1)
