@@ -2267,13 +2267,14 @@ cpma_status cpma_apply_updates(cpma* s, uint32_t nreq, const int32_t* kind, cons
 // sets, 8-byte words.
 static int interior_kind(const QueryArgs& a) { return a.raw || a.vals ? 2 : (a.zero_fill ? 0 : 1); }
 static uint32_t interior_blocks(const cpma* s, const QueryArgs& a) { return s->rm_blocks[interior_kind(a)]; }
-static void launch_interior(const QueryArgs& a, uint32_t blocks, hipStream_t st, const uint64_t* voff,
+static void launch_interior(const QueryArgs& a, uint32_t blocks, hipStream_t st, uint64_t* voff, const uint64_t* nvis,
                             const uint64_t* first, uint32_t chunk, unsigned long long* dsum, unsigned long long* dcount,
                             unsigned long long* alg, const LeafPrefix& lp) {
-  hipLaunchKernelGGL(kInteriorScans[interior_kind(a)], dim3(blocks), dim3(256), 0, st, a, voff, first, chunk, dsum,
-                     dcount, alg, lp);
+  hipLaunchKernelGGL(kInteriorScans[interior_kind(a)], dim3(blocks), dim3(256), 0, st, a, voff, nvis, first, chunk,
+                     dsum, dcount, alg, lp);
   if (lp.ps && a.q > kPrefixInline)
-    hipLaunchKernelGGL(k_rm_prefix_apply, dim3(grid_for(a.q, 256, 1024)), dim3(256), 0, st, a, voff, first, lp, blocks,
+    hipLaunchKernelGGL(k_rm_prefix_apply, dim3(grid_for(a.q, 256, 1024)), dim3(256), 0, st, a, (const uint64_t*)voff,
+                       first, lp, blocks,
                        dsum, dcount);
 }
 
@@ -2403,9 +2404,10 @@ static cpma_status range_map_impl(const cpma* cs, const uint64_t* lo, const uint
     }
     hipLaunchKernelGGL(ends_kernel(a), dim3(egrid), dim3(256), 0, st, a, s->qfirst.as<uint64_t>(), s->qnvis.as<uint64_t>(), dsum, dcount, qalg, lp.ticket, per);
     HIPCHK(hipGetLastError());
-    scan<uint64_t>(s, s->qvoff.as<uint64_t>(), q, st, LoadFn<uint64_t>{s->qnvis.as<uint64_t>()});
+    if (q > kOwnScanQueries)
+      scan<uint64_t>(s, s->qvoff.as<uint64_t>(), q, st, LoadFn<uint64_t>{s->qnvis.as<uint64_t>()});
     PhaseMark ps = phase_begin(s, CPMA_PHASE_RANGE_SCAN, st);
-    launch_interior(a, blocks, st, s->qvoff.as<uint64_t>(), s->qfirst.as<uint64_t>(), s->cfg.range_chunk, dsum,
+    launch_interior(a, blocks, st, s->qvoff.as<uint64_t>(), s->qnvis.as<uint64_t>(), s->qfirst.as<uint64_t>(), s->cfg.range_chunk, dsum,
                     dcount, qalg ? qalg + ewaves : qalg, lp);
     HIPCHK(hipGetLastError());
     phase_end(s, ps, st, 32ull * q);
@@ -2538,8 +2540,8 @@ cpma_status cpma_range_map_noalloc(const cpma* cs, const uint64_t* lo, const uin
     hipLaunchKernelGGL(ends_kernel(a), dim3(ends_grid(s, a, per)), dim3(256), 0, st, a, first, nvis, dsum, dcount,
                        (unsigned long long*)nullptr, (unsigned int*)nullptr, per);
     HIPCHK(hipGetLastError());
-    HIPCHK(scan_exclusive<uint64_t>(LoadFn<uint64_t>{nvis}, q, voff, tmp, st));
-    launch_interior(a, interior_blocks(s, a), st, voff, first, s->cfg.range_chunk, dsum, dcount, nullptr,
+    if (q > kOwnScanQueries) HIPCHK(scan_exclusive<uint64_t>(LoadFn<uint64_t>{nvis}, q, voff, tmp, st));
+    launch_interior(a, interior_blocks(s, a), st, voff, nvis, first, s->cfg.range_chunk, dsum, dcount, nullptr,
                     LeafPrefix{});
     HIPCHK(hipGetLastError());
   });

@@ -628,31 +628,84 @@ __host__ __device__ inline uint64_t lane_visits(const QueryArgs& a) {
   return codes <= 512 ? 32768 : (codes <= 2048 ? 65536 : 262144);
 }
 
+// Batches of up to kOwnScanQueries queries: every block scans the visit counts itself,
+// into LDS (block 0 also to memory, for k_rm_prefix_apply), which takes it a
+// microsecond; a launch for it costs 2.8.
+constexpr uint32_t kOwnScanQueries = 1024;
+__device__ __forceinline__ void visit_offsets(const uint64_t* __restrict__ nint, uint32_t q, uint64_t* offs,
+                                              uint64_t* __restrict__ ioff) {
+  __shared__ uint64_t red[4];
+  const uint32_t i0 = 4 * threadIdx.x, wid = threadIdx.x / kWave;
+  uint64_t x[4], t = 0;
+#pragma unroll
+  for (uint32_t j = 0; j < 4; j++) {
+    x[j] = i0 + j < q ? nint[i0 + j] : 0;
+    t += x[j];
+  }
+  const uint64_t incl = wave_incl_scan(t);
+  if (lane_id() == kWave - 1) red[wid] = incl;
+  __syncthreads();
+  uint64_t at = incl - t;
+#pragma unroll
+  for (uint32_t w = 0; w < 4; w++) at += w < wid ? red[w] : 0;
+#pragma unroll
+  for (uint32_t j = 0; j < 4; j++) {
+    if (i0 + j <= q) {
+      offs[i0 + j] = at;
+      if (blockIdx.x == 0) ioff[i0 + j] = at;
+    }
+    at += x[j];
+  }
+  if (q == kOwnScanQueries && threadIdx.x == 255) {
+    offs[q] = at;
+    if (blockIdx.x == 0) ioff[q] = at;
+  }
+  __syncthreads();
+}
+
 // Compressed leaves (kPlain: zero past `used`; the other instance takes three waves
 // per SIMD, at four it spills 46 registers: a scan of 5e7 key-value keys 117 and 87 us).
+// nint: with few queries, the visit counts to scan.
 template <bool kPlain>
-__global__ void __launch_bounds__(256, kPlain ? 4 : 3) k_rm_interior(QueryArgs a, const uint64_t* __restrict__ ioff,
+__global__ void __launch_bounds__(256, kPlain ? 4 : 3) k_rm_interior(QueryArgs a, uint64_t* __restrict__ ioff,
+                                                     const uint64_t* __restrict__ nint,
                                                      const uint64_t* __restrict__ first_int, uint32_t chunk,
                                                      unsigned long long* __restrict__ sum,
                                                      unsigned long long* __restrict__ count,
                                                      unsigned long long* __restrict__ alg, LeafPrefix lp) {
   __shared__ __align__(16) uint8_t stages[256 / kWave][kStageBytes];
+  __shared__ uint64_t offs[kOwnScanQueries + 1];
   constexpr Visit kVisit = kPlain ? Visit::kPlain : Visit::kCodes;
   uint8_t* const stage = stages[threadIdx.x / kWave];
-  const uint64_t V = uniform64(ioff[a.q]);
-  if ((lp.ps && V > a.L ? a.L : V) >= lane_visits(a))
-    interior_visits<kVisit, 1>(a, ioff, first_int, chunk, sum, count, alg, lp, stage);
-  else
-    interior_visits<kVisit, 2>(a, ioff, first_int, chunk, sum, count, alg, lp, stage);
+  auto visits = [&](const uint64_t* off) {
+    const uint64_t V = uniform64(off[a.q]);
+    if ((lp.ps && V > a.L ? a.L : V) >= lane_visits(a))
+      interior_visits<kVisit, 1>(a, off, first_int, chunk, sum, count, alg, lp, stage);
+    else
+      interior_visits<kVisit, 2>(a, off, first_int, chunk, sum, count, alg, lp, stage);
+  };
+  if (a.q <= kOwnScanQueries) {
+    visit_offsets(nint, (uint32_t)a.q, offs, ioff);
+    visits(offs);
+  } else {
+    visits(ioff);
+  }
 }
 
 // 8-byte words.
-__global__ void __launch_bounds__(256, 4) k_rm_words(QueryArgs a, const uint64_t* __restrict__ ioff,
+__global__ void __launch_bounds__(256, 4) k_rm_words(QueryArgs a, uint64_t* __restrict__ ioff,
+                                                  const uint64_t* __restrict__ nint,
                                                   const uint64_t* __restrict__ first_int, uint32_t chunk,
                                                   unsigned long long* __restrict__ sum,
                                                   unsigned long long* __restrict__ count,
                                                   unsigned long long* __restrict__ alg, LeafPrefix lp) {
-  interior_visits<Visit::kWords, 2>(a, ioff, first_int, chunk, sum, count, alg, lp, nullptr);
+  __shared__ uint64_t offs[kOwnScanQueries + 1];
+  if (a.q <= kOwnScanQueries) {
+    visit_offsets(nint, (uint32_t)a.q, offs, ioff);
+    interior_visits<Visit::kWords, 2>(a, offs, first_int, chunk, sum, count, alg, lp, nullptr);
+  } else {
+    interior_visits<Visit::kWords, 2>(a, ioff, first_int, chunk, sum, count, alg, lp, nullptr);
+  }
 }
 
 // After a prefix pass of more than kPrefixInline queries (the same test as in

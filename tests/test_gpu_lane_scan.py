@@ -43,7 +43,7 @@ def test_scans(cp, S, n, bits, form):
     vals = synth.uniform_keys(len(keys), 8101, bits=64) if form == "values" else None
     c = cp.CPMA(keys, leaf_bytes=S, uncompressed=form == "raw", values=vals)
     r = np.random.default_rng(8102)
-    for q in (1, 9, 31, 40, 3000):
+    for q in (1, 9, 31, 40, 1023, 1024, 1025, 3000):  # blocks scan up to 1024 queries themselves
         a = r.integers(0, len(keys), (q, 2))
         if q <= 40:  # long ranges, so that few queries make many visits
             a[:, 0] //= 50
