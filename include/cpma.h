@@ -263,8 +263,13 @@ cpma_status cpma_contains(const cpma* set, const uint64_t* keys, uint64_t q,
  * (Section "Packed Memory Array", "Design and operations": search for the first
  * element, then scan) with f = (sum, count): sum[i] is the sum mod 2^64 of the
  * keys in the range and count[i] their number.  lo >= hi gives (0, 0).  Every
- * key of every range is decoded; no per-leaf aggregate is cached.  lo, hi, sum
- * and count are all in memory space `mem`.
+ * leaf that a range touches is decoded in the call, at least once: a batch whose
+ * ranges visit more leaves than the set has decodes each leaf once and shares
+ * its sum between the ranges.  Nothing is reused by a later call; the handle
+ * only keeps the memory of those sums (about 13 bytes a leaf, counted by
+ * cpma_bytes_held, released by cpma_trim), which a batch of 32 queries and more
+ * takes, and fewer on a large set.  lo, hi, sum and count are all in memory
+ * space `mem`.
  */
 cpma_status cpma_range_map(const cpma* set, const uint64_t* lo, const uint64_t* hi,
                            uint64_t q, cpma_mem mem, uint64_t* sum,
@@ -383,10 +388,16 @@ cpma_status cpma_export_code_bytes(const cpma* set, uint32_t* clen, void* stream
  *
  * cpma_fgraph_pagerank: `iters` rounds (the paper runs 10) of
  *   p'(v) = (1 - damping) / nv + damping * sum over edges (v, u) of p(u) / deg(u)
- * from p = 1/nv, with deg(u) the number of edges leaving u and FP32 arithmetic
- * and accumulation.  The edge set must be symmetric (an undirected graph, as
- * in the paper's F-Graph); then this equals pushing p(u)/deg(u) along every
- * edge u -> v.  p is nv floats in memory space `mem`.
+ * from p = 1/nv, with deg(u) the number of edges leaving u, FP32 ranks and
+ * contributions and at least FP32 accumulation (FP64 unless the set has fewer
+ * than about 8 edges per run of the binned form below).  The edge set must be
+ * symmetric (an undirected graph, as in the paper's F-Graph); then this equals
+ * pushing p(u)/deg(u) along every edge u -> v.  p is nv floats in memory space
+ * `mem`.  Where enough edges and iterations pay for it, the edges are first laid
+ * out by destination and source for the call, which takes 8 bytes an edge and
+ * about 20 per pair of a part (32768 destinations) and a bin (up to 8192 sources);
+ * the handle keeps that memory for later calls until cpma_trim, and the call does
+ * without when it cannot be had.
  */
 cpma_status cpma_fgraph_bfs(const cpma* set, uint32_t nv, uint32_t source, int symmetric, cpma_mem mem,
                             uint32_t* level, void* stream);

@@ -1707,7 +1707,7 @@ uint64_t apply_batch(cpma* s, const uint64_t* B, uint64_t kbound, bool insert, h
     PhaseMark ph = phase_begin(s, CPMA_PHASE_HEAVY, st);
     a.part = slots(mg.wide_grid, false);
     hipLaunchKernelGGL(k_merge_wave, dim3(mg.wide_grid), dim3(kWave), 0, st, a);
-    if (insert) {  // long insert slices, one wave each
+    if (insert) {  // long insert slices, a block each
       a.part = slots(hgrid_spill, false);
       hipLaunchKernelGGL(k_merge_heavy, dim3(hgrid_spill), dim3(kHeavyThreads), heavy_smem(s->S, kHeavyLds), st, a,
                          kHeavyLds, 1, giant_list(s, kbound));
@@ -2338,14 +2338,14 @@ static uint32_t ends_grid(const cpma* s, const QueryArgs& a, uint32_t per) {
   return lookup_grid(s, 2 * a.q, per);
 }
 
-// values: sum the values of key-value leaves instead of the keys.
 // Host queries up to this many skip the copies of pageable memory: the end kernel
 // reads the bounds from pinned memory (once, a cache line per 8 queries) and one
-// copy brings sums and counts back: 64 ranges after a small update, 135 -> 110 us
-// for the pair of updates and the ranges.  More queries are bound by other things,
-// and reading them over the host link would hold up the end kernel.
+// copy brings sums and counts back.  16 ranges of 3 keys 52 -> 29 us, 1024 83 -> 33.  It
+// still pays above (16384 130 -> 80, 65536 200 -> 160); the line is what the 64 KB of
+// pinned memory hold that every handle with updates has, 32 bytes a query.
 static constexpr uint64_t kPinnedQueries = 1024;
 
+// values: sum the values of key-value leaves instead of the keys.
 static cpma_status range_map_impl(const cpma* cs, const uint64_t* lo, const uint64_t* hi, uint64_t q, cpma_mem mem,
                                   uint64_t* sum, uint64_t* count, void* stream, bool values) {
   cpma* s = const_cast<cpma*>(cs);

@@ -9,8 +9,11 @@
 // load and walks its leaf in a chain of a dozen rounds, and a wave waits for the
 // longest of its 64 walks.  1e6 membership tests on 1e8 keys: 389 -> 200 us; the
 // partial end leaves of 1e6 ranges: 816 -> 423 us; get of 1e6 keys of a key-value
-// set (byte loads before): 727 -> 151 us.  Bound: VALU issue of the byte walk
-// (about 135 instructions per round).
+// set (byte loads before): 727 -> 151 us.  Walks that sum are bound by vector
+// instructions (about 135 per round); membership in a large set by its random 256-byte
+// reads (0.5 GB at 3.7 TB/s) and the head search (60 of the 200 us): a walk of a third
+// fewer instructions changed nothing.  In leaves of fewer bytes than a round, large
+// batches take a lane per lookup (lane_lookups).
 #pragma once
 #include "scan_lane.hpp"
 #include "update.hpp"

@@ -442,10 +442,11 @@ __device__ __forceinline__ void leaf_prefix_finish(const QueryArgs& a, const Lea
 
 // Interior visits, flattened over all queries.  When they outnumber the leaves,
 // every leaf is summed once into the prefixes above, a block taking one run of
-// leaves.  Otherwise waves take groups of consecutive visits, group g by wave g mod (number of waves): `chunk` steps of
-// 64 leaves, fewer when that would leave waves idle.  Part of a group: 32 visits,
-// two lanes each, so the wave's loads fall on neighbouring leaves, and the waves
-// running at the same time sweep one region of the leaf array together.  The
+// leaves.  Otherwise waves take groups of consecutive visits, group g by wave
+// g mod (number of waves): `chunk` steps of 64 leaves, fewer when that would leave
+// waves idle.  Part of a group: 64 visits with a lane each or 32 with two, so the
+// wave's loads fall on neighbouring leaves, and the waves running at the same time
+// sweep one region of the leaf array together.  The
 // query of a group's first visit is found by one binary search over the visit
 // offsets, with wave-uniform (scalar) loads; each lane then walks forward to its
 // own visit's query, and the next part continues from there.  Partial sums are

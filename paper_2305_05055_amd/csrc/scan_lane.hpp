@@ -1,14 +1,12 @@
-// Lane-per-leaf decoders for range_map and contains.
+// Per-lane pieces of the leaf decoders.
 //
 // A range query is a search followed by a scan (Section "Packed Memory Array",
 // "Design and operations").  Leaves strictly inside a query's leaf span hold only
-// keys of the range, so they need a sum and a count but no comparisons; the two
-// end leaves (and a point query's single leaf) compare every key.
-//
-// Each lane decodes a whole leaf on its own.  All lanes of a wave walk their
-// leaves one byte per step from offset 0, so their 16-byte chunk loads happen
-// in the same step (coalesced in time, no divergent stalls), and no cross-lane
-// operation is needed.
+// keys of the range, so they need a sum and a count but no comparisons: zf_chunk
+// decodes a lane's share of one, 16 bytes at a time.  leaf_sum_range walks a whole
+// leaf in one lane and compares every key, for the ends of ranges and membership in
+// small leaves; leaf_sum_fast sums one without comparisons and gives its last key,
+// for the resize.
 #pragma once
 #include "common.hpp"
 

@@ -409,7 +409,10 @@ constexpr uint64_t kMsdMaxKeys = kBktTarget << kMsdMaxBits;
 // Batches of 4097 to 2^18 keys split too, into 256 buckets of at most 1024 keys on
 // average, in tiles of 4096 keys and sorted by blocks of 256 threads: 1e5 keys 34 us
 // in eight launches and no wait for a copy, the radix passes and the removal of
-// repeats 58 in twelve.  Above 2^18 (up to the large split's size) the passes stay.
+// repeats 58 in twelve.  Below, the small batches' one-block preparation; from 2^18 to
+// the large split's size the passes stay, which is not their crossing: insert and delete
+// of 2^18 keys into 5e7 484 us split, of one more 565 with passes and 486 split, of 5e5
+// 661 and 563.  Low parts are 32 bits, so keys of more than 40 take the passes too.
 constexpr int kMidItems = 4;
 constexpr uint32_t kMidTile = kMsdThreads * kMidItems;
 constexpr uint64_t kMidMinKeys = 4097, kMidMaxKeys = 1ull << 18;
