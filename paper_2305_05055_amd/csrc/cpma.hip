@@ -125,6 +125,12 @@ int tree_height(uint64_t L) {
 // The instances of range_map's interior scan, by interior_kind.
 static decltype(&k_rm_words) const kInteriorScans[3] = {k_rm_interior<true>, k_rm_interior<false>, k_rm_words};
 
+// Whether a set's range queries use instance i: uncompressed sets scan words, plain
+// ones codes that are zero past `used`, key-value sets codes or, for values, words.
+static bool scans_with(const cpma_config& c, int i) {
+  return c.values ? i > 0 : i == (c.uncompressed ? 2 : 0);
+}
+
 struct cpma {
   int device = 0;
   int num_cus = 256;
@@ -1927,7 +1933,10 @@ static cpma_status build_impl(const uint64_t* keys, const uint64_t* vals, uint64
     s->num_cus = prop.multiProcessorCount;
     // the interior range scan runs one generation of blocks: every block
     // resident at once, so no block starts after the others have finished
+    // (only for the instances this set uses: a build of 1000 keys 287 us with all
+    // three, 271 with one)
     for (int i = 0; i < 3; i++) {
+      if (!scans_with(s->cfg, i)) continue;
       int per = 0;
       HIPCHK(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, kInteriorScans[i], 256, 0));
       // four at most: the end of the prefix pass costs every block
