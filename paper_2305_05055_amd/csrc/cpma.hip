@@ -2411,13 +2411,14 @@ static cpma_status range_map_impl(const cpma* cs, const uint64_t* lo, const uint
       ensure(s->qparts, 8 * nslots);
       qalg = s->qparts.as<unsigned long long>();
     }
-    hipLaunchKernelGGL(ends_kernel(a), dim3(egrid), dim3(256), 0, st, a, s->qfirst.as<uint64_t>(), s->qnvis.as<uint64_t>(), dsum, dcount, qalg, lp.ticket, per);
+    hipLaunchKernelGGL(ends_kernel(a), dim3(egrid), dim3(256), 0, st, a, s->qfirst.as<uint64_t>(),
+                       s->qnvis.as<uint64_t>(), dsum, dcount, qalg, lp.ticket, per);
     HIPCHK(hipGetLastError());
     if (q > kOwnScanQueries)
       scan<uint64_t>(s, s->qvoff.as<uint64_t>(), q, st, LoadFn<uint64_t>{s->qnvis.as<uint64_t>()});
     PhaseMark ps = phase_begin(s, CPMA_PHASE_RANGE_SCAN, st);
-    launch_interior(a, blocks, st, s->qvoff.as<uint64_t>(), s->qnvis.as<uint64_t>(), s->qfirst.as<uint64_t>(), s->cfg.range_chunk, dsum,
-                    dcount, qalg ? qalg + ewaves : qalg, lp);
+    launch_interior(a, blocks, st, s->qvoff.as<uint64_t>(), s->qnvis.as<uint64_t>(), s->qfirst.as<uint64_t>(),
+                    s->cfg.range_chunk, dsum, dcount, qalg ? qalg + ewaves : qalg, lp);
     HIPCHK(hipGetLastError());
     phase_end(s, ps, st, 32ull * q);
     phase_end(s, pq, st);
